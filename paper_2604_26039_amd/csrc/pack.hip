@@ -38,31 +38,66 @@ PackedLayout packed_layout(const ramp_shape &s)
 
 namespace {
 
-// src: [E][K][F] (F contiguous).  dst: [E][F/16][K/32][512] (+ dst_expert_stride between experts).
-// One lane writes one 16-byte chunk (8 consecutive k of one output row).
-__global__ __launch_bounds__(256) void pack_kernel(const uint16_t *__restrict__ src, uint16_t *__restrict__ dst, int E,
-                                                   int K, int F, size_t dst_expert_stride)
+// src: [E][K][F] (F contiguous) -> dst: [E][F/16][K/32][512] (+ dst_expert_stride between experts), all three matrices of
+// a layer in one launch.
+//
+// Bound by HBM: every weight is read once and written once.  A workgroup transposes one 128 (k) x 128 (feature) block:
+// 16-byte loads of 256-byte row pieces, eight of them in flight per lane (8 consecutive k of the same 8 features, so the
+// transposition to "8 consecutive k of one feature" stays inside the lane), then through LDS, where the block has the order
+// of its 32 output fragments, so that stores are whole runs of 4 KB (the four k-steps of a row block).  The 16-byte chunk
+// index inside a fragment is XOR-ed with its k-quarter: the eight writes of a lane then meet each bank no more often than the
+// linear reads do.  OLMoE-shaped layer (1.61 GB moved): 432 -> 302 us (5.3 TB/s; a large copy reaches 4.9), against one
+// lane gathering its chunk as eight 2-byte loads a row apart and three launches.
+struct PackPart {
+    const uint16_t *src;
+    uint16_t *dst;
+    int K, F;
+    size_t dst_expert_stride;
+    size_t first_block;  // blocks of the parts before this one
+};
+struct PackArgs {
+    PackPart part[3];
+    size_t total_blocks;
+};
+constexpr int kPackBlock = 128;
+
+__global__ __launch_bounds__(256) void pack_kernel(PackArgs a)
 {
-    const size_t chunks_per_expert = (size_t)K * F / 8;
-    const size_t total = chunks_per_expert * E;
-    for (size_t c = (size_t)blockIdx.x * blockDim.x + threadIdx.x; c < total; c += (size_t)gridDim.x * blockDim.x) {
-        const int e = (int)(c / chunks_per_expert);
-        const size_t ce = c % chunks_per_expert;
-        const int lane = (int)(ce % 64);
-        const size_t frag = ce / 64;
-        const int kst = K / 32;
-        const int ks = (int)(frag % kst);
-        const int rb = (int)(frag / kst);
-        const int f = packed_row_feature(rb, lane % 16);
-        const int k0 = ks * 32 + (lane / 16) * 8;
-        const uint16_t *s = src + (size_t)e * K * F + (size_t)k0 * F + f;
+    __shared__ uint4 lds[8 * 4 * 64];  // [row block][k-step][16-byte chunk]
+    const int t = threadIdx.x, c = t & 15, g = t >> 4;
+    for (size_t b = blockIdx.x; b < a.total_blocks; b += gridDim.x) {
+        const int which = b >= a.part[2].first_block ? 2 : (b >= a.part[1].first_block ? 1 : 0);
+        const PackPart &p = a.part[which];
+        const size_t bl = b - p.first_block;
+        const int nf = p.F / kPackBlock, nk = p.K / kPackBlock;
+        const int fb = (int)(bl % nf), kb = (int)(bl / nf % nk);
+        const size_t e = bl / nf / nk;
+        const uint16_t *s = p.src + (e * p.K + (size_t)(kb * kPackBlock + g * 8)) * p.F + (size_t)fb * kPackBlock + c * 8;
         union {
-            uint16_t h[8];
             uint4 v;
-        } u;
+            uint16_t h[8];
+        } in[8], o;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) u.h[j] = s[(size_t)j * F];
-        *reinterpret_cast<uint4 *>(dst + (size_t)e * dst_expert_stride + frag * kFragElems + (size_t)lane * 8) = u.v;
+        for (int i = 0; i < 8; ++i) in[i].v = *reinterpret_cast<const uint4 *>(s + (size_t)i * p.F);
+        const int ks = g >> 2, q = g & 3;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            // feature c*8 + j of the block -> row r of row block rb (inverse of packed_row_feature)
+            const int rb = (c >> 3) * 4 + (c & 1) * 2 + (j >> 2), r = ((c >> 1) & 3) * 4 + (j & 3);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) o.h[i] = in[i].h[j];
+            lds[(rb * 4 + ks) * 64 + q * 16 + (r ^ q)] = o.v;
+        }
+        __syncthreads();
+        uint16_t *d = p.dst + e * p.dst_expert_stride;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int x = t + 256 * i;  // chunk x % 64 of fragment (row block x / 256, k-step x / 64 % 4)
+            const int slot = x & 63;
+            const uint4 v = lds[(x & ~63) + (slot ^ (slot >> 4))];
+            *reinterpret_cast<uint4 *>(d + ((size_t)(fb * 8 + (x >> 8)) * (p.K / 32) + kb * 4) * kFragElems + (size_t)(x & 255) * 8) = v;
+        }
+        __syncthreads();
     }
 }
 
@@ -137,13 +172,14 @@ extern "C" int ramp_pack_weights(const ramp_shape *shape, const void *W_gate, co
     const PackedLayout L = packed_layout(s);
     uint16_t *dst = static_cast<uint16_t *>(packed);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const int grid = kNumCU * 8;
-    hipLaunchKernelGGL(pack_kernel, dim3(grid), dim3(256), 0, st, static_cast<const uint16_t *>(W_gate), dst, s.E, s.H,
-                       s.I, L.w1_expert_elems);
-    hipLaunchKernelGGL(pack_kernel, dim3(grid), dim3(256), 0, st, static_cast<const uint16_t *>(W_up),
-                       dst + L.up_offset_elems, s.E, s.H, s.I, L.w1_expert_elems);
-    hipLaunchKernelGGL(pack_kernel, dim3(grid), dim3(256), 0, st, static_cast<const uint16_t *>(W_down),
-                       dst + L.w2_base_elems, s.E, s.I, s.H, L.w2_expert_elems);
+    const size_t blocks = (size_t)s.E * (s.H / kPackBlock) * (s.I / kPackBlock);  // of one matrix
+    PackArgs a;
+    a.part[0] = PackPart{static_cast<const uint16_t *>(W_gate), dst, s.H, s.I, L.w1_expert_elems, 0};
+    a.part[1] = PackPart{static_cast<const uint16_t *>(W_up), dst + L.up_offset_elems, s.H, s.I, L.w1_expert_elems, blocks};
+    a.part[2] = PackPart{static_cast<const uint16_t *>(W_down), dst + L.w2_base_elems, s.I, s.H, L.w2_expert_elems, 2 * blocks};
+    a.total_blocks = 3 * blocks;
+    const size_t grid = a.total_blocks < ((size_t)1 << 20) ? a.total_blocks : ((size_t)1 << 20);
+    hipLaunchKernelGGL(pack_kernel, dim3((unsigned)grid), dim3(256), 0, st, a);
     return check_launch("pack_kernel");
 }
 
