@@ -88,6 +88,21 @@ __device__ __forceinline__ uint32_t e4m3_of_f32(float v)
     return sign | (uint32_t)__builtin_rintf(f);
 }
 
+// Four of them, in one 32-bit word, by the conversion instruction of the chip (v_cvt_pk_fp8_f32): the same rounding, ties
+// included; it turns values past 448 into NaN, so they are saturated first.
+__device__ __forceinline__ uint32_t e4m3x4_of_f32(const float *v)
+{
+    float s[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t u = __builtin_bit_cast(uint32_t, v[i]);
+        const uint32_t a = u & 0x7fffffffu;
+        s[i] = __builtin_bit_cast(float, (a > 0x43e00000u ? 0x43e00000u : a) | (u & 0x80000000u));
+    }
+    int w = __builtin_amdgcn_cvt_pk_fp8_f32(s[0], s[1], 0, false);
+    return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(s[2], s[3], w, true);
+}
+
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t h) { return __builtin_bit_cast(float, h << 16); }
 
 // ---- quantisers -----------------------------------------------------------------------------------------------
@@ -122,54 +137,78 @@ __global__ __launch_bounds__(256) void quant_rows_kernel(const uint16_t *__restr
     }
 }
 
-// One workgroup per 128 x 128 block of src [E][K][F] (F contiguous): scale byte into sb[e][f block][k block].
-__global__ __launch_bounds__(256) void block_scale_kernel(const uint16_t *__restrict__ src, int K, int F,
-                                                          uint8_t *__restrict__ sb, size_t sb_expert_stride, int stride)
-{
-    __shared__ float red[4];
-    const int kb = blockIdx.x, fb = blockIdx.y, e = blockIdx.z;
-    const int ff = threadIdx.x & 127, k0 = threadIdx.x >> 7;
-    const uint16_t *p = src + (size_t)e * K * F + (size_t)(kb * kGroup) * F + (size_t)fb * kGroup + ff;
-    float amax = 0.f;
-    for (int kk = k0; kk < kGroup; kk += 2) amax = fmaxf(amax, fabsf(bf16_bits_to_f32(p[(size_t)kk * F])));
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) amax = fmaxf(amax, __shfl_xor(amax, d));
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = amax;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        amax = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-        sb[(size_t)e * sb_expert_stride + (size_t)fb * stride + kb] = (uint8_t)e8m0_of_amax(amax);
-    }
-}
+// Weight quantiser and packer: src [E][K][F] bf16 (F contiguous) -> E4M3 fragments [E][F/16][K/128][2 KB] and the scale byte
+// of every 128 x 128 block, all three matrices of a layer in one launch.
+//
+// Bound by HBM: a weight is two bytes read and one written.  A workgroup owns one scale block and keeps it in registers
+// between the two uses, the block maximum and the codes, so the weights are read once: eight 16-byte loads in flight per lane
+// (8 consecutive k of the same 8 features, 256-byte row pieces).  The codes leave through LDS in fragment order, 2 KB runs per
+// 16-row block.  Qwen3-shaped layer (1.81 GB moved): 1352 -> 334 us (5.4 TB/s; a large copy reaches 4.9), against a
+// maximum pass and a code pass per matrix that both gathered 2-byte values.
+struct QuantPackPart {
+    const uint16_t *src;
+    uint8_t *dst, *sb;
+    int K, F;
+    size_t dst_expert_stride;
+    int sb_stride;
+    size_t first_block;  // blocks of the parts before this one
+};
+struct QuantPackArgs {
+    QuantPackPart part[3];
+    size_t sb_expert_stride, total_blocks;
+};
 
-// src [E][K][F] bf16 -> packed E4M3 fragments [E][F/16][K/128][2 KB]; one lane writes one 16-byte chunk
-// (16 consecutive k of one weight row).
-__global__ __launch_bounds__(256) void pack_fp8_kernel(const uint16_t *__restrict__ src, uint8_t *__restrict__ dst, int E, int K,
-                                                       int F, size_t dst_expert_stride, const uint8_t *__restrict__ sb,
-                                                       size_t sb_expert_stride, int stride)
+__global__ __launch_bounds__(256) void quant_pack_kernel(QuantPackArgs a)
 {
-    const size_t chunks_per_expert = (size_t)K * F / 16;
-    const size_t total = chunks_per_expert * E;
-    const int kt = K / kGroup;
-    for (size_t c = (size_t)blockIdx.x * blockDim.x + threadIdx.x; c < total; c += (size_t)gridDim.x * blockDim.x) {
-        const int e = (int)(c / chunks_per_expert);
-        const size_t ce = c % chunks_per_expert;
-        const int lane = (int)(ce % 64);
-        const int h = (int)((ce / 64) % 2);
-        const size_t frag = ce / 128;
-        const int ks = (int)(frag % kt);
-        const int rb = (int)(frag / kt);
-        const int f = packed_row_feature(rb, lane % 16);
-        const int k0 = ks * kGroup + (lane / 16) * 32 + h * 16;
-        const float inv = inv_scale_of(sb[(size_t)e * sb_expert_stride + (size_t)(f / kGroup) * stride + ks]);
-        const uint16_t *s = src + (size_t)e * K * F + (size_t)k0 * F + f;
+    __shared__ __attribute__((aligned(16))) uint8_t lds[8 * 2048];  // [row block][half][lane][16 bytes]
+    __shared__ float red[4];
+    const int t = threadIdx.x, c = t & 15, g = t >> 4;
+    for (size_t b = blockIdx.x; b < a.total_blocks; b += gridDim.x) {
+        const int which = b >= a.part[2].first_block ? 2 : (b >= a.part[1].first_block ? 1 : 0);
+        const QuantPackPart &p = a.part[which];
+        const size_t bl = b - p.first_block;
+        const int nf = p.F / kGroup, nk = p.K / kGroup;
+        const int fb = (int)(bl % nf), kb = (int)(bl / nf % nk);
+        const size_t e = bl / nf / nk;
+        const uint16_t *s = p.src + (e * p.K + (size_t)(kb * kGroup + g * 8)) * p.F + (size_t)fb * kGroup + c * 8;
         union {
-            uint8_t b[16];
             uint4 v;
-        } u;
+            uint16_t h[8];
+        } in[8];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) u.b[j] = (uint8_t)e4m3_of_f32(bf16_bits_to_f32(s[(size_t)j * F]) * inv);
-        *reinterpret_cast<uint4 *>(dst + (size_t)e * dst_expert_stride + frag * 2048 + (size_t)h * 1024 + (size_t)lane * 16) = u.v;
+        for (int i = 0; i < 8; ++i) in[i].v = *reinterpret_cast<const uint4 *>(s + (size_t)i * p.F);
+        float amax = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) amax = fmaxf(amax, fabsf(bf16_bits_to_f32(in[i].h[j])));
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) amax = fmaxf(amax, __shfl_xor(amax, d));
+        if ((t & 63) == 0) red[t >> 6] = amax;
+        __syncthreads();
+        const uint32_t sbyte = e8m0_of_amax(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])));
+        const float inv = inv_scale_of(sbyte);
+        if (t == 0) p.sb[e * a.sb_expert_stride + (size_t)fb * p.sb_stride + kb] = (uint8_t)sbyte;
+        // k = 8*g + i of the block: quarter g/4, half g/2 % 2, bytes 8*(g % 2) + i of the 16-byte piece
+        uint8_t *piece = lds + ((g >> 1) & 1) * 1024 + (g >> 2) * 256 + (g & 1) * 8;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            // feature c*8 + j of the block -> row r of row block rb (inverse of packed_row_feature)
+            const int rb = (c >> 3) * 4 + (c & 1) * 2 + (j >> 2), r = ((c >> 1) & 3) * 4 + (j & 3);
+            float v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = bf16_bits_to_f32(in[i].h[j]) * inv;
+            *reinterpret_cast<uint2 *>(piece + rb * 2048 + r * 16) = make_uint2(e4m3x4_of_f32(v), e4m3x4_of_f32(v + 4));
+        }
+        __syncthreads();
+        uint8_t *d = p.dst + e * p.dst_expert_stride;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int x = t + 256 * i;  // 16-byte piece x % 128 of the fragment of row block x / 128
+            *reinterpret_cast<uint4 *>(d + ((size_t)(fb * 8 + (x >> 7)) * nk + kb) * 2048 + (size_t)(x & 127) * 16) =
+                *reinterpret_cast<const uint4 *>(lds + x * 16);
+        }
+        __syncthreads();
     }
 }
 
@@ -595,26 +634,18 @@ extern "C" int ramp_fp8_pack_weights(const ramp_shape *shape, const void *W_gate
     hipStream_t st = static_cast<hipStream_t>(stream);
     uint8_t *dst = static_cast<uint8_t *>(packed);
     uint8_t *sc = dst + L.scale_base;
-    struct Part {
-        const void *src;
-        int K, F;
-        size_t dst_off, dst_stride, sc_off;
-        int stride;
-    } parts[3] = {{W_gate, s.H, s.I, 0, L.w1_expert_bytes, L.scale_g, L.stride1},
-                  {W_up, s.H, s.I, L.up_offset_bytes, L.w1_expert_bytes, L.scale_u, L.stride1},
-                  {W_down, s.I, s.H, L.w2_base_bytes, L.w2_expert_bytes, L.scale_d, L.stride2}};
-    for (const Part &p : parts) {
-        const uint16_t *src = static_cast<const uint16_t *>(p.src);
-        hipLaunchKernelGGL(block_scale_kernel, dim3(p.K / kGroup, p.F / kGroup, s.E), dim3(256), 0, st, src, p.K, p.F,
-                           sc + p.sc_off, L.scale_expert_bytes, p.stride);
-        if (int rc = check_launch("block_scale_kernel")) return rc;
-        const size_t chunks = (size_t)s.E * p.K * p.F / 16;
-        size_t blocks = (chunks + 255) / 256;
-        if (blocks > (size_t)kNumCU * 64) blocks = (size_t)kNumCU * 64;
-        hipLaunchKernelGGL(pack_fp8_kernel, dim3((unsigned)blocks), dim3(256), 0, st, src, dst + p.dst_off, s.E, p.K, p.F,
-                           p.dst_stride, sc + p.sc_off, L.scale_expert_bytes, p.stride);
-        if (int rc = check_launch("pack_fp8_kernel")) return rc;
-    }
+    const size_t blocks = (size_t)s.E * (s.H / kGroup) * (s.I / kGroup);  // of one matrix
+    QuantPackArgs a;
+    a.part[0] = QuantPackPart{static_cast<const uint16_t *>(W_gate), dst, sc + L.scale_g, s.H, s.I, L.w1_expert_bytes, L.stride1, 0};
+    a.part[1] = QuantPackPart{static_cast<const uint16_t *>(W_up), dst + L.up_offset_bytes, sc + L.scale_u, s.H, s.I,
+                              L.w1_expert_bytes, L.stride1, blocks};
+    a.part[2] = QuantPackPart{static_cast<const uint16_t *>(W_down), dst + L.w2_base_bytes, sc + L.scale_d, s.I, s.H,
+                              L.w2_expert_bytes, L.stride2, 2 * blocks};
+    a.sb_expert_stride = L.scale_expert_bytes;
+    a.total_blocks = 3 * blocks;
+    const size_t grid = a.total_blocks < ((size_t)1 << 20) ? a.total_blocks : ((size_t)1 << 20);
+    hipLaunchKernelGGL(quant_pack_kernel, dim3((unsigned)grid), dim3(256), 0, st, a);
+    if (int rc = check_launch("quant_pack_kernel")) return rc;
     return RAMP_OK;
 }
 
