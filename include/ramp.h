@@ -176,7 +176,8 @@ int ramp_fused_moe_workspace_layout(const ramp_shape *shape, const ramp_config *
  * accumulation is fp32 in the matrix pipe (v_mfma_scale_f32_16x16x128_f8f6f4, which applies the block scales).
  * ramp_fp8_pack_weights quantises bf16 boundary-layout weights (as ramp_pack_weights takes them) on the device and
  * lays the codes out in MFMA fragment order, followed by the scale bytes; outside the timed path.
- * The FP8 tile family is enumerated apart from the bf16 one (mode bit 0x10000, bk = 128); its configurations
+ * The FP8 tile family is enumerated apart from the bf16 one (mode bit 0x10000, bk = 128; 0x400 with it = the persistent
+ * ping-pong kernels, for H and I of at least 384); its configurations
  * work with ramp_config_ntiles, ramp_grid, ramp_cost_model_fit / select like any other. */
 int ramp_fp8_num_configs(const ramp_shape *shape);
 int ramp_fp8_get_config(const ramp_shape *shape, int idx, ramp_config *out);

@@ -10,6 +10,7 @@
 //
 // Path:  align(bm) -> quantise X per token and 128-group -> up-projection (FP8 MFMA, fp32 accumulate) + SwiGLU ->
 // A in bf16, row-major -> quantise A -> down-projection (FP8 MFMA) x router weight -> per-pair rows -> combine.
+// The persistent kernels (moe_fp8_pingpong.h) quantise A in the epilogue of their up-projection instead.
 //
 // Layouts.  A "fragment" here is 16 rows x 128 k-values of E4M3 = 2 KB: the operand of one MFMA, lane l holding
 // row l%16 and the 32 consecutive k-values 32*(l/16) ...  It is stored as two 1 KB halves, half h holding bytes
@@ -19,13 +20,9 @@
 //   scale bytes:    [E][gate, up, down][feature block of 128][k block, row stride padded to 4 bytes]
 //   quantised activations: codes row-major [rows, K], scale bytes [rows][K/128 padded to 4]
 // Which feature sits in row r of row block rb is the interleave of the bf16 layout (packed_row_feature).
-#include "moe_gemm.h"
+#include "moe_fp8_pingpong.h"
 
 namespace ramp {
-
-typedef int intx8 __attribute__((ext_vector_type(8)));
-typedef int intx4 __attribute__((ext_vector_type(4)));
-
 namespace {
 
 constexpr int kGroup = 128;  // k-values per scale block
@@ -55,55 +52,6 @@ Fp8Layout fp8_layout(const ramp_shape &s)
     L.total_bytes = align_up(L.scale_base + (size_t)s.E * L.scale_expert_bytes, 256);
     return L;
 }
-
-// ---- number formats -------------------------------------------------------------------------------------------
-
-// E8M0 byte of the smallest power of two s with amax / s <= 448 (448 = 1.75 * 2^8): from the fp32 bits of amax.
-__device__ __forceinline__ uint32_t e8m0_of_amax(float amax)
-{
-    const uint32_t u = __builtin_bit_cast(uint32_t, amax) & 0x7fffffffu;
-    if (u == 0u || u >= 0x7f800000u) return 127u;  // all-zero block (or not finite): scale 1
-    const int field = (int)(u >> 23);
-    const int b = field - ((u & 0x7fffffu) <= 0x600000u ? 8 : 7);
-    return (uint32_t)(b < 0 ? 0 : (b > 254 ? 254 : b));
-}
-// 2^(127-b): the factor that brings a block into the E4M3 range.
-__device__ __forceinline__ float inv_scale_of(uint32_t b) { return __builtin_bit_cast(float, (254u - b) << 23); }
-
-// fp32 -> E4M3 code: round to nearest, ties to even, saturate at 448.
-__device__ __forceinline__ uint32_t e4m3_of_f32(float v)
-{
-    const uint32_t u = __builtin_bit_cast(uint32_t, v);
-    const uint32_t sign = (u >> 24) & 0x80u;
-    uint32_t a = u & 0x7fffffffu;
-    if (a > 0x43e00000u) a = 0x43e00000u;  // 448
-    if (a >= 0x3c800000u) {                // >= 2^-6: normal code; keep 3 mantissa bits
-        const uint32_t r = a + 0x7ffffu + ((a >> 20) & 1u);
-        uint32_t code = (r >> 20) - (120u << 3);
-        if (code > 0x7eu) code = 0x7eu;
-        return sign | code;
-    }
-    // subnormal range: multiples of 2^-9 (8 of them reach the smallest normal value, code 8)
-    const float f = __builtin_bit_cast(float, a) * 512.0f;
-    return sign | (uint32_t)__builtin_rintf(f);
-}
-
-// Four of them, in one 32-bit word, by the conversion instruction of the chip (v_cvt_pk_fp8_f32): the same rounding, ties
-// included; it turns values past 448 into NaN, so they are saturated first.
-__device__ __forceinline__ uint32_t e4m3x4_of_f32(const float *v)
-{
-    float s[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint32_t u = __builtin_bit_cast(uint32_t, v[i]);
-        const uint32_t a = u & 0x7fffffffu;
-        s[i] = __builtin_bit_cast(float, (a > 0x43e00000u ? 0x43e00000u : a) | (u & 0x80000000u));
-    }
-    int w = __builtin_amdgcn_cvt_pk_fp8_f32(s[0], s[1], 0, false);
-    return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(s[2], s[3], w, true);
-}
-
-__device__ __forceinline__ float bf16_bits_to_f32(uint32_t h) { return __builtin_bit_cast(float, h << 16); }
 
 // ---- quantisers -----------------------------------------------------------------------------------------------
 
@@ -431,6 +379,7 @@ struct Fp8Kernel {
     ramp_config cfg;
     int lds_bytes, waves_per_cu_limit;
     void (*launch)(int stage, const GemmArgs &, const Fp8Args &, hipStream_t);
+    void (*launch_pp)(int stage, const GemmArgs &, const Fp8PingPongArgs &, hipStream_t);  // persistent family, else NULL
 };
 
 template <int BM, int BN, int WM, int WN, int NSTAGE>
@@ -458,6 +407,20 @@ Fp8Kernel make_fp8()
     k.waves_per_cu_limit = by_lds < by_regs ? by_lds : by_regs;
     if (k.waves_per_cu_limit < 1) k.waves_per_cu_limit = 1;
     k.launch = &launch_fp8<BM, BN, WM, WN, NSTAGE>;
+    k.launch_pp = nullptr;
+    return k;
+}
+
+template <int NH>
+Fp8Kernel make_fp8_pingpong()
+{
+    using PT = Fp8PingPongTraits<1, NH>;
+    Fp8Kernel k;
+    k.cfg = ramp_config{PT::BM, PT::BN, kGroup, 8, PT::NW, 1 | kModePingPong | kModeFp8};
+    k.lds_bytes = PT::LDS_BYTES;
+    k.waves_per_cu_limit = 1;
+    k.launch = nullptr;
+    k.launch_pp = &launch_fp8_pingpong<NH>;
     return k;
 }
 
@@ -475,6 +438,8 @@ const Fp8Kernel *fp8_kernels(int *n)
 #define X(BM, BN, WM, WN, NS) make_fp8<BM, BN, WM, WN, NS>(),
         RAMP_FP8_CONFIGS(X)
 #undef X
+        make_fp8_pingpong<1>(),
+        make_fp8_pingpong<2>(),
     };
     *n = (int)(sizeof(table) / sizeof(table[0]));
     return table;
@@ -486,6 +451,11 @@ bool fp8_valid_for_shape(const Fp8Kernel &k, const ramp_shape &s)
     if ((2 * s.I) % k.cfg.bn || s.H % k.cfg.bn) return false;
     const size_t cap = ramp_align_capacity(s.T, s.k, s.E, k.cfg.bm);
     if ((cap + 16) * (size_t)s.I >= (1ull << 32) || (size_t)s.T * s.H >= (1ull << 32)) return false;
+    if (k.launch_pp) {
+        // its load stream runs two slices ahead, across one tile boundary at most; 32-bit offsets inside an expert
+        constexpr int least = Fp8PingPongTraits<1, 1>::MIN_SLICES;
+        if (s.H / kGroup < least || s.I / kGroup < least || 2ull * s.I * s.H >= (1ull << 32)) return false;
+    }
     return true;
 }
 
@@ -502,8 +472,9 @@ const Fp8Kernel *find_fp8(const ramp_config &c)
 }
 
 struct Fp8Workspace {
-    size_t sorted, tile_expert, tile_rows, counts, meta, align_ws, xq, xs, a_buf, aq, as, y_buf, total;
+    size_t sorted, tile_expert, tile_rows, counts, meta, slot_w, align_ws, xq, xs, a_buf, aq, as, y_buf, total;
     size_t cap, align_ws_bytes;
+    int xs_stride, as_stride;  // scale bytes per row: the persistent kernels read them 16 at a time
 };
 Fp8Workspace fp8_workspace(const ramp_shape &s, const ramp_config &c)
 {
@@ -520,26 +491,30 @@ Fp8Workspace fp8_workspace(const ramp_shape &s, const ramp_config &c)
     w.tile_rows = take((w.cap / (size_t)c.bm) * 4);
     w.counts = take((size_t)s.E * 4);
     w.meta = take(16);
+    const bool pp = (c.mode & kModePingPong) != 0;
+    w.slot_w = pp ? take(w.cap * 4) : off;
     w.align_ws_bytes = ramp_align_workspace_bytes(s.T, s.k, s.E);
     w.align_ws = take(w.align_ws_bytes);
+    w.xs_stride = pp ? (int)align_up(s.H / kGroup, 16) : scale_stride(s.H);
+    w.as_stride = pp ? (int)align_up(s.I / kGroup, 16) : scale_stride(s.I);
     w.xq = take((size_t)s.T * s.H);
-    w.xs = take((size_t)s.T * scale_stride(s.H));
-    w.a_buf = take(w.cap * (size_t)s.I * 2);
+    w.xs = take((size_t)s.T * w.xs_stride);
+    w.a_buf = pp ? off : take(w.cap * (size_t)s.I * 2);  // the persistent up-projection writes the codes itself
     w.aq = take(w.cap * (size_t)s.I);
-    w.as = take(w.cap * (size_t)scale_stride(s.I));
+    w.as = take(w.cap * (size_t)w.as_stride);
     w.y_buf = take((size_t)s.T * s.k * s.H * 4);
     w.total = off;
     return w;
 }
 
-int launch_quant_rows(const uint16_t *src, int rows, int K, uint8_t *codes, uint8_t *sb, const int32_t *n_rows_dev,
+int launch_quant_rows(const uint16_t *src, int rows, int K, uint8_t *codes, uint8_t *sb, int sb_stride, const int32_t *n_rows_dev,
                       const int32_t *pred, int pred_value, hipStream_t st)
 {
     if (rows <= 0) return RAMP_OK;
     const size_t groups = (size_t)rows * (K / kGroup);
     size_t blocks = (groups + 3) / 4;
     if (blocks > (size_t)kNumCU * 32) blocks = (size_t)kNumCU * 32;
-    hipLaunchKernelGGL(quant_rows_kernel, dim3((unsigned)blocks), dim3(256), 0, st, src, rows, K, codes, sb, scale_stride(K),
+    hipLaunchKernelGGL(quant_rows_kernel, dim3((unsigned)blocks), dim3(256), 0, st, src, rows, K, codes, sb, sb_stride,
                        n_rows_dev, pred, pred_value);
     return check_launch("quant_rows_kernel");
 }
@@ -656,7 +631,7 @@ extern "C" int ramp_fp8_quantize_rows(const void *src, int rows, int K, void *co
         return RAMP_EINVAL;
     }
     return launch_quant_rows(static_cast<const uint16_t *>(src), rows, K, static_cast<uint8_t *>(codes),
-                             static_cast<uint8_t *>(scales), nullptr, nullptr, 0, static_cast<hipStream_t>(stream));
+                             static_cast<uint8_t *>(scales), scale_stride(K), nullptr, nullptr, 0, static_cast<hipStream_t>(stream));
 }
 
 extern "C" size_t ramp_fused_moe_fp8_workspace_bytes(const ramp_shape *shape, const ramp_config *cfg)
@@ -711,10 +686,12 @@ extern "C" int ramp_fused_moe_fp8(const ramp_shape *shape, const ramp_config *cf
     uint8_t *aq = reinterpret_cast<uint8_t *>(base + w.aq), *as = reinterpret_cast<uint8_t *>(base + w.as);
     float *y_buf = reinterpret_cast<float *>(base + w.y_buf);
 
+    AlignSlotWeights sw = {nullptr, nullptr};
+    if (k->launch_pp) sw = AlignSlotWeights{topk_w, reinterpret_cast<float *>(base + w.slot_w)};
     if (int rc = launch_align(topk_ids, s.T, s.k, s.E, cfg->bm, sorted, tile_expert, tile_rows, counts, meta, base + w.align_ws,
-                              w.align_ws_bytes, st))
+                              w.align_ws_bytes, st, nullptr, 0, sw))
         return rc;
-    if (int rc = launch_quant_rows(static_cast<const uint16_t *>(X), s.T, s.H, xq, xs, nullptr, nullptr, 0, st)) return rc;
+    if (int rc = launch_quant_rows(static_cast<const uint16_t *>(X), s.T, s.H, xq, xs, w.xs_stride, nullptr, nullptr, 0, st)) return rc;
 
     const Fp8Layout L = fp8_layout(s);
     const uint8_t *packed = static_cast<const uint8_t *>(packed_fp8);
@@ -733,6 +710,44 @@ extern "C" int ramp_fused_moe_fp8(const ramp_shape *shape, const ramp_config *cf
     g.topk = s.k;
     g.m_tiles_cap = (int)(w.cap / (size_t)cfg->bm);
     g.group_m_req = 0;
+
+    if (k->launch_pp) {
+        g.slot_w = sw.slot_w;
+        Fp8PingPongArgs p = {};
+        // up-projection + SwiGLU + re-quantisation
+        p.act_q = xq;
+        p.act_scale = xs;
+        p.act_stride = w.xs_stride;
+        p.wq = packed;
+        p.expert_stride = L.w1_expert_bytes;
+        p.up_offset = (uint32_t)L.up_offset_bytes;
+        p.wscale = packed + L.scale_base + L.scale_g;
+        p.wscale_expert_stride = L.scale_expert_bytes;
+        p.wscale_up_offset = (uint32_t)(L.scale_u - L.scale_g);
+        p.w_stride = L.stride1;
+        p.aq_out = aq;
+        p.as_out = as;
+        p.as_stride = w.as_stride;
+        g.K = s.H;
+        g.F = s.I;
+        g.n_tiles = 2 * s.I / cfg->bn;
+        k->launch_pp(1, g, p, st);
+        if (int rc = check_launch("moe_fp8_pingpong_kernel<1>")) return rc;
+        // down-projection
+        p.act_q = aq;
+        p.act_scale = as;
+        p.act_stride = w.as_stride;
+        p.wq = packed + L.w2_base_bytes;
+        p.expert_stride = L.w2_expert_bytes;
+        p.wscale = packed + L.scale_base + L.scale_d;
+        p.w_stride = L.stride2;
+        g.K = s.I;
+        g.F = s.H;
+        g.n_tiles = s.H / cfg->bn;
+        k->launch_pp(2, g, p, st);
+        if (int rc = check_launch("moe_fp8_pingpong_kernel<2>")) return rc;
+        return launch_combine(y_buf, g.y_bf16, topk_ids, s.T, s.k, s.E, s.H, static_cast<uint16_t *>(out), st);
+    }
 
     Fp8Args f = {};
     // up-projection + SwiGLU
@@ -753,7 +768,7 @@ extern "C" int ramp_fused_moe_fp8(const ramp_shape *shape, const ramp_config *cf
     if (int rc = check_launch("moe_fp8_kernel<1>")) return rc;
 
     // the activation, per slot and 128 features; rows past the padded length of this call are skipped
-    if (int rc = launch_quant_rows(a_buf, (int)w.cap, s.I, aq, as, meta, nullptr, 0, st)) return rc;
+    if (int rc = launch_quant_rows(a_buf, (int)w.cap, s.I, aq, as, w.as_stride, meta, nullptr, 0, st)) return rc;
 
     // down-projection
     f.act_q = aq;

@@ -327,8 +327,8 @@ extern "C" int ramp_config_rounds(const ramp_shape *shape, const ramp_config *cf
         int gm = 1, gn = 1;
         // only the persistent kernels walk the map with a fixed set of workgroups; the others are dispatched
         // tile by tile as compute units free up
-        if ((cfg->mode & kModePingPong) && !(cfg->mode & kModeFp8)) xcd_block_shape(nt[s], group_m_of_mode(cfg->mode), &gm, &gn);
-        out[2 * s] = (cfg->mode & kModePingPong) && !(cfg->mode & kModeFp8) ? 8 * gm : 1;
+        if (cfg->mode & kModePingPong) xcd_block_shape(nt[s], group_m_of_mode(cfg->mode), &gm, &gn);
+        out[2 * s] = (cfg->mode & kModePingPong) ? 8 * gm : 1;
         out[2 * s + 1] = nt[s];
     }
     return RAMP_OK;
