@@ -10,7 +10,8 @@
 //
 // Path:  align(bm) -> quantise X per token and 128-group -> up-projection (FP8 MFMA, fp32 accumulate) + SwiGLU ->
 // A in bf16, row-major -> quantise A -> down-projection (FP8 MFMA) x router weight -> per-pair rows -> combine.
-// The persistent kernels (moe_fp8_pingpong.h) quantise A in the epilogue of their up-projection instead.
+// The persistent kernels (moe_fp8_pingpong.h) quantise A in the epilogue of their up-projection instead; the weight-streaming
+// ones (moe_fp8_stream.h) quantise both token operands in registers as they load them, and need neither pass.
 //
 // Layouts.  A "fragment" here is 16 rows x 128 k-values of E4M3 = 2 KB: the operand of one MFMA, lane l holding
 // row l%16 and the 32 consecutive k-values 32*(l/16) ...  It is stored as two 1 KB halves, half h holding bytes
@@ -21,6 +22,7 @@
 //   quantised activations: codes row-major [rows, K], scale bytes [rows][K/128 padded to 4]
 // Which feature sits in row r of row block rb is the interleave of the bf16 layout (packed_row_feature).
 #include "moe_fp8_pingpong.h"
+#include "moe_fp8_stream.h"
 
 namespace ramp {
 namespace {
@@ -380,6 +382,8 @@ struct Fp8Kernel {
     int lds_bytes, waves_per_cu_limit;
     void (*launch)(int stage, const GemmArgs &, const Fp8Args &, hipStream_t);
     void (*launch_pp)(int stage, const GemmArgs &, const Fp8PingPongArgs &, hipStream_t);  // persistent family, else NULL
+    void (*launch_stream)(int stage, const GemmArgs &, const Fp8StreamArgs &, hipStream_t);  // weight-streaming family
+    void (*launch_decode_up)(const GemmArgs &, const Fp8StreamArgs &, const DecodeArgs &, hipStream_t);  // its two-launch form
 };
 
 template <int BM, int BN, int WM, int WN, int NSTAGE>
@@ -398,7 +402,7 @@ template <int BM, int BN, int WM, int WN, int NSTAGE>
 Fp8Kernel make_fp8()
 {
     using TT = TileTraits<BM, BN, 64, WM, WN, NSTAGE>;
-    Fp8Kernel k;
+    Fp8Kernel k = {};
     k.cfg = ramp_config{BM, BN, kGroup, WM * WN, NSTAGE, (WM - 1) | kModeFp8};
     k.lds_bytes = TT::LDS_BYTES;
     // workgroups per compute unit: LDS, and one wavefront per SIMD for the large register tiles
@@ -407,7 +411,6 @@ Fp8Kernel make_fp8()
     k.waves_per_cu_limit = by_lds < by_regs ? by_lds : by_regs;
     if (k.waves_per_cu_limit < 1) k.waves_per_cu_limit = 1;
     k.launch = &launch_fp8<BM, BN, WM, WN, NSTAGE>;
-    k.launch_pp = nullptr;
     return k;
 }
 
@@ -415,14 +418,40 @@ template <int NH>
 Fp8Kernel make_fp8_pingpong()
 {
     using PT = Fp8PingPongTraits<1, NH>;
-    Fp8Kernel k;
+    Fp8Kernel k = {};
     k.cfg = ramp_config{PT::BM, PT::BN, kGroup, 8, PT::NW, 1 | kModePingPong | kModeFp8};
     k.lds_bytes = PT::LDS_BYTES;
     k.waves_per_cu_limit = 1;
-    k.launch = nullptr;
     k.launch_pp = &launch_fp8_pingpong<NH>;
     return k;
 }
+
+template <int BM, int FBW, int WF, int WK, int U, bool DECODE>
+Fp8Kernel make_fp8_stream()
+{
+    using ST = Fp8StreamTraits<BM, FBW, WF, WK, U>;
+    Fp8Kernel k = {};
+    k.cfg = ramp_config{BM, ST::BN, kGroup, WF * WK, 2 * U, kModeStream | WK | kModeFp8 | (DECODE ? kModeDecode : 0)};
+    k.lds_bytes = ST::RED_FLOATS * 4;
+    // 16 wavefronts per compute unit while two register batches take up to 128 registers, 8 beyond that
+    k.waves_per_cu_limit = (FBW == 2 && ST::NB * U == 1 ? 16 : 8) / (WF * WK);
+    k.launch_stream = &launch_fp8_stream<BM, FBW, WF, WK, U>;
+    if constexpr (DECODE) k.launch_decode_up = &launch_fp8_decode_up<BM, FBW, WF, WK, U>;
+    return k;
+}
+
+// The weight-streaming tiles: X(bm, FBW, WF, WK, U), bn = 16 * FBW * WF; those of RAMP_FP8_DECODE_CONFIGS run calls of at most
+// 64 pairs (k dividing 16) in two launches.  Measured and left out, never the fastest of 21 batches of the five shapes of the
+// tests: bm 8, 32-row tiles of two weight blocks, U = 2 with WK = 4.
+#define RAMP_FP8_STREAM_CONFIGS(X) \
+    X(16, 2, 1, 4, 1)              \
+    X(16, 2, 4, 2, 1)              \
+    X(16, 4, 2, 2, 1)              \
+    X(16, 2, 2, 2, 2)              \
+    X(32, 4, 2, 2, 1)
+#define RAMP_FP8_DECODE_CONFIGS(X) \
+    X(16, 2, 1, 8, 1)              \
+    X(16, 2, 2, 4, 1)
 
 // The FP8 tile family: X(bm, bn, WM, WN, NSTAGE), bk = 128.
 #define RAMP_FP8_CONFIGS(X) \
@@ -440,6 +469,12 @@ const Fp8Kernel *fp8_kernels(int *n)
 #undef X
         make_fp8_pingpong<1>(),
         make_fp8_pingpong<2>(),
+#define X(BM, FBW, WF, WK, U) make_fp8_stream<BM, FBW, WF, WK, U, false>(),
+        RAMP_FP8_STREAM_CONFIGS(X)
+#undef X
+#define X(BM, FBW, WF, WK, U) make_fp8_stream<BM, FBW, WF, WK, U, true>(),
+        RAMP_FP8_DECODE_CONFIGS(X)
+#undef X
     };
     *n = (int)(sizeof(table) / sizeof(table[0]));
     return table;
@@ -451,12 +486,21 @@ bool fp8_valid_for_shape(const Fp8Kernel &k, const ramp_shape &s)
     if ((2 * s.I) % k.cfg.bn || s.H % k.cfg.bn) return false;
     const size_t cap = ramp_align_capacity(s.T, s.k, s.E, k.cfg.bm);
     if ((cap + 16) * (size_t)s.I >= (1ull << 32) || (size_t)s.T * s.H >= (1ull << 32)) return false;
+    if (k.launch_stream && 2ull * s.I * s.H >= (1ull << 32)) return false;  // 32-bit byte offsets inside an expert
     if (k.launch_pp) {
         // its load stream runs two slices ahead, across one tile boundary at most; 32-bit offsets inside an expert
         constexpr int least = Fp8PingPongTraits<1, 1>::MIN_SLICES;
         if (s.H / kGroup < least || s.I / kGroup < least || 2ull * s.I * s.H >= (1ull << 32)) return false;
     }
     return true;
+}
+
+// Pool membership, as config_in_pool: the weight-streaming tiles are enumerated up to 32 pairs per expert of the layer.  Past
+// that every tile of theirs reads weights that another one has read too, with any routing (Mixtral-shaped, 32 pairs per expert:
+// 397 us, 317 us with the 128-row tile; at 16 pairs 294 against 315), and profiling them would only cost time.
+bool fp8_in_pool(const Fp8Kernel &k, const ramp_shape &s)
+{
+    return fp8_valid_for_shape(k, s) && (!k.launch_stream || (size_t)s.T * s.k <= (size_t)s.E * 32);
 }
 
 const Fp8Kernel *find_fp8(const ramp_config &c)
@@ -497,11 +541,14 @@ Fp8Workspace fp8_workspace(const ramp_shape &s, const ramp_config &c)
     w.align_ws = take(w.align_ws_bytes);
     w.xs_stride = pp ? (int)align_up(s.H / kGroup, 16) : scale_stride(s.H);
     w.as_stride = pp ? (int)align_up(s.I / kGroup, 16) : scale_stride(s.I);
-    w.xq = take((size_t)s.T * s.H);
-    w.xs = take((size_t)s.T * w.xs_stride);
-    w.a_buf = pp ? off : take(w.cap * (size_t)s.I * 2);  // the persistent up-projection writes the codes itself
-    w.aq = take(w.cap * (size_t)s.I);
-    w.as = take(w.cap * (size_t)w.as_stride);
+    // the weight-streaming kernels quantise in registers: no codes in memory; their two-launch form indexes A by pair
+    const bool stream = (c.mode & kModeStream) != 0;
+    const size_t rows = (stream && (size_t)s.T * s.k > w.cap) ? (size_t)s.T * s.k : w.cap;
+    w.xq = stream ? off : take((size_t)s.T * s.H);
+    w.xs = stream ? off : take((size_t)s.T * w.xs_stride);
+    w.a_buf = pp ? off : take(rows * (size_t)s.I * 2);  // the persistent up-projection writes the codes itself
+    w.aq = stream ? off : take(w.cap * (size_t)s.I);
+    w.as = stream ? off : take(w.cap * (size_t)w.as_stride);
     w.y_buf = take((size_t)s.T * s.k * s.H * 4);
     w.total = off;
     return w;
@@ -532,7 +579,7 @@ extern "C" int ramp_fp8_num_configs(const ramp_shape *shape)
     }
     int n = 0, cnt = 0;
     const Fp8Kernel *t = fp8_kernels(&n);
-    for (int i = 0; i < n; ++i) cnt += fp8_valid_for_shape(t[i], *shape) ? 1 : 0;
+    for (int i = 0; i < n; ++i) cnt += fp8_in_pool(t[i], *shape) ? 1 : 0;
     return cnt;
 }
 
@@ -545,7 +592,7 @@ extern "C" int ramp_fp8_get_config(const ramp_shape *shape, int idx, ramp_config
     int n = 0, cnt = 0;
     const Fp8Kernel *t = fp8_kernels(&n);
     for (int i = 0; i < n; ++i) {
-        if (!fp8_valid_for_shape(t[i], *shape)) continue;
+        if (!fp8_in_pool(t[i], *shape)) continue;
         if (cnt++ == idx) {
             *out = t[i].cfg;
             return RAMP_OK;
@@ -686,13 +733,6 @@ extern "C" int ramp_fused_moe_fp8(const ramp_shape *shape, const ramp_config *cf
     uint8_t *aq = reinterpret_cast<uint8_t *>(base + w.aq), *as = reinterpret_cast<uint8_t *>(base + w.as);
     float *y_buf = reinterpret_cast<float *>(base + w.y_buf);
 
-    AlignSlotWeights sw = {nullptr, nullptr};
-    if (k->launch_pp) sw = AlignSlotWeights{topk_w, reinterpret_cast<float *>(base + w.slot_w)};
-    if (int rc = launch_align(topk_ids, s.T, s.k, s.E, cfg->bm, sorted, tile_expert, tile_rows, counts, meta, base + w.align_ws,
-                              w.align_ws_bytes, st, nullptr, 0, sw))
-        return rc;
-    if (int rc = launch_quant_rows(static_cast<const uint16_t *>(X), s.T, s.H, xq, xs, w.xs_stride, nullptr, nullptr, 0, st)) return rc;
-
     const Fp8Layout L = fp8_layout(s);
     const uint8_t *packed = static_cast<const uint8_t *>(packed_fp8);
     GemmArgs g = {};
@@ -710,6 +750,62 @@ extern "C" int ramp_fused_moe_fp8(const ramp_shape *shape, const ramp_config *cf
     g.topk = s.k;
     g.m_tiles_cap = (int)(w.cap / (size_t)cfg->bm);
     g.group_m_req = 0;
+
+    if (k->launch_stream) {
+        Fp8StreamArgs up = {}, down = {};
+        up.wq = packed;
+        up.expert_stride = L.w1_expert_bytes;
+        up.up_offset = (uint32_t)L.up_offset_bytes;
+        up.wscale = packed + L.scale_base + L.scale_g;
+        up.wscale_expert_stride = L.scale_expert_bytes;
+        up.wscale_up_offset = (uint32_t)(L.scale_u - L.scale_g);
+        up.w_stride = L.stride1;
+        down.wq = packed + L.w2_base_bytes;
+        down.expert_stride = L.w2_expert_bytes;
+        down.wscale = packed + L.scale_base + L.scale_d;
+        down.wscale_expert_stride = L.scale_expert_bytes;
+        down.w_stride = L.stride2;
+        g.act = static_cast<const uint16_t *>(X);
+        g.K = s.H;
+        g.F = s.I;
+        g.n_tiles = 2 * s.I / cfg->bn;
+        if (k->launch_decode_up && g.P <= kDecodeMaxPairs && 16 % s.k == 0) {
+            const DecodeArgs da = {topk_ids, s.E, cfg->bm, (int)w.cap, sorted, tile_expert, tile_rows, counts, meta};
+            k->launch_decode_up(g, up, da, st);
+            if (int rc = check_launch("moe_fp8_decode_up_kernel")) return rc;
+            DecodeDownArgs dd = {};
+            dd.act = a_buf;
+            dd.ids = topk_ids;
+            dd.topk_w = topk_w;
+            dd.out = static_cast<uint16_t *>(out);
+            dd.T = s.T;
+            dd.k = s.k;
+            dd.E = s.E;
+            dd.H = s.H;
+            dd.I = s.I;
+            launch_fp8_decode_down(dd, down, st);
+            return check_launch("moe_fp8_decode_down_kernel");
+        }
+        if (int rc = launch_align(topk_ids, s.T, s.k, s.E, cfg->bm, sorted, tile_expert, tile_rows, counts, meta, base + w.align_ws,
+                                  w.align_ws_bytes, st))
+            return rc;
+        k->launch_stream(1, g, up, st);
+        if (int rc = check_launch("moe_fp8_stream_kernel<1>")) return rc;
+        g.act = a_buf;
+        g.K = s.I;
+        g.F = s.H;
+        g.n_tiles = s.H / cfg->bn;
+        k->launch_stream(2, g, down, st);
+        if (int rc = check_launch("moe_fp8_stream_kernel<2>")) return rc;
+        return launch_combine(y_buf, g.y_bf16, topk_ids, s.T, s.k, s.E, s.H, static_cast<uint16_t *>(out), st);
+    }
+
+    AlignSlotWeights sw = {nullptr, nullptr};
+    if (k->launch_pp) sw = AlignSlotWeights{topk_w, reinterpret_cast<float *>(base + w.slot_w)};
+    if (int rc = launch_align(topk_ids, s.T, s.k, s.E, cfg->bm, sorted, tile_expert, tile_rows, counts, meta, base + w.align_ws,
+                              w.align_ws_bytes, st, nullptr, 0, sw))
+        return rc;
+    if (int rc = launch_quant_rows(static_cast<const uint16_t *>(X), s.T, s.H, xq, xs, w.xs_stride, nullptr, nullptr, 0, st)) return rc;
 
     if (k->launch_pp) {
         g.slot_w = sw.slot_w;

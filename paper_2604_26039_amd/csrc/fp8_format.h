@@ -53,4 +53,62 @@ __device__ __forceinline__ uint32_t e4m3x4_of_f32(const float *v)
 
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t h) { return __builtin_bit_cast(float, h << 16); }
 
+typedef int intx8 __attribute__((ext_vector_type(8)));
+typedef int intx4 __attribute__((ext_vector_type(4)));
+typedef unsigned short ushortx2 __attribute__((ext_vector_type(2)));
+typedef short shortx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// Largest magnitude bits of two bf16 in a word, kept per half.
+__device__ __forceinline__ ushortx2 max_bf16_bits(ushortx2 m, uint32_t two)
+{
+    return __builtin_elementwise_max(m, __builtin_bit_cast(ushortx2, two & 0x7fff7fffu));
+}
+
+// Quantises the 2 * NW values of this lane; its group of 128 lies in the lanes that differ in the bits D0 ... DEND/2 of the lane
+// index.  Codes in order, one scale byte, the same bits as e8m0_of_amax and e4m3_of_f32 give.  v_cvt_scalef32_pk_fp8_bf16 divides two bf16 by a power of two
+// and converts them; for finite groups nothing exceeds 448 after that and its results are e4m3_of_f32's (compared for every
+// bf16 value and scale bytes over the whole range), at a third of the instructions of unpacking, scaling and saturating.
+// A group with an infinity or NaN takes the general conversion: NaN counts as no magnitude and converts to +-448.
+template <int NW, int D0, int DEND>
+__device__ __forceinline__ uint32_t quantise_group(const uint32_t *w, uint32_t *codes)
+{
+    ushortx2 m = {0, 0};
+#pragma unroll
+    for (int i = 0; i < NW; ++i) m = max_bf16_bits(m, w[i]);
+    auto group_max = [](uint32_t v) __attribute__((always_inline)) {
+#pragma unroll
+        for (int d = D0; d < DEND; d <<= 1) v = max(v, (uint32_t)__shfl_xor((int)v, d));
+        return v;
+    };
+    uint32_t top = group_max(m[0] > m[1] ? m[0] : m[1]);
+    if (__builtin_expect(top >= 0x7f80u, 0)) {
+        top = 0;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            const uint32_t lo = w[i] & 0x7fffu, hi = (w[i] >> 16) & 0x7fffu;
+            top = max(top, max(lo > 0x7f80u ? 0u : lo, hi > 0x7f80u ? 0u : hi));
+        }
+        const uint32_t b = e8m0_of_amax(bf16_bits_to_f32(group_max(top)));
+        const float inv = inv_scale_of(b);
+#pragma unroll
+        for (int i = 0; i < NW / 2; ++i) {
+            const float v[4] = {bf16_bits_to_f32(w[2 * i] & 0xffffu) * inv, bf16_bits_to_f32(w[2 * i] >> 16) * inv,
+                                bf16_bits_to_f32(w[2 * i + 1] & 0xffffu) * inv, bf16_bits_to_f32(w[2 * i + 1] >> 16) * inv};
+            codes[i] = e4m3x4_of_f32(v);
+        }
+        return b;
+    }
+    const uint32_t b = e8m0_of_amax(bf16_bits_to_f32(top));
+    const float scale = __builtin_bit_cast(float, b << 23);
+#pragma unroll
+    for (int i = 0; i < NW / 2; ++i) {
+        shortx2 r = {0, 0};
+        r = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(r, __builtin_bit_cast(bf16x2, w[2 * i]), scale, false);
+        r = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(r, __builtin_bit_cast(bf16x2, w[2 * i + 1]), scale, true);
+        codes[i] = __builtin_bit_cast(uint32_t, r);
+    }
+    return b;
+}
+
 }  // namespace ramp

@@ -35,9 +35,6 @@
 
 namespace ramp {
 
-typedef int intx8 __attribute__((ext_vector_type(8)));
-typedef int intx4 __attribute__((ext_vector_type(4)));
-
 struct Fp8PingPongArgs {
     const uint8_t *act_q;      // token operand: codes row-major [T, H] (stage 1), fragments [slots/16][I/128][2 KB] (stage 2)
     const uint8_t *act_scale;  // [rows][act_stride] E8M0 bytes, rows padded to 16 k-blocks
