@@ -8,10 +8,9 @@
 //   - ranks inside an expert come from a wavefront ballot (lanes of lower index),
 //     a per-wavefront count table in LDS (wavefronts of lower index) and a running
 //     cursor (earlier chunks / earlier workgroups).
-// Up to 64 pairs a single wavefront does everything; up to kAlignSingleMaxP pairs one
-// 1024-lane workgroup does histogram, scan and scatter in a single launch; larger inputs take two launches (per-chunk
-// histograms, then a kernel in which every workgroup scans them and scatters
-// its chunk); the histogram-only entry point ends with a small scan kernel.
+// Up to 64 pairs a single wavefront does everything; up to kAlignOneLaunchMaxP pairs one launch of a workgroup per 1024
+// pairs, each of which counts all pairs itself; larger inputs take two launches (per-chunk histograms, then a kernel in which
+// every workgroup scans them and scatters its chunk); the histogram-only entry point ends with a small scan kernel.
 #include "ramp_internal.h"
 #include "align_tiny.h"
 
@@ -161,52 +160,153 @@ __device__ void block_scatter_chunk(const int32_t *ids, int base, int P, int E, 
     __syncthreads();
 }
 
-// LDS carve-up (ints): hist[E] | toff[E+1] | wsum[NW] | misc[1] | wcnt[NW*E]
-__device__ __forceinline__ void carve(int *lds, int E, int *&hist, int *&toff, int *&wsum, int *&misc, unsigned *&wcnt)
+// ---- histogram only, one workgroup ----
+__global__ __launch_bounds__(NT) void histogram_kernel(const int32_t *ids, int P, int E, int32_t *counts)
 {
-    hist = lds;
-    toff = hist + E;
-    wsum = toff + E + 1;
-    misc = wsum + NW;
-    wcnt = reinterpret_cast<unsigned *>(misc + 1);
+    __shared__ int hist[kAlignMaxE];
+    __shared__ int dropped;
+    for (int x = threadIdx.x; x < E; x += NT) hist[x] = 0;
+    if (threadIdx.x == 0) dropped = 0;
+    __syncthreads();
+    block_histogram(ids, 0, P, E, hist, &dropped);
+    __syncthreads();
+    for (int x = threadIdx.x; x < E; x += NT) counts[x] = hist[x];
 }
-size_t lds_ints(int E) { return (size_t)E + (E + 1) + NW + 1 + (size_t)NW * E; }
 
-// ---- single workgroup: everything in one launch ----
-__global__ __launch_bounds__(NT) void align_single_kernel(const int32_t *ids, int P, int E, int bm, int cap,
-                                                          int32_t *sorted, int32_t *tile_expert, int32_t *tile_rows,
-                                                          int32_t *counts, int32_t *meta, int scatter,
-                                                          const int32_t *pred, int pred_value,
-                                                          AlignSlotWeights slot_weights)
+// ---- one launch, a workgroup per chunk of NT pairs: histogram, scan, scatter ----
+//
+// Bound by latency: a few dependent steps of a hundred nanoseconds each behind the launch.  A lane keeps its pair in a register
+// through all of them; ranks inside the chunk come from ballots and a table of 16-bit counts per wavefront and expert, so
+// the own chunk takes no atomics; the other chunks are counted with LDS atomics (sums, order independent) instead of in an
+// earlier launch.  Slots without a pair are filled from the scanned offsets, each by exactly one lane, so nothing has to be
+// filled before the scatter.  Per call in a captured graph: P = 2048, E = 8 7.2 -> 4.3 us; P = 4096,
+// E = 128, two launches before, 8.1 -> 5.1 us; P = 16384, E = 256 8.3 -> 7.7 us, where the limit lies.
+__global__ __launch_bounds__(NT) void align_kernel(const int32_t *ids, int P, int E, int bm, int cap, int32_t *sorted,
+                                                   int32_t *tile_expert, int32_t *tile_rows, int32_t *counts, int32_t *meta,
+                                                   const int32_t *pred, int pred_value, AlignSlotWeights slot_weights)
 {
     if (launch_deselected(pred, pred_value)) return;
     extern __shared__ int lds[];
-    int *hist, *toff, *wsum, *misc;
-    unsigned *wcnt;
-    carve(lds, E, hist, toff, wsum, misc, wcnt);
-    for (int x = threadIdx.x; x < E; x += NT) hist[x] = 0;
-    for (int x = threadIdx.x; x < NW * E; x += NT) wcnt[x] = 0;
-    if (threadIdx.x == 0) misc[0] = 0;
+    // total[E] (other chunks; then all pairs) | first[E] (earlier chunks; then the chunk's first slot) | toff[E+1] | wsum[NW] |
+    // dropped | wcnt[NW][E] of 16 bits
+    int *total = lds, *first = total + E, *toff = first + E, *wsum = toff + E + 1, *dropped = wsum + NW;
+    uint16_t *wcnt = reinterpret_cast<uint16_t *>(dropped + 1);
+    const int tid = threadIdx.x, lane = lane_id(), wv = tid >> 6;
+    const int chunk = blockIdx.x, B = gridDim.x;
+    const int p = chunk * NT + tid;
+    int e = p < P ? ids[p] : -1;
+    float weight = 0.f;
+    if (slot_weights.slot_w && p < P) weight = slot_weights.topk_w[p];
+    for (int x = tid; x < 2 * E; x += NT) total[x] = 0;
+    for (int x = tid; x < NW * E / 2; x += NT) reinterpret_cast<int *>(wcnt)[x] = 0;
+    if (tid == 0) *dropped = 0;
     __syncthreads();
-    block_histogram(ids, 0, P, E, hist, misc);
-    if (scatter)
-        for (int s = threadIdx.x; s < cap; s += NT) sorted[s] = P;
-    __syncthreads();
-    if (!scatter) {  // histogram only
-        for (int x = threadIdx.x; x < E; x += NT) counts[x] = hist[x];
-        return;
+    if (e < 0 || e >= E) {
+        if (p < P) atomicAdd(dropped, 1);
+        e = -1;
     }
-    int n_e = ((int)threadIdx.x < E) ? hist[threadIdx.x] : 0;
-    int dropped = misc[0];
-    block_scan_and_emit(n_e, E, bm, cap, dropped, toff, wsum, hist, counts, meta, tile_expert, tile_rows);
+    const int ebits = 32 - __clz((E - 1) | 1);
+    unsigned long long same = __ballot(e >= 0);
+#pragma unroll
+    for (int b = 0; b < 10; ++b) {  // E <= 1024
+        if (b < ebits) {
+            const bool bit = (e >> b) & 1;
+            const unsigned long long m = __ballot(e >= 0 && bit);
+            same &= bit ? m : ~m;
+        }
+    }
+    const int rank = __popcll(same & ((1ull << lane) - 1ull));
+    if (e >= 0 && rank == 0) wcnt[wv * E + e] = (uint16_t)__popcll(same);
+    for (int c = 0; c < B; c += 4) {
+        int v[4];
+        bool other[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int o = (c + i) * NT + tid;
+            other[i] = c + i != chunk && o < P;
+            v[i] = other[i] ? ids[o] : -1;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (v[i] >= 0 && v[i] < E) {
+                atomicAdd(&total[v[i]], 1);
+                if (c + i < chunk) atomicAdd(&first[v[i]], 1);
+            } else if (other[i]) {
+                atomicAdd(dropped, 1);
+            }
+        }
+    }
     __syncthreads();
-    int *cursor = hist;  // histogram no longer needed
-    for (int x = threadIdx.x; x < E; x += NT) cursor[x] = toff[x];
+    // lane = expert: counts of the wavefronts -> pairs before each wavefront, all pairs, padded slots
+    int n = 0, slots = 0, incl = 0;
+    if ((tid & ~(kWave - 1)) < E) {
+        if (tid < E) {
+            int run = 0;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const int c = wcnt[w * E + tid];
+                wcnt[w * E + tid] = (uint16_t)run;
+                run += c;
+            }
+            n = total[tid] + run;
+            slots = (n + bm - 1) / bm * bm;
+        }
+        incl = slots;
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1) {
+            const int up = __shfl_up(incl, d, kWave);
+            if (lane >= d) incl += up;
+        }
+        if (lane == kWave - 1) wsum[wv] = incl;
+    }
     __syncthreads();
-    unsigned stamp = 1;
-    for (int base = 0; base < P; base += NT, ++stamp)
-        block_scatter_chunk(ids, base, P, E, cursor, wcnt, stamp, sorted, slot_weights);
+    const int used = (E + kWave - 1) / kWave;  // wavefronts that hold experts
+    if (wv < used) {
+        int off = incl - slots, sum = 0;
+        for (int w = 0; w < used; ++w) {
+            if (w == wv) off += sum;
+            sum += wsum[w];
+        }
+        if (tid < E) {
+            toff[tid] = off;
+            first[tid] += off;
+            total[tid] = n;
+            if (chunk == 0) counts[tid] = n;
+        }
+        if (tid == 0) {
+            toff[E] = sum;
+            if (chunk == 0) {
+                meta[0] = sum;
+                meta[1] = sum / bm;
+                meta[2] = *dropped;
+                meta[3] = 0;
+            }
+        }
+    }
+    __syncthreads();
+    if (e >= 0) {
+        const int slot = first[e] + wcnt[wv * E + e] + rank;
+        sorted[slot] = p;
+        if (slot_weights.slot_w) slot_weights.slot_w[slot] = weight;
+    }
+    // sentinels: the padding of an expert by 16 or 64 lanes, then everything past the padded length
+    const int width = bm <= 16 ? 16 : kWave, per = NT / width, sub = tid & (width - 1);
+    for (int x = chunk * per + tid / width; x < E; x += B * per) {
+        const int end = toff[x + 1];
+        for (int s = toff[x] + total[x] + sub; s < end; s += width) sorted[s] = P;
+    }
+    const int p_pad = toff[E];
+    for (int s = p_pad + chunk * NT + tid; s < cap; s += B * NT) sorted[s] = P;
+    // tiles
+    const int m_tiles = p_pad / bm, m_cap = cap / bm;
+    for (int m = chunk * NT + tid; m < m_cap; m += B * NT) {
+        int owner = -1, rows = 0;
+        if (m < m_tiles) tiny_align_tile(m, E, bm, total, toff, owner, rows);
+        tile_expert[m] = owner;
+        if (tile_rows) tile_rows[m] = rows;
+    }
 }
+size_t align_lds_bytes(int E) { return ((size_t)2 * E + (E + 1) + NW + 1) * sizeof(int) + (size_t)NW * E * sizeof(uint16_t); }
 
 // ---- up to 64 pairs (decode-sized calls): one wavefront, one pair per lane, no workgroup-wide steps ----
 constexpr int kAlignTinyMaxP = 64;
@@ -364,18 +464,20 @@ static int launch_align_impl(const int32_t *ids, int T, int k, int E, int bm, in
                            tile_rows, counts, meta, pred, pred_value, slot_weights);
         return check_launch("align_tiny_kernel");
     }
-    if (P <= kAlignSingleMaxP) {
-        size_t lds = lds_ints(E) * sizeof(int);
-        if (int rc = allow_lds(align_single_kernel, lds)) return rc;
-        hipLaunchKernelGGL(align_single_kernel, dim3(1), dim3(NT), lds, stream, ids, P, E, bm, cap, sorted,
-                           tile_expert, tile_rows, counts, meta, scatter, pred, pred_value, slot_weights);
-        return check_launch("align_single_kernel");
+    if (!scatter && P <= kAlignSingleMaxP) {
+        hipLaunchKernelGGL(histogram_kernel, dim3(1), dim3(NT), 0, stream, ids, P, E, counts);
+        return check_launch("histogram_kernel");
     }
     const int B = num_blocks(P);
     const size_t need = ramp_align_workspace_bytes(T, k, E);
-    if (!ws || ws_bytes < need) {
+    if (P > kAlignSingleMaxP && (!ws || ws_bytes < need)) {
         set_error("align: workspace %zu < %zu bytes", ws_bytes, need);
         return RAMP_ENOSPC;
+    }
+    if (scatter && P <= kAlignOneLaunchMaxP) {
+        hipLaunchKernelGGL(align_kernel, dim3(B > 0 ? B : 1), dim3(NT), align_lds_bytes(E), stream, ids, P, E, bm, cap, sorted,
+                           tile_expert, tile_rows, counts, meta, pred, pred_value, slot_weights);
+        return check_launch("align_kernel");
     }
     int32_t *block_counts = static_cast<int32_t *>(ws);
     int32_t *block_base = block_counts + (size_t)B * E;
