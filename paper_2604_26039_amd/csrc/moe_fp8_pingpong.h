@@ -494,9 +494,7 @@ __global__ __launch_bounds__(512, 1) void moe_fp8_pingpong_kernel(GemmArgs a, Fp
                         }
                     }
                 } else {
-                    const int pair = pairs[row0 + er];
-                    if (pair < a.P)
-                        store_token_row<2, FB>(a, &acc[0][nb], &acc[0][nb], NB, (size_t)pair * a.F, f0 / 16, eq, wgt);
+                    store_pair_rows_f32<SR / 2>(a, stg, &acc[0][nb], NB, pairs[row0 + er], wgt, f0, el);
                 }
             }
         }

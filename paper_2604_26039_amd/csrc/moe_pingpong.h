@@ -59,7 +59,7 @@ struct PingPongTraits {
     static constexpr int W_BYTES = TT::W_FRAGS * kFragElems * 2;
     static constexpr int WSLOTS = TT::W_FRAGS / TT::NWAVE;     // weight load instructions per wavefront per slice
     static constexpr int RING_BYTES = NX * X_BYTES + NSTAGE * W_BYTES;
-    static constexpr int STG_BYTES = (STAGE == 2) ? 4096 * TT::NWAVE : 0;  // per-wavefront staging of bf16 output rows
+    static constexpr int STG_BYTES = (STAGE == 2) ? 4096 * TT::NWAVE : 0;  // per-wavefront staging of output rows
     // A down-projection tile with tail blocks has no registers to spare for the destination pair and router weight of its
     // token rows through the whole tile: they wait in LDS instead (pairs and weights of up to 512 slots, two tiles deep).
     static constexpr bool SLOT_LDS = (STAGE == 2) && TAILB > 0;
@@ -590,6 +590,9 @@ __global__ __launch_bounds__(512, 1) void moe_pingpong_kernel(GemmArgs a)
                 }
             }
         } else {
+        // opaque: addresses derived from the lane would be computed in front of the slice loop and spilled across it
+        int el = lane;
+        asm volatile("" : "+v"(el));
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
             if (nb >= nb_valid) continue;
@@ -598,9 +601,7 @@ __global__ __launch_bounds__(512, 1) void moe_pingpong_kernel(GemmArgs a)
             if (STAGE == 1) {
                 store_token_row<1, FB>(a, &acc[0][nb], &acc[FB][nb], NB, (size_t)slot, rb0, q, 1.0f);
             } else {
-                const int pair = out_pair[nb];
-                if (pair >= a.P) continue;
-                store_token_row<2, FB>(a, &acc[0][nb], &acc[0][nb], NB, (size_t)pair * a.F, rb0, q, out_wgt[nb]);
+                store_pair_rows_f32<16>(a, lds_stage + wave * 4096, &acc[0][nb], NB, out_pair[nb], out_wgt[nb], rb0 * 16, el);
             }
         }
         }
