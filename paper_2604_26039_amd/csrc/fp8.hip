@@ -57,33 +57,33 @@ Fp8Layout fp8_layout(const ramp_shape &s)
 
 // ---- quantisers -----------------------------------------------------------------------------------------------
 
-// src bf16 [rows, K] row-major -> codes [rows, K], scale bytes [rows, stride].  One wavefront per (row, 128-group),
-// two values per lane.  Rows at or past *n_rows_dev (when given) are skipped.
+// src bf16 [rows, K] row-major -> codes [rows, K], scale bytes [rows, stride].  Rows at or past *n_rows_dev (when given) are
+// skipped.  Bound by memory, and at small sizes by the launch: K is a multiple of the group, so the groups are consecutive in
+// both arrays; 16 lanes take one, a 16-byte load and an 8-byte store each, and the maximum is four lane exchanges.  The vector
+// types carry the alignment of one value: the entry point takes any address.
+typedef uint32_t UnalignedWords4 __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t UnalignedWords2 __attribute__((ext_vector_type(2), aligned(1)));
 __global__ __launch_bounds__(256) void quant_rows_kernel(const uint16_t *__restrict__ src, int rows, int K,
                                                          uint8_t *__restrict__ codes, uint8_t *__restrict__ sb, int stride,
                                                          const int32_t *__restrict__ n_rows_dev, const int32_t *pred,
                                                          int pred_value)
 {
     if (launch_deselected(pred, pred_value)) return;
-    const int lane = threadIdx.x & 63;
+    const int sub = threadIdx.x & 15;
     const int groups = K / kGroup;
     const int live_rows = n_rows_dev ? min(rows, *n_rows_dev) : rows;
     const size_t total = (size_t)live_rows * groups;
-    const size_t wave0 = (size_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
-    const size_t nwaves = (size_t)gridDim.x * (blockDim.x / 64);
-    for (size_t w = wave0; w < total; w += nwaves) {
-        const size_t row = w / groups;
-        const int g = (int)(w % groups);
-        const uint32_t two = *reinterpret_cast<const uint32_t *>(src + row * (size_t)K + (size_t)g * kGroup + 2 * lane);
-        const float v0 = bf16_bits_to_f32(two & 0xffffu), v1 = bf16_bits_to_f32(two >> 16);
-        float amax = fmaxf(fabsf(v0), fabsf(v1));
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) amax = fmaxf(amax, __shfl_xor(amax, d));
-        const uint32_t b = e8m0_of_amax(amax);
-        const float inv = inv_scale_of(b);
-        const uint32_t c = e4m3_of_f32(v0 * inv) | (e4m3_of_f32(v1 * inv) << 8);
-        *reinterpret_cast<uint16_t *>(codes + row * (size_t)K + (size_t)g * kGroup + 2 * lane) = (uint16_t)c;
-        if (lane == 0) sb[row * (size_t)stride + g] = (uint8_t)b;
+    const size_t step = (size_t)gridDim.x * (blockDim.x / 16);
+    for (size_t g = (size_t)blockIdx.x * (blockDim.x / 16) + (threadIdx.x >> 4); g < total; g += step) {
+        const UnalignedWords4 v = *reinterpret_cast<const UnalignedWords4 *>(src + g * kGroup + sub * 8);
+        const uint32_t w[4] = {v[0], v[1], v[2], v[3]};
+        uint32_t c[2];
+        const uint32_t b = quantise_group<4, 1, 16>(w, c);
+        *reinterpret_cast<UnalignedWords2 *>(codes + g * kGroup + sub * 8) = UnalignedWords2{c[0], c[1]};
+        if (sub == 0) {
+            const size_t row = (total >> 32) ? g / groups : (uint32_t)g / (uint32_t)groups;
+            sb[row * (size_t)stride + (g - row * groups)] = (uint8_t)b;
+        }
     }
 }
 
@@ -559,7 +559,7 @@ int launch_quant_rows(const uint16_t *src, int rows, int K, uint8_t *codes, uint
 {
     if (rows <= 0) return RAMP_OK;
     const size_t groups = (size_t)rows * (K / kGroup);
-    size_t blocks = (groups + 3) / 4;
+    size_t blocks = (groups + 15) / 16;
     if (blocks > (size_t)kNumCU * 32) blocks = (size_t)kNumCU * 32;
     hipLaunchKernelGGL(quant_rows_kernel, dim3((unsigned)blocks), dim3(256), 0, st, src, rows, K, codes, sb, sb_stride,
                        n_rows_dev, pred, pred_value);

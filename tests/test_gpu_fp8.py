@@ -48,6 +48,27 @@ def test_activation_quantiser_bit_exact():
     assert np.array_equal(codes.cpu().numpy(), want_c)
 
 
+def test_activation_quantiser_edges():
+    """Group counts that fill no wavefront or workgroup, sources and codes at odd addresses, magnitudes at both ends of bf16."""
+    rng = np.random.default_rng(1)
+    for rows, K, shift in ((1, 128, 0), (3, 128, 1), (17, 640, 3), (300, 1152, 0)):
+        x = rng.normal(0, 1, (rows, K)) * np.exp2(rng.uniform(-126, 120, (rows, 1)))
+        X = torch.from_numpy(x).to(torch.bfloat16)
+        src = torch.zeros(rows * K + shift, dtype=torch.bfloat16, device=DEV)
+        src[shift:] = X.flatten().to(DEV)
+        codes = torch.full((rows * K + 2 * shift,), 99, dtype=torch.uint8, device=DEV)
+        stride = (K // 128 + 3) // 4 * 4
+        scales = torch.full((rows, stride), 77, dtype=torch.uint8, device=DEV)
+        ramp.fp8_quantize_rows(src[shift:].view(rows, K), codes[shift:shift + rows * K].view(rows, K), scales)
+        torch.cuda.synchronize()
+        want_c, want_s = ofp8.quantize_rows(f64(X))
+        got = codes.cpu().numpy()
+        assert np.array_equal(scales.cpu().numpy()[:, :K // 128], want_s), (rows, K, shift)
+        assert (scales.cpu().numpy()[:, K // 128:] == 77).all()
+        assert np.array_equal(got[shift:shift + rows * K].reshape(rows, K), want_c), (rows, K, shift)
+        assert (got[:shift] == 99).all() and (got[shift + rows * K:] == 99).all()
+
+
 def row_feature(rb, r):
     """Feature held by row r of packed row block rb (interleave inside groups of four row blocks)."""
     return (rb // 4) * 64 + (r >> 2) * 16 + (rb % 4) * 4 + (r & 3)
