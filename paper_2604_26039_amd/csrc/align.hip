@@ -181,11 +181,10 @@ __global__ __launch_bounds__(NT) void histogram_kernel(const int32_t *ids, int P
 // earlier launch.  Slots without a pair are filled from the scanned offsets, each by exactly one lane, so nothing has to be
 // filled before the scatter.  Per call in a captured graph: P = 2048, E = 8 7.2 -> 4.3 us; P = 4096,
 // E = 128, two launches before, 8.1 -> 5.1 us; P = 16384, E = 256 8.3 -> 7.7 us, where the limit lies.
-__global__ __launch_bounds__(NT) void align_kernel(const int32_t *ids, int P, int E, int bm, int cap, int32_t *sorted,
-                                                   int32_t *tile_expert, int32_t *tile_rows, int32_t *counts, int32_t *meta,
-                                                   const int32_t *pred, int pred_value, AlignSlotWeights slot_weights)
+__device__ __forceinline__ void align_one_launch(const int32_t *ids, int P, int E, int bm, int cap, int32_t *sorted,
+                                                 int32_t *tile_expert, int32_t *tile_rows, int32_t *counts, int32_t *meta,
+                                                 AlignSlotWeights slot_weights)
 {
-    if (launch_deselected(pred, pred_value)) return;
     extern __shared__ int lds[];
     // total[E] (other chunks; then all pairs) | first[E] (earlier chunks; then the chunk's first slot) | toff[E+1] | wsum[NW] |
     // dropped | wcnt[NW][E] of 16 bits
@@ -305,6 +304,30 @@ __global__ __launch_bounds__(NT) void align_kernel(const int32_t *ids, int P, in
         tile_expert[m] = owner;
         if (tile_rows) tile_rows[m] = rows;
     }
+}
+
+__global__ __launch_bounds__(NT) void align_kernel(const int32_t *ids, int P, int E, int bm, int cap, int32_t *sorted,
+                                                   int32_t *tile_expert, int32_t *tile_rows, int32_t *counts, int32_t *meta,
+                                                   const int32_t *pred, int pred_value, AlignSlotWeights slot_weights)
+{
+    if (launch_deselected(pred, pred_value)) return;
+    align_one_launch(ids, P, E, bm, cap, sorted, tile_expert, tile_rows, counts, meta, slot_weights);
+}
+
+// The same for the candidate whose position *sel names, nothing for a position that is out of range or aligns by itself.  One
+// launch in the place of one per candidate, all but one of which would start only to return.
+__global__ __launch_bounds__(NT) void align_selected_kernel(const int32_t *ids, int P, int E, const float *topk_w, char *base,
+                                                            const int32_t *sel, int n_cand, AlignChoices choices)
+{
+    const int idx = *sel;
+    if (idx < 0 || idx >= n_cand) return;
+    const AlignChoice c = choices.c[idx];
+    if (c.bm == 0) return;
+    AlignSlotWeights sw = {nullptr, nullptr};
+    if (c.with_slot_w) sw = AlignSlotWeights{topk_w, reinterpret_cast<float *>(base + c.slot_w)};
+    align_one_launch(ids, P, E, c.bm, c.cap, reinterpret_cast<int32_t *>(base + c.sorted),
+                     reinterpret_cast<int32_t *>(base + c.tile_expert), reinterpret_cast<int32_t *>(base + c.tile_rows),
+                     reinterpret_cast<int32_t *>(base + c.counts), reinterpret_cast<int32_t *>(base + c.meta), sw);
 }
 size_t align_lds_bytes(int E) { return ((size_t)2 * E + (E + 1) + NW + 1) * sizeof(int) + (size_t)NW * E * sizeof(uint16_t); }
 
@@ -527,6 +550,18 @@ int launch_align(const int32_t *ids, int T, int k, int E, int bm, int32_t *sorte
     }
     return launch_align_impl(ids, T, k, E, bm, sorted, tile_expert, tile_rows, counts, meta, ws, ws_bytes, stream, 1,
                              pred, pred_value, slot_weights);
+}
+
+int launch_align_selected(const int32_t *ids, int P, int E, const float *topk_w, char *base, const int32_t *sel, int n_cand,
+                          const AlignChoices &choices, hipStream_t stream)
+{
+    if (P < 1 || P > kAlignOneLaunchMaxP || n_cand > kMaxCandidates) {
+        set_error("align_selected: P=%d n_cand=%d", P, n_cand);
+        return RAMP_EINVAL;
+    }
+    hipLaunchKernelGGL(align_selected_kernel, dim3(num_blocks(P)), dim3(NT), align_lds_bytes(E), stream, ids, P, E, topk_w, base, sel,
+                       n_cand, choices);
+    return check_launch("align_selected_kernel");
 }
 
 }  // namespace ramp

@@ -446,12 +446,18 @@ bool pair_rows_bf16(const ramp_shape &s)
     return (size_t)s.T * s.k * s.H >= kPairRowsBf16Elems;
 }
 
+bool runs_two_launches(const KernelInfo &ki, const ramp_shape &s)
+{
+    return ki.launch_decode_up && s.T * s.k <= kDecodeMaxPairs && 16 % s.k == 0;
+}
+
 // align(bm) + both projections of one configuration; `base` holds every workspace section but the per-pair rows,
 // which go to y_buf.  With pred != NULL every launch is a no-op unless *pred == pred_value on the device.
-// *wrote_out is set when the configuration's launches wrote `out` themselves (two-launch decode form): no combine then.
+// aligned: an earlier launch has filled the align sections.  *wrote_out is set when the configuration's launches wrote `out` themselves (two-launch decode form): no combine then.
 int enqueue_projections(const ramp_shape &s, const ramp_config &cfg, const KernelInfo &ki, const Workspace &w, const void *X,
                         const int32_t *topk_ids, const float *topk_w, const void *packed_weights, char *base,
-                        float *y_buf, void *out, const int32_t *pred, int pred_value, hipStream_t st, bool *wrote_out)
+                        float *y_buf, void *out, const int32_t *pred, int pred_value, hipStream_t st, bool *wrote_out,
+                        bool aligned = false)
 {
     *wrote_out = false;
     int32_t *sorted = reinterpret_cast<int32_t *>(base + w.sorted);
@@ -464,7 +470,7 @@ int enqueue_projections(const ramp_shape &s, const ramp_config &cfg, const Kerne
     const PackedLayout L = packed_layout(s);
     const uint16_t *packed = static_cast<const uint16_t *>(packed_weights);
     const int P = s.T * s.k;
-    if (ki.launch_decode_up && P <= kDecodeMaxPairs && 16 % s.k == 0) {
+    if (runs_two_launches(ki, s)) {
         // decode-sized call: align + up-projection + SwiGLU in one launch, down-projection + top-k sum in the other
         GemmArgs g = {};
         g.act = static_cast<const uint16_t *>(X);
@@ -497,8 +503,8 @@ int enqueue_projections(const ramp_shape &s, const ramp_config &cfg, const Kerne
         return check_launch("moe_decode_down_kernel");
     }
 
-    int rc;
-    {
+    int rc = RAMP_OK;
+    if (!aligned) {
         ProbeScope probe(1, st);
         AlignSlotWeights sw = {nullptr, nullptr};
         if (cfg.mode & kModePingPong) sw = AlignSlotWeights{topk_w, reinterpret_cast<float *>(base + w.slot_w)};
@@ -663,11 +669,11 @@ extern "C" int ramp_fused_moe_selected(const ramp_shape *shape, int n_cand, cons
                                        const float *topk_w, const void *packed_weights, void *out, void *ws,
                                        size_t ws_bytes, void *stream)
 {
-    if (n_cand <= 0 || n_cand > 16 || !cfgs || !selected_idx) {
+    if (n_cand <= 0 || n_cand > kMaxCandidates || !cfgs || !selected_idx) {
         set_error("fused_moe_selected: need 1..16 candidate configurations and a device index");
         return RAMP_EINVAL;
     }
-    const KernelInfo *ki[16];
+    const KernelInfo *ki[kMaxCandidates];
     for (int c = 0; c < n_cand; ++c)
         if (int rc = check_fused_call("fused_moe_selected", shape, &cfgs[c], &ki[c])) return rc;
     const ramp_shape &s = *shape;
@@ -683,11 +689,27 @@ extern "C" int ramp_fused_moe_selected(const ramp_shape *shape, int n_cand, cons
     char *base = static_cast<char *>(ws) + align_up((size_t)s.T * s.k * s.H * 4, 256);
     // every candidate is enqueued; on the device only the one whose position equals *selected_idx does anything
     unsigned self_combined = 0;  // candidates whose own launches write `out` (two-launch decode form)
+    // One align launch for all candidates wherever an align is one launch: a launch that is not the selected one still takes
+    // its turn in the stream.
+    AlignChoices choices = {};
+    int aligns = 0;
+    for (int c = 0; c < n_cand; ++c) {
+        if (runs_two_launches(*ki[c], s)) continue;
+        const Workspace w = workspace_layout(s, cfgs[c]);
+        choices.c[c] = AlignChoice{cfgs[c].bm, (int32_t)w.cap, (cfgs[c].mode & kModePingPong) ? 1 : 0, w.sorted, w.tile_expert,
+                                   w.tile_rows, w.counts, w.meta, w.slot_w};
+        ++aligns;
+    }
+    const bool shared_align = aligns > 1 && s.T * s.k <= kAlignOneLaunchMaxP;
+    if (shared_align) {
+        ProbeScope probe(1, st);
+        if (int rc = launch_align_selected(topk_ids, s.T * s.k, s.E, topk_w, base, selected_idx, n_cand, choices, st)) return rc;
+    }
     for (int c = 0; c < n_cand; ++c) {
         const Workspace w = workspace_layout(s, cfgs[c]);
         bool wrote_out = false;
         if (int rc = enqueue_projections(s, cfgs[c], *ki[c], w, X, topk_ids, topk_w, packed_weights, base, y_buf, out,
-                                         selected_idx, c, st, &wrote_out))
+                                         selected_idx, c, st, &wrote_out, shared_align))
             return rc;
         if (wrote_out) self_combined |= 1u << c;
     }

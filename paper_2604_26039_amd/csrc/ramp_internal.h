@@ -47,6 +47,19 @@ int launch_align(const int32_t *ids, int T, int k, int E, int bm, int32_t *sorte
                  int32_t *tile_rows, int32_t *counts, int32_t *meta, void *ws, size_t ws_bytes, hipStream_t stream,
                  const int32_t *pred = nullptr, int pred_value = 0, AlignSlotWeights slot_weights = {nullptr, nullptr});
 
+// Align for the device-selected layer: bm, capacity and workspace sections (byte offsets) of every candidate; bm = 0 for one
+// that aligns in its own kernels.
+constexpr int kMaxCandidates = 16;
+struct AlignChoice {
+    int32_t bm, cap, with_slot_w;
+    size_t sorted, tile_expert, tile_rows, counts, meta, slot_w;
+};
+struct AlignChoices {
+    AlignChoice c[kMaxCandidates];
+};
+int launch_align_selected(const int32_t *ids, int P, int E, const float *topk_w, char *base, const int32_t *sel, int n_cand,
+                          const AlignChoices &choices, hipStream_t stream);
+
 // ---- packed weights ----
 // One fragment = 16 weight rows x 32 k-values = 512 bf16 = 1 KB, stored in the lane order
 // of the A operand of v_mfma_f32_16x16x32_bf16: element (row r, k = 8*q + j) at (q*16 + r)*8 + j.
