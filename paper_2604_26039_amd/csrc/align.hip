@@ -13,6 +13,7 @@
 // every workgroup scans them and scatters its chunk); the histogram-only entry point ends with a small scan kernel.
 #include "ramp_internal.h"
 #include "align_tiny.h"
+#include "fp8_format.h"
 
 namespace ramp {
 namespace {
@@ -183,7 +184,7 @@ __global__ __launch_bounds__(NT) void histogram_kernel(const int32_t *ids, int P
 // E = 128, two launches before, 8.1 -> 5.1 us; P = 16384, E = 256 8.3 -> 7.7 us, where the limit lies.
 __device__ __forceinline__ void align_one_launch(const int32_t *ids, int P, int E, int bm, int cap, int32_t *sorted,
                                                  int32_t *tile_expert, int32_t *tile_rows, int32_t *counts, int32_t *meta,
-                                                 AlignSlotWeights slot_weights)
+                                                 AlignSlotWeights slot_weights, int B)
 {
     extern __shared__ int lds[];
     // total[E] (other chunks; then all pairs) | first[E] (earlier chunks; then the chunk's first slot) | toff[E+1] | wsum[NW] |
@@ -191,7 +192,7 @@ __device__ __forceinline__ void align_one_launch(const int32_t *ids, int P, int 
     int *total = lds, *first = total + E, *toff = first + E, *wsum = toff + E + 1, *dropped = wsum + NW;
     uint16_t *wcnt = reinterpret_cast<uint16_t *>(dropped + 1);
     const int tid = threadIdx.x, lane = lane_id(), wv = tid >> 6;
-    const int chunk = blockIdx.x, B = gridDim.x;
+    const int chunk = blockIdx.x;
     const int p = chunk * NT + tid;
     int e = p < P ? ids[p] : -1;
     float weight = 0.f;
@@ -311,7 +312,7 @@ __global__ __launch_bounds__(NT) void align_kernel(const int32_t *ids, int P, in
                                                    const int32_t *pred, int pred_value, AlignSlotWeights slot_weights)
 {
     if (launch_deselected(pred, pred_value)) return;
-    align_one_launch(ids, P, E, bm, cap, sorted, tile_expert, tile_rows, counts, meta, slot_weights);
+    align_one_launch(ids, P, E, bm, cap, sorted, tile_expert, tile_rows, counts, meta, slot_weights, (int)gridDim.x);
 }
 
 // The same for the candidate whose position *sel names, nothing for a position that is out of range or aligns by itself.  One
@@ -327,7 +328,19 @@ __global__ __launch_bounds__(NT) void align_selected_kernel(const int32_t *ids, 
     if (c.with_slot_w) sw = AlignSlotWeights{topk_w, reinterpret_cast<float *>(base + c.slot_w)};
     align_one_launch(ids, P, E, c.bm, c.cap, reinterpret_cast<int32_t *>(base + c.sorted),
                      reinterpret_cast<int32_t *>(base + c.tile_expert), reinterpret_cast<int32_t *>(base + c.tile_rows),
-                     reinterpret_cast<int32_t *>(base + c.counts), reinterpret_cast<int32_t *>(base + c.meta), sw);
+                     reinterpret_cast<int32_t *>(base + c.counts), reinterpret_cast<int32_t *>(base + c.meta), sw, (int)gridDim.x);
+}
+
+// Align by the first B workgroups, the FP8 codes of the hidden state by the others: two short launches that do not depend on
+// each other in the time of the longer one.
+__global__ __launch_bounds__(NT) void align_quant_kernel(const int32_t *ids, int P, int B, int E, int bm, int cap, int32_t *sorted,
+                                                         int32_t *tile_expert, int32_t *tile_rows, int32_t *counts, int32_t *meta,
+                                                         AlignSlotWeights slot_weights, QuantRows q)
+{
+    if ((int)blockIdx.x < B)
+        align_one_launch(ids, P, E, bm, cap, sorted, tile_expert, tile_rows, counts, meta, slot_weights, B);
+    else
+        quantise_rows(q, (size_t)(blockIdx.x - B) * (NT / 16), (size_t)(gridDim.x - B) * (NT / 16));
 }
 size_t align_lds_bytes(int E) { return ((size_t)2 * E + (E + 1) + NW + 1) * sizeof(int) + (size_t)NW * E * sizeof(uint16_t); }
 
@@ -562,6 +575,22 @@ int launch_align_selected(const int32_t *ids, int P, int E, const float *topk_w,
     hipLaunchKernelGGL(align_selected_kernel, dim3(num_blocks(P)), dim3(NT), align_lds_bytes(E), stream, ids, P, E, topk_w, base, sel,
                        n_cand, choices);
     return check_launch("align_selected_kernel");
+}
+
+int launch_align_quant(const int32_t *ids, int T, int k, int E, int bm, int32_t *sorted, int32_t *tile_expert, int32_t *tile_rows,
+                       int32_t *counts, int32_t *meta, AlignSlotWeights slot_weights, const QuantRows &q, hipStream_t stream)
+{
+    const int P = T * k;
+    if (P < 1 || P > kAlignOneLaunchMaxP) {
+        set_error("align_quant: P=%d", P);
+        return RAMP_EINVAL;
+    }
+    const int cap = (int)ramp_align_capacity(T, k, E, bm), B = num_blocks(P);
+    size_t blocks = ((size_t)q.rows * (q.K / kGroup) + NT / 16 - 1) / (NT / 16);
+    if (blocks > (size_t)kNumCU * 8) blocks = (size_t)kNumCU * 8;
+    hipLaunchKernelGGL(align_quant_kernel, dim3((unsigned)(B + blocks)), dim3(NT), align_lds_bytes(E), stream, ids, P, B, E, bm, cap,
+                       sorted, tile_expert, tile_rows, counts, meta, slot_weights, q);
+    return check_launch("align_quant_kernel");
 }
 
 }  // namespace ramp

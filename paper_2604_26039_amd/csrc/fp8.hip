@@ -27,8 +27,6 @@
 namespace ramp {
 namespace {
 
-constexpr int kGroup = 128;  // k-values per scale block
-
 __host__ __device__ inline int scale_stride(int K) { return (K / kGroup + 3) / 4 * 4; }
 
 struct Fp8Layout {
@@ -57,34 +55,11 @@ Fp8Layout fp8_layout(const ramp_shape &s)
 
 // ---- quantisers -----------------------------------------------------------------------------------------------
 
-// src bf16 [rows, K] row-major -> codes [rows, K], scale bytes [rows, stride].  Rows at or past *n_rows_dev (when given) are
-// skipped.  Bound by memory, and at small sizes by the launch: K is a multiple of the group, so the groups are consecutive in
-// both arrays; 16 lanes take one, a 16-byte load and an 8-byte store each, and the maximum is four lane exchanges.  The vector
-// types carry the alignment of one value: the entry point takes any address.
-typedef uint32_t UnalignedWords4 __attribute__((ext_vector_type(4), aligned(2)));
-typedef uint32_t UnalignedWords2 __attribute__((ext_vector_type(2), aligned(1)));
-__global__ __launch_bounds__(256) void quant_rows_kernel(const uint16_t *__restrict__ src, int rows, int K,
-                                                         uint8_t *__restrict__ codes, uint8_t *__restrict__ sb, int stride,
-                                                         const int32_t *__restrict__ n_rows_dev, const int32_t *pred,
-                                                         int pred_value)
+// Rows at or past *n_rows_dev (when given) are skipped.
+__global__ __launch_bounds__(256) void quant_rows_kernel(QuantRows q, const int32_t *__restrict__ n_rows_dev)
 {
-    if (launch_deselected(pred, pred_value)) return;
-    const int sub = threadIdx.x & 15;
-    const int groups = K / kGroup;
-    const int live_rows = n_rows_dev ? min(rows, *n_rows_dev) : rows;
-    const size_t total = (size_t)live_rows * groups;
-    const size_t step = (size_t)gridDim.x * (blockDim.x / 16);
-    for (size_t g = (size_t)blockIdx.x * (blockDim.x / 16) + (threadIdx.x >> 4); g < total; g += step) {
-        const UnalignedWords4 v = *reinterpret_cast<const UnalignedWords4 *>(src + g * kGroup + sub * 8);
-        const uint32_t w[4] = {v[0], v[1], v[2], v[3]};
-        uint32_t c[2];
-        const uint32_t b = quantise_group<4, 1, 16>(w, c);
-        *reinterpret_cast<UnalignedWords2 *>(codes + g * kGroup + sub * 8) = UnalignedWords2{c[0], c[1]};
-        if (sub == 0) {
-            const size_t row = (total >> 32) ? g / groups : (uint32_t)g / (uint32_t)groups;
-            sb[row * (size_t)stride + (g - row * groups)] = (uint8_t)b;
-        }
-    }
+    if (n_rows_dev) q.rows = min(q.rows, *n_rows_dev);
+    quantise_rows(q, (size_t)blockIdx.x * (blockDim.x / 16), (size_t)gridDim.x * (blockDim.x / 16));
 }
 
 // Weight quantiser and packer: src [E][K][F] bf16 (F contiguous) -> E4M3 fragments [E][F/16][K/128][2 KB] and the scale byte
@@ -554,15 +529,13 @@ Fp8Workspace fp8_workspace(const ramp_shape &s, const ramp_config &c)
     return w;
 }
 
-int launch_quant_rows(const uint16_t *src, int rows, int K, uint8_t *codes, uint8_t *sb, int sb_stride, const int32_t *n_rows_dev,
-                      const int32_t *pred, int pred_value, hipStream_t st)
+int launch_quant_rows(const QuantRows &q, const int32_t *n_rows_dev, hipStream_t st)
 {
-    if (rows <= 0) return RAMP_OK;
-    const size_t groups = (size_t)rows * (K / kGroup);
+    if (q.rows <= 0) return RAMP_OK;
+    const size_t groups = (size_t)q.rows * (q.K / kGroup);
     size_t blocks = (groups + 15) / 16;
     if (blocks > (size_t)kNumCU * 32) blocks = (size_t)kNumCU * 32;
-    hipLaunchKernelGGL(quant_rows_kernel, dim3((unsigned)blocks), dim3(256), 0, st, src, rows, K, codes, sb, sb_stride,
-                       n_rows_dev, pred, pred_value);
+    hipLaunchKernelGGL(quant_rows_kernel, dim3((unsigned)blocks), dim3(256), 0, st, q, n_rows_dev);
     return check_launch("quant_rows_kernel");
 }
 
@@ -677,8 +650,9 @@ extern "C" int ramp_fp8_quantize_rows(const void *src, int rows, int K, void *co
         set_error("fp8_quantize_rows: bad argument (K must be a multiple of 128)");
         return RAMP_EINVAL;
     }
-    return launch_quant_rows(static_cast<const uint16_t *>(src), rows, K, static_cast<uint8_t *>(codes),
-                             static_cast<uint8_t *>(scales), scale_stride(K), nullptr, nullptr, 0, static_cast<hipStream_t>(stream));
+    return launch_quant_rows(QuantRows{static_cast<const uint16_t *>(src), rows, K, static_cast<uint8_t *>(codes),
+                                       static_cast<uint8_t *>(scales), scale_stride(K)},
+                             nullptr, static_cast<hipStream_t>(stream));
 }
 
 extern "C" size_t ramp_fused_moe_fp8_workspace_bytes(const ramp_shape *shape, const ramp_config *cfg)
@@ -802,10 +776,18 @@ extern "C" int ramp_fused_moe_fp8(const ramp_shape *shape, const ramp_config *cf
 
     AlignSlotWeights sw = {nullptr, nullptr};
     if (k->launch_pp) sw = AlignSlotWeights{topk_w, reinterpret_cast<float *>(base + w.slot_w)};
-    if (int rc = launch_align(topk_ids, s.T, s.k, s.E, cfg->bm, sorted, tile_expert, tile_rows, counts, meta, base + w.align_ws,
-                              w.align_ws_bytes, st, nullptr, 0, sw))
-        return rc;
-    if (int rc = launch_quant_rows(static_cast<const uint16_t *>(X), s.T, s.H, xq, xs, w.xs_stride, nullptr, nullptr, 0, st)) return rc;
+    const QuantRows qx = {static_cast<const uint16_t *>(X), s.T, s.H, xq, xs, w.xs_stride};
+    if (g.P <= kAlignOneLaunchMaxP) {
+        // neither needs the other's result: one launch as long as the align is one (past that the align is two, and the hidden
+        // state large enough that a launch more is under a hundredth of the layer)
+        if (int rc = launch_align_quant(topk_ids, s.T, s.k, s.E, cfg->bm, sorted, tile_expert, tile_rows, counts, meta, sw, qx, st))
+            return rc;
+    } else {
+        if (int rc = launch_align(topk_ids, s.T, s.k, s.E, cfg->bm, sorted, tile_expert, tile_rows, counts, meta, base + w.align_ws,
+                                  w.align_ws_bytes, st, nullptr, 0, sw))
+            return rc;
+        if (int rc = launch_quant_rows(qx, nullptr, st)) return rc;
+    }
 
     if (k->launch_pp) {
         g.slot_w = sw.slot_w;
@@ -864,7 +846,7 @@ extern "C" int ramp_fused_moe_fp8(const ramp_shape *shape, const ramp_config *cf
     if (int rc = check_launch("moe_fp8_kernel<1>")) return rc;
 
     // the activation, per slot and 128 features; rows past the padded length of this call are skipped
-    if (int rc = launch_quant_rows(a_buf, (int)w.cap, s.I, aq, as, w.as_stride, meta, nullptr, 0, st)) return rc;
+    if (int rc = launch_quant_rows(QuantRows{a_buf, (int)w.cap, s.I, aq, as, w.as_stride}, meta, st)) return rc;
 
     // down-projection
     f.act_q = aq;

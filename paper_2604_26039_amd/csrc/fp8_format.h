@@ -4,7 +4,11 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "ramp_internal.h"
+
 namespace ramp {
+
+constexpr int kGroup = 128;  // k-values per scale block
 
 // E8M0 byte of the smallest power of two s with amax / s <= 448 (448 = 1.75 * 2^8): from the fp32 bits of amax.
 __device__ __forceinline__ uint32_t e8m0_of_amax(float amax)
@@ -109,6 +113,31 @@ __device__ __forceinline__ uint32_t quantise_group(const uint32_t *w, uint32_t *
         codes[i] = __builtin_bit_cast(uint32_t, r);
     }
     return b;
+}
+
+// src bf16 [rows, K] row-major -> codes [rows, K], scale bytes [rows, stride].  Bound by memory, and at small sizes by the
+// launch: K is a multiple of the group, so the groups are consecutive in both arrays; 16 lanes take one, a 16-byte load and an
+// 8-byte store each, and the maximum is four lane exchanges.  The vector types carry the alignment of one value: the
+// quantising entry point takes any address.
+// first, step: group of the workgroup's first 16 lanes, and groups of the whole launch.
+typedef uint32_t UnalignedWords4 __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t UnalignedWords2 __attribute__((ext_vector_type(2), aligned(1)));
+__device__ __forceinline__ void quantise_rows(const QuantRows &q, size_t first, size_t step)
+{
+    const int sub = threadIdx.x & 15;
+    const int groups = q.K / kGroup;
+    const size_t total = (size_t)q.rows * groups;
+    for (size_t g = first + (threadIdx.x >> 4); g < total; g += step) {
+        const UnalignedWords4 v = *reinterpret_cast<const UnalignedWords4 *>(q.src + g * kGroup + sub * 8);
+        const uint32_t w[4] = {v[0], v[1], v[2], v[3]};
+        uint32_t c[2];
+        const uint32_t b = quantise_group<4, 1, 16>(w, c);
+        *reinterpret_cast<UnalignedWords2 *>(q.codes + g * kGroup + sub * 8) = UnalignedWords2{c[0], c[1]};
+        if (sub == 0) {
+            const size_t row = (total >> 32) ? g / groups : (uint32_t)g / (uint32_t)groups;
+            q.sb[row * (size_t)q.stride + (g - row * groups)] = (uint8_t)b;
+        }
+    }
 }
 
 }  // namespace ramp

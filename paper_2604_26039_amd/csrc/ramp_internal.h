@@ -60,6 +60,17 @@ struct AlignChoices {
 int launch_align_selected(const int32_t *ids, int P, int E, const float *topk_w, char *base, const int32_t *sel, int n_cand,
                           const AlignChoices &choices, hipStream_t stream);
 
+// bf16 rows to quantise to E4M3 codes and a scale byte per 128 values (fp8_format.h)
+struct QuantRows {
+    const uint16_t *src;
+    int rows, K;
+    uint8_t *codes, *sb;
+    int stride;  // scale bytes per row
+};
+// Align of 1 .. kAlignOneLaunchMaxP pairs and, by the other workgroups of the same launch, the quantised hidden state.
+int launch_align_quant(const int32_t *ids, int T, int k, int E, int bm, int32_t *sorted, int32_t *tile_expert, int32_t *tile_rows,
+                       int32_t *counts, int32_t *meta, AlignSlotWeights slot_weights, const QuantRows &q, hipStream_t stream);
+
 // ---- packed weights ----
 // One fragment = 16 weight rows x 32 k-values = 512 bf16 = 1 KB, stored in the lane order
 // of the A operand of v_mfma_f32_16x16x32_bf16: element (row r, k = 8*q + j) at (q*16 + r)*8 + j.

@@ -1,0 +1,49 @@
+"""Align inside a launch that does something else too: with the quantised hidden state of the FP8 layer, and once for all
+candidates of the device-selected layer.  Sizes around a workgroup's 1024 pairs and the 16384 pairs where the align becomes a
+launch of its own again."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2604_26039_amd import ramp, synth, tuner
+from test_gpu_fp8 import DEV, Fp8Layer, assert_close
+
+pytestmark = pytest.mark.gpu
+S = synth.Shape("am", 384, 384, 20, 2)
+
+
+@pytest.mark.parametrize("T", [1, 33, 512, 513, 8192, 8193])
+def test_fp8_layer(T):
+    L = Fp8Layer(S, T, seed=T)
+    ids, w = synth.routing(T, S, 0.5, seed=2)
+    ids[T // 2, 1] = S.E + 3                                            # a dropped pair
+    rows = sorted({0, T // 2, T - 1, *np.random.default_rng(T).integers(0, T, 6).tolist()})
+    want = L.oracle_rows(ids, w, rows=rows)
+    for cfg in [c for c in ramp.fp8_configs(L.rs) if not c.mode & 0x100]:
+        print(f"case T={T} {cfg}", flush=True)
+        assert_close(L.run(cfg, ids, w)[torch.tensor(rows, device=DEV)], want, f"T={T} {cfg}")
+
+
+@pytest.mark.parametrize("T", [8192, 8193])
+def test_selected_layer(T):
+    X, Wg, Wu, Wd = synth.layer_tensors(S, T, seed=T, device=DEV, x_std=1.0)
+    rs = ramp.Shape(T, S.k, S.E, S.H, S.I)
+    packed = torch.empty(ramp.pack_bytes(rs), dtype=torch.uint8, device=DEV)
+    ramp.pack_weights(rs, Wg, Wu, Wd, packed)
+    ids, w = synth.routing(T, S, 0.5, seed=5)
+    d_ids = torch.from_numpy(np.ascontiguousarray(ids, np.int32)).to(DEV)
+    d_w = torch.from_numpy(np.ascontiguousarray(w, np.float32)).to(DEV)
+    cfgs = tuner.Family.of(S, T).cfgs
+    # a tile with per-slot weights, one without, and the smallest and the largest token block
+    cands = [next(c for c in cfgs if c.mode & 0x400), next(c for c in cfgs if not c.mode & 0x700),
+             min(cfgs, key=lambda c: c.bm), max(cfgs, key=lambda c: c.bm)]
+    nbytes = ramp.fused_moe_selected_workspace_bytes(rs, cands)
+    for pos, cfg in enumerate(cands):
+        print(f"case T={T} {cfg}", flush=True)
+        ref, out = (torch.zeros((T, S.H), dtype=torch.bfloat16, device=DEV) for _ in range(2))
+        ws = torch.full((ramp.fused_moe_workspace_bytes(rs, cfg),), 0xFF, dtype=torch.uint8, device=DEV)
+        ramp.fused_moe(rs, cfg, X, d_ids, d_w, packed, ref, ws)
+        ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device=DEV)
+        ramp.fused_moe_selected(rs, cands, torch.tensor([pos], dtype=torch.int32, device=DEV), X, d_ids, d_w, packed, out, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16), ref.view(torch.int16)), f"candidate {pos} {cfg}"
