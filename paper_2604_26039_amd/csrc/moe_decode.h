@@ -10,7 +10,11 @@
 //              ONE token and all of its k pairs; wavefront (j, wk) streams expert e_j's weight rows of the slice over
 //              1/WK of the reduction, the partial sums meet in LDS and are added in fixed order (wk, then j), so the
 //              result is bit-identical from run to run and no per-pair rows, no combine launch and no atomics exist.
-// Workgroup 0 of launch 1 also writes the align result (sorted pairs, tile tables, counts, meta) to the workspace,
+// Bound by HBM for large experts, by the latency of the chain ids -> expert -> weights -> sum for small ones (an OLMoE-shaped up
+// launch takes 16 us for 67 MB, its FP8 twin 12 us for 33 MB: some 7 us do not depend on the bytes).  So the tile's expert is
+// found by the lane that holds the tile's first pair, without a search, and the router weights are in LDS before the final sum
+// needs them: one OLMoE-shaped token 25.4 -> 24.5 us in bf16, 18.0 -> 17.2 us in FP8.
+// Workgroup 0 of launch 1 writes the align result (sorted pairs, tile tables, counts, meta) to the workspace,
 // so the layout query of the general path keeps its meaning.
 #pragma once
 
@@ -32,11 +36,13 @@ __global__ __launch_bounds__(WF *WK * 64) void moe_decode_up_kernel(GemmArgs a, 
     __shared__ int n_lds[kAlignMaxE];
     __shared__ int toff[kAlignMaxE + 1];
     __shared__ int tile_pair[BM];
-    __shared__ int tile_info[2];  // expert of this workgroup's M-tile, number of M-tiles of the call
+    __shared__ int tile_expert, tile_count;  // expert of this workgroup's M-tile, number of M-tiles of the call
 
     if (launch_deselected(a.pred, a.pred_value)) return;
-    const int n_tile = blockIdx.x % a.n_tiles;
-    const int m_tile = blockIdx.x / a.n_tiles;
+    // workgroup 0 only writes the align result: in front of a tile of its own that would be the last tile to end
+    const int tile = (int)blockIdx.x - 1;
+    const int n_tile = tile % a.n_tiles;
+    const int m_tile = tile < 0 ? a.m_tiles_cap : tile / a.n_tiles;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
 
@@ -45,29 +51,26 @@ __global__ __launch_bounds__(WF *WK * 64) void moe_decode_up_kernel(GemmArgs a, 
     __syncthreads();
     if (wave == 0) {
         int e, rank;
-        tiny_align_wavefront(d.ids, a.P, d.E, d.bm, lane, n_lds, toff, e, rank);
+        tiny_align_wavefront(d.ids, a.P, d.E, BM, lane, n_lds, toff, e, rank);
         if (e >= 0) {
             const int slot = toff[e] + rank;
-            if (slot / BM == m_tile) tile_pair[slot - m_tile * BM] = lane;
+            if (slot / BM == m_tile) {
+                tile_pair[slot - m_tile * BM] = lane;
+                if (slot % BM == 0) tile_expert = e;  // the tile's first row: every tile has a pair there, one lane
+            }
         }
-        if (lane == 0) {
-            const int m_tiles = toff[d.E] / BM;
-            int owner = -1, rows = 0;
-            if (m_tile < m_tiles) tiny_align_tile(m_tile, d.E, BM, n_lds, toff, owner, rows);
-            tile_info[0] = owner;
-            tile_info[1] = m_tiles;
-        }
+        if (lane == 0) tile_count = toff[d.E] / BM;
         if (blockIdx.x == 0)
-            tiny_align_emit(a.P, d.E, d.bm, d.cap, lane, n_lds, toff, e, rank, d.ids, d.sorted, d.tile_expert, d.tile_rows,
+            tiny_align_emit(a.P, d.E, BM, d.cap, lane, n_lds, toff, e, rank, d.ids, d.sorted, d.tile_expert, d.tile_rows,
                             d.counts, d.meta);
     }
     __syncthreads();
-    if (m_tile >= tile_info[1]) return;
+    if (m_tile >= tile_count) return;
 
     // ---- up-projection of this M-tile x feature tile, as moe_stream_kernel<1, ...>
     const int wf = wave % WF, wk = wave / WF;
     const int r16 = lane & 15, q = lane >> 4;
-    const int e = tile_info[0];
+    const int e = __builtin_amdgcn_readfirstlane(tile_expert);
     const int K = a.K, KST = K / 32;
     const int f0 = n_tile * FEAT_PER_TILE + wf * FPW * 16;
     const uint16_t *wexp = a.wpacked + (size_t)e * a.expert_stride;
@@ -171,9 +174,11 @@ template <int FBW, int U>
 __global__ __launch_bounds__(1024) void moe_decode_down_kernel(DecodeDownArgs d)
 {
     __shared__ float red[16][FBW * 16];  // [wavefront][feature of the slice]
+    __shared__ PairWeights weight;
     if (launch_deselected(d.pred, d.pred_value)) return;
     const int n_ft = d.H / (16 * FBW);
     const int t = blockIdx.x / n_ft, ft = blockIdx.x % n_ft;
+    const PairWeight own_weight = load_pair_weight(d, t);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int WK = 16 / d.k;
@@ -236,18 +241,12 @@ __global__ __launch_bounds__(1024) void moe_decode_down_kernel(DecodeDownArgs d)
 #pragma unroll
             for (int c = 0; c < 4; ++c) red[wave][i * 16 + q * 4 + c] = acc[i][c];
     }
+    store_pair_weight(weight, d, own_weight);
     __syncthreads();
     // one thread per output feature of the slice: sum the split-K partials in wk order, weight, sum over j in order
     if ((int)threadIdx.x < FBW * 16) {
         const int i = threadIdx.x / 16, r = threadIdx.x % 16;
-        float y = 0.f;
-        for (int jj = 0; jj < d.k; ++jj) {
-            const int id = d.ids[t * d.k + jj];
-            if (id < 0 || id >= d.E) continue;
-            float s = red[jj * WK][threadIdx.x];
-            for (int w = 1; w < WK; ++w) s += red[jj * WK + w][threadIdx.x];
-            y += d.topk_w[t * d.k + jj] * s;
-        }
+        const float y = sum_of_pairs(WK, weight, [&](int w) { return red[w][threadIdx.x]; });
         d.out[(size_t)t * d.H + packed_row_feature(ft * FBW + i, r)] = f32_to_bf16_bits(y);
     }
 }
@@ -255,8 +254,8 @@ __global__ __launch_bounds__(1024) void moe_decode_down_kernel(DecodeDownArgs d)
 template <int BM, int FBW, int WF, int WK, int U>
 void launch_decode_up(const GemmArgs &a, const DecodeArgs &d, hipStream_t stream)
 {
-    const dim3 grid((unsigned)a.n_tiles * (unsigned)a.m_tiles_cap), block(WF * WK * 64);
-    if (grid.x == 0) return;
+    if (a.n_tiles <= 0 || a.m_tiles_cap <= 0) return;
+    const dim3 grid((unsigned)a.n_tiles * (unsigned)a.m_tiles_cap + 1), block(WF * WK * 64);
     hipLaunchKernelGGL((moe_decode_up_kernel<BM, FBW, WF, WK, U>), grid, block, 0, stream, a, d);
 }
 

@@ -8,7 +8,7 @@
 // trips through memory, are gone, for about 60 instructions per 16 rows and slice that hide under the weight loads.
 //
 // Measured (layer, best configuration of each family, against the best LDS-staged or persistent FP8 tile): OLMoE-shaped T = 1
-// 36 -> 20 us (two launches instead of six), Qwen3-shaped T = 8 80 -> 61 us, Mixtral-shaped T = 1 222 -> 75 us and T = 8
+// 36 -> 17 us (two launches instead of six), Qwen3-shaped T = 8 80 -> 61 us, Mixtral-shaped T = 1 222 -> 75 us and T = 8
 // 297 -> 252 us (5.6 TB/s of weights), DeepSeek-V3-shaped T = 16 844 -> 786 us (6.05 TB/s).  From about 16 rows per expert on
 // the tiles with shared operands are the better ones (Mixtral-shaped T = 128: 317 us against 397).
 #pragma once
@@ -215,33 +215,33 @@ __global__ __launch_bounds__(WF *WK * 64) void moe_fp8_decode_up_kernel(GemmArgs
     __shared__ int n_lds[kAlignMaxE];
     __shared__ int toff[kAlignMaxE + 1];
     __shared__ int tile_pair[BM];
-    __shared__ int tile_info[2];  // expert of this workgroup's M-tile, number of M-tiles of the call
-    const int n_tile = blockIdx.x % a.n_tiles, m_tile = blockIdx.x / a.n_tiles;
+    __shared__ int tile_expert, tile_count;  // expert of this workgroup's M-tile, number of M-tiles of the call
+    // workgroup 0 only writes the align result: in front of a tile of its own that would be the last tile to end
+    const int tile = (int)blockIdx.x - 1;
+    const int n_tile = tile % a.n_tiles;
+    const int m_tile = tile < 0 ? a.m_tiles_cap : tile / a.n_tiles;
     const int lane = threadIdx.x & 63, r16 = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for (int x = threadIdx.x; x < BM; x += blockDim.x) tile_pair[x] = a.P;
     __syncthreads();
     if (wave == 0) {
         int e, rank;
-        tiny_align_wavefront(d.ids, a.P, d.E, d.bm, lane, n_lds, toff, e, rank);
+        tiny_align_wavefront(d.ids, a.P, d.E, BM, lane, n_lds, toff, e, rank);
         if (e >= 0) {
             const int slot = toff[e] + rank;
-            if (slot / BM == m_tile) tile_pair[slot - m_tile * BM] = lane;
+            if (slot / BM == m_tile) {
+                tile_pair[slot - m_tile * BM] = lane;
+                if (slot % BM == 0) tile_expert = e;  // the tile's first row: every tile has a pair there, one lane
+            }
         }
-        if (lane == 0) {
-            const int m_tiles = toff[d.E] / BM;
-            int owner = -1, rows = 0;
-            if (m_tile < m_tiles) tiny_align_tile(m_tile, d.E, BM, n_lds, toff, owner, rows);
-            tile_info[0] = owner;
-            tile_info[1] = m_tiles;
-        }
+        if (lane == 0) tile_count = toff[d.E] / BM;
         if (blockIdx.x == 0)
-            tiny_align_emit(a.P, d.E, d.bm, d.cap, lane, n_lds, toff, e, rank, d.ids, d.sorted, d.tile_expert, d.tile_rows, d.counts,
+            tiny_align_emit(a.P, d.E, BM, d.cap, lane, n_lds, toff, e, rank, d.ids, d.sorted, d.tile_expert, d.tile_rows, d.counts,
                             d.meta);
     }
     __syncthreads();
-    if (m_tile >= tile_info[1]) return;
-    const int e = __builtin_amdgcn_readfirstlane(tile_info[0]);
+    if (m_tile >= tile_count) return;
+    const int e = __builtin_amdgcn_readfirstlane(tile_expert);
     int pair_of[NB];
     uint32_t act_row[NB];
 #pragma unroll
@@ -261,8 +261,10 @@ template <int FBW, int U>
 __global__ __launch_bounds__(1024) void moe_fp8_decode_down_kernel(DecodeDownArgs d, Fp8StreamArgs f)
 {
     __shared__ float red[16][FBW * 16];
+    __shared__ PairWeights weight;
     const int n_ft = d.H / (16 * FBW);
     const int t = blockIdx.x / n_ft, ft = blockIdx.x % n_ft;
+    const PairWeight own_weight = load_pair_weight(d, t);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int WK = 16 / d.k;
@@ -291,17 +293,11 @@ __global__ __launch_bounds__(1024) void moe_fp8_decode_down_kernel(DecodeDownArg
 #pragma unroll
             for (int c = 0; c < 4; ++c) red[wave][i * 16 + q * 4 + c] = acc[i][0][c];
     }
+    store_pair_weight(weight, d, own_weight);
     __syncthreads();
     if ((int)threadIdx.x < FBW * 16) {
         const int i = threadIdx.x / 16, r = threadIdx.x % 16;
-        float y = 0.f;
-        for (int jj = 0; jj < d.k; ++jj) {
-            const int id = d.ids[t * d.k + jj];
-            if (id < 0 || id >= d.E) continue;
-            float s = red[jj * WK][threadIdx.x];
-            for (int w = 1; w < WK; ++w) s += red[jj * WK + w][threadIdx.x];
-            y += d.topk_w[t * d.k + jj] * s;
-        }
+        const float y = sum_of_pairs(WK, weight, [&](int w) { return red[w][threadIdx.x]; });
         d.out[(size_t)t * d.H + packed_row_feature(ft * FBW + i, r)] = f32_to_bf16_bits(y);
     }
 }
@@ -320,8 +316,8 @@ void launch_fp8_stream(int stage, const GemmArgs &a, const Fp8StreamArgs &f, hip
 template <int BM, int FBW, int WF, int WK, int U>
 void launch_fp8_decode_up(const GemmArgs &a, const Fp8StreamArgs &f, const DecodeArgs &d, hipStream_t stream)
 {
-    const dim3 grid((unsigned)a.n_tiles * (unsigned)a.m_tiles_cap), block(WF * WK * 64);
-    if (grid.x == 0) return;
+    if (a.n_tiles <= 0 || a.m_tiles_cap <= 0) return;
+    const dim3 grid((unsigned)a.n_tiles * (unsigned)a.m_tiles_cap + 1), block(WF * WK * 64);
     hipLaunchKernelGGL((moe_fp8_decode_up_kernel<BM, FBW, WF, WK, U>), grid, block, 0, stream, a, f, d);
 }
 

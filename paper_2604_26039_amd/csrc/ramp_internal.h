@@ -227,6 +227,46 @@ struct DecodeDownArgs {
     const int32_t *pred;
     int pred_value;
 };
+
+// Router weights of one token's pairs for the final sum of the decode down-projections.  Thread j < k loads pair j's when the
+// kernel starts and stores them in LDS in front of its last barrier: read by the sum itself, id and weight of one pair after the
+// other, they were 2 * k dependent loads behind it.
+struct PairWeights {
+    float w[16];
+    int live[16];  // the pair's expert exists
+};
+struct PairWeight {
+    int id;
+    float w;
+};
+__device__ __forceinline__ PairWeight load_pair_weight(const DecodeDownArgs &d, int t)
+{
+    PairWeight p = {-1, 0.f};
+    if ((int)threadIdx.x < d.k) p = PairWeight{d.ids[t * d.k + threadIdx.x], d.topk_w[t * d.k + threadIdx.x]};
+    return p;
+}
+__device__ __forceinline__ void store_pair_weight(PairWeights &all, const DecodeDownArgs &d, PairWeight p)
+{
+    if ((int)threadIdx.x >= d.k) return;
+    all.w[threadIdx.x] = p.w;
+    all.live[threadIdx.x] = p.id >= 0 && p.id < d.E;
+}
+// Sum over the 16 wavefronts' partial sums: the WK (a power of two) of one pair in order, weighted, then over the pairs in order.
+template <class Partial>
+__device__ __forceinline__ float sum_of_pairs(int WK, const PairWeights &p, Partial partial)
+{
+    float part[16];
+#pragma unroll
+    for (int w = 0; w < 16; ++w) part[w] = partial(w);
+    const int shift = 31 - __clz(WK);
+    float y = 0.f, s = 0.f;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+        s = (w & (WK - 1)) ? s + part[w] : part[w];
+        if ((w & (WK - 1)) == WK - 1 && p.live[w >> shift]) y += p.w[w >> shift] * s;
+    }
+    return y;
+}
 constexpr int kDecodeMaxPairs = 64;
 void launch_decode_down_any(const DecodeDownArgs &d, hipStream_t stream);
 
