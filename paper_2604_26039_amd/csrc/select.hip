@@ -37,14 +37,15 @@ struct ResultHeader {
 };
 static_assert(sizeof(ResultHeader) == 16, "result layout is part of the ABI");
 
+// Bound by latency: one workgroup, a chain of dependent steps.  So the loads of the table and of four ids per lane are in flight
+// together, every sum over the experts has a wavefront of its own, and the counts leave for host memory under the model.
 __global__ __launch_bounds__(NT) void select_kernel(const int32_t *ids, int P, int B, const int32_t *block_counts, int E,
                                                     int n_cfg, const TableHeader *table, ResultHeader *res,
                                                     uint32_t ticket, int32_t *best_dev)
 {
     __shared__ int hist[kAlignMaxE];
-    __shared__ int mt[kMaxBm];
-    __shared__ int active_pairs[2];
-    const int tid = threadIdx.x, lane = tid & 63;
+    __shared__ int sums[kMaxBm + 2];  // M-tiles for every distinct bm, active experts, routed pairs
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // n_cfg is the caller's (the result block was sized with it); a table that is not one of
     // ramp_select_table_build's for that many configurations yields best = -1 and no predictions
     const bool table_ok = table->magic == kMagic && table->n_cfg == n_cfg && table->n_bm >= 1 && table->n_bm <= kMaxBm;
@@ -54,49 +55,53 @@ __global__ __launch_bounds__(NT) void select_kernel(const int32_t *ids, int P, i
     double *pred = reinterpret_cast<double *>(res + 1);
     int32_t *counts_out = reinterpret_cast<int32_t *>(pred + n_cfg);
 
-    if (tid < kMaxBm) mt[tid] = 0;
-    if (tid < 2) active_pairs[tid] = 0;
     // ---- histogram: own pass over the ids (small inputs), or the per-chunk histograms of align_hist_kernel
     if (tid < E) hist[tid] = 0;
     __syncthreads();
+    TableRow own_row = {};  // of this lane's first configuration, on its way while the histogram is made
+    if (wave == 0 && lane < n_eval) own_row = rows[lane];
+    const int own_bm = wave < n_bm ? table->bm[wave] : 1;
     if (B == 0) {
-        for (int p = tid; p < P; p += NT) {
-            const int v = ids[p];
-            if (v >= 0 && v < E) atomicAdd(&hist[v], 1);
+        for (int base = tid; base < P; base += 4 * NT) {  // four loads in flight
+            int v[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = base + i * NT < P ? ids[base + i * NT] : -1;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (v[i] >= 0 && v[i] < E) atomicAdd(&hist[v[i]], 1);
         }
     } else {
         // all lanes share the B x E chunk counts (coalesced; integer sums do not depend on the order)
         for (int i = tid; i < B * E; i += NT) atomicAdd(&hist[i % E], block_counts[i]);
     }
     __syncthreads();
-    const int n = (tid < E) ? hist[tid] : 0;
-    // ---- sums over the experts: M-tiles for every distinct bm, active experts, routed pairs
-    if ((tid & ~63) < E) {  // wavefronts that hold experts
-        for (int j = 0; j < n_bm + 2; ++j) {
-            int v;
-            if (j < n_bm) {
-                const int bm = table->bm[j];
-                v = (n + bm - 1) / bm;
-            } else {
-                v = (j == n_bm) ? (n > 0 ? 1 : 0) : n;
-            }
-#pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, kWave);
-            if (lane == 0) atomicAdd(j < n_bm ? &mt[j] : &active_pairs[j - n_bm], v);
+    // ---- sums over the experts: a wavefront per sum
+    for (int j = wave; j < n_bm + 2; j += NW) {
+        const int bm = j == wave ? own_bm : (j < n_bm ? table->bm[j] : 1);
+        int v = 0;
+        for (int e = lane; e < E; e += kWave) {
+            const int n = hist[e];
+            v += j < n_bm ? (n + bm - 1) / bm : (j == n_bm ? (n > 0 ? 1 : 0) : n);
         }
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, kWave);
+        if (lane == 0) sums[j] = v;
     }
     __syncthreads();
     if (tid >= kWave) return;
+    // on their way to host memory while the model is evaluated
+    for (int e = lane; e < E; e += kWave) counts_out[e] = hist[e];
     // ---- the model for every configuration, and the lowest index with the smallest prediction
     const bool use_distinct = (flags & RAMP_CM_DISTINCT_TILES) != 0;
     const bool wave_floor = (flags & RAMP_CM_WAVE_FLOOR) != 0;
     const bool use_pairs = (flags & RAMP_CM_PAIRS) != 0;
     const bool use_rounds = (flags & RAMP_CM_ROUNDS) != 0;
-    const long long active = active_pairs[0], pairs = active_pairs[1];
+    const int *mt = sums;
+    const long long active = sums[n_bm], pairs = sums[n_bm + 1];
     int best = -1;
     double best_t = 0.0;
     for (int c = lane; c < n_eval; c += kWave) {
-        const TableRow r = rows[c];
+        const TableRow r = c == lane ? own_row : rows[c];
         const double g = (double)((long long)mt[r.bm_slot] * (long long)r.ntiles);
         double t = (double)r.theta[0];
         double gw = g;
@@ -131,7 +136,6 @@ __global__ __launch_bounds__(NT) void select_kernel(const int32_t *ids, int P, i
     }
     // Only this wavefront writes the result block: payload, one system-scope fence (one round trip to host
     // memory), then the word that carries the ticket.
-    for (int e = lane; e < E; e += kWave) counts_out[e] = hist[e];
     if (lane == 0) {
         res->n_cfg = n_cfg;
         res->reserved = 0;
