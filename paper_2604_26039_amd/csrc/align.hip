@@ -8,8 +8,8 @@
 //   - ranks inside an expert come from a wavefront ballot (lanes of lower index),
 //     a per-wavefront count table in LDS (wavefronts of lower index) and a running
 //     cursor (earlier chunks / earlier workgroups).
-// Up to 64 pairs a single wavefront does everything; up to kAlignOneLaunchMaxP pairs one launch of a workgroup per 1024
-// pairs, each of which counts all pairs itself; larger inputs take two launches (per-chunk histograms, then a kernel in which
+// Up to 64 pairs a single wavefront does everything; up to 2048 tokens and kAlignOneLaunchMaxP pairs one launch of a workgroup
+// per 1024 pairs, each of which counts all pairs itself; larger inputs take two launches (per-chunk histograms, then a kernel in which
 // every workgroup scans them and scatters its chunk); the histogram-only entry point ends with a small scan kernel.
 #include "ramp_internal.h"
 #include "align_tiny.h"
@@ -181,13 +181,19 @@ __global__ __launch_bounds__(NT) void histogram_kernel(const int32_t *ids, int P
 // the own chunk takes no atomics; the other chunks are counted with LDS atomics (sums, order independent) instead of in an
 // earlier launch.  Slots without a pair are filled from the scanned offsets, each by exactly one lane, so nothing has to be
 // filled before the scatter.  Per call in a captured graph: P = 2048, E = 8 7.2 -> 4.3 us; P = 4096,
-// E = 128, two launches before, 8.1 -> 5.1 us; P = 16384, E = 256 8.3 -> 7.7 us, where the limit lies.
+// E = 128, two launches before, 8.1 -> 5.1 us; P = 16384, E = 128 8.4 -> 7.4 us.
+//
+// Where the limit lies (align_is_one_launch): every workgroup counts every chunk, and pairs of one expert meet at one LDS word.
+// A token names an expert once, so at most one pair in k does: 16384 pairs with k = 8 take 7.3 us on the same eight experts
+// (two launches 8.3), but with k = 4 10.3 (8.1), k = 2 16.4 (7.9) and k = 1 29 us (8.4).  Up to 2048 tokens the time of
+// the worst routing is that of 2048 pairs on one expert.  One atomic per wavefront and distinct expert, found by ballots, is
+// slower with any routing: 14.6 us with E = 128.
 __device__ __forceinline__ void align_one_launch(const int32_t *ids, int P, int E, int bm, int cap, int32_t *sorted,
                                                  int32_t *tile_expert, int32_t *tile_rows, int32_t *counts, int32_t *meta,
                                                  AlignSlotWeights slot_weights, int B)
 {
     extern __shared__ int lds[];
-    // total[E] (other chunks; then all pairs) | first[E] (earlier chunks; then the chunk's first slot) | toff[E+1] | wsum[NW] |
+    // total[E] (later chunks; then all pairs) | first[E] (earlier chunks; then the chunk's first slot) | toff[E+1] | wsum[NW] |
     // dropped | wcnt[NW][E] of 16 bits
     int *total = lds, *first = total + E, *toff = first + E, *wsum = toff + E + 1, *dropped = wsum + NW;
     uint16_t *wcnt = reinterpret_cast<uint16_t *>(dropped + 1);
@@ -228,12 +234,10 @@ __device__ __forceinline__ void align_one_launch(const int32_t *ids, int P, int 
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            if (v[i] >= 0 && v[i] < E) {
-                atomicAdd(&total[v[i]], 1);
-                if (c + i < chunk) atomicAdd(&first[v[i]], 1);
-            } else if (other[i]) {
-                atomicAdd(dropped, 1);
-            }
+            const bool ok = v[i] >= 0 && v[i] < E;
+            if (ok) atomicAdd(c + i < chunk ? &first[v[i]] : &total[v[i]], 1);
+            const unsigned long long lost = __ballot(other[i] && !ok);
+            if (lost && lane == 0) atomicAdd(dropped, __popcll(lost));
         }
     }
     __syncthreads();
@@ -248,7 +252,7 @@ __device__ __forceinline__ void align_one_launch(const int32_t *ids, int P, int 
                 wcnt[w * E + tid] = (uint16_t)run;
                 run += c;
             }
-            n = total[tid] + run;
+            n = total[tid] + first[tid] + run;
             slots = (n + bm - 1) / bm * bm;
         }
         incl = slots;
@@ -510,7 +514,7 @@ static int launch_align_impl(const int32_t *ids, int T, int k, int E, int bm, in
         set_error("align: workspace %zu < %zu bytes", ws_bytes, need);
         return RAMP_ENOSPC;
     }
-    if (scatter && P <= kAlignOneLaunchMaxP) {
+    if (scatter && align_is_one_launch(T, k)) {
         hipLaunchKernelGGL(align_kernel, dim3(B > 0 ? B : 1), dim3(NT), align_lds_bytes(E), stream, ids, P, E, bm, cap, sorted,
                            tile_expert, tile_rows, counts, meta, pred, pred_value, slot_weights);
         return check_launch("align_kernel");

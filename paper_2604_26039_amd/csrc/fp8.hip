@@ -777,7 +777,7 @@ extern "C" int ramp_fused_moe_fp8(const ramp_shape *shape, const ramp_config *cf
     AlignSlotWeights sw = {nullptr, nullptr};
     if (k->launch_pp) sw = AlignSlotWeights{topk_w, reinterpret_cast<float *>(base + w.slot_w)};
     const QuantRows qx = {static_cast<const uint16_t *>(X), s.T, s.H, xq, xs, w.xs_stride};
-    if (g.P <= kAlignOneLaunchMaxP) {
+    if (align_is_one_launch(s.T, s.k)) {
         // neither needs the other's result: one launch as long as the align is one (past that the align is two, and the hidden
         // state large enough that a launch more is under a hundredth of the layer)
         if (int rc = launch_align_quant(topk_ids, s.T, s.k, s.E, cfg->bm, sorted, tile_expert, tile_rows, counts, meta, sw, qx, st))

@@ -700,7 +700,7 @@ extern "C" int ramp_fused_moe_selected(const ramp_shape *shape, int n_cand, cons
                                    w.tile_rows, w.counts, w.meta, w.slot_w};
         ++aligns;
     }
-    const bool shared_align = aligns > 1 && s.T * s.k <= kAlignOneLaunchMaxP;
+    const bool shared_align = aligns > 1 && align_is_one_launch(s.T, s.k);
     if (shared_align) {
         ProbeScope probe(1, st);
         if (int rc = launch_align_selected(topk_ids, s.T * s.k, s.E, topk_w, base, selected_idx, n_cand, choices, st)) return rc;

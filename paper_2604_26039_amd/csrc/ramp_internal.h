@@ -32,8 +32,10 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 constexpr int kAlignThreads = 1024;   // one workgroup = 16 wavefronts
 constexpr int kAlignChunk = 1024;     // pairs per workgroup in the multi-workgroup path
 constexpr int kAlignSingleMaxP = 2048; // up to this many pairs no workspace is needed
-// up to this many pairs every workgroup of one launch counts all of them itself; past it, two launches share the counting
+// up to this many pairs and tokens every workgroup of one launch counts all pairs itself; past it, two launches share the counting
 constexpr int kAlignOneLaunchMaxP = 16384;
+constexpr int kAlignOneLaunchMaxT = 2048;
+inline bool align_is_one_launch(int T, int k) { return T <= kAlignOneLaunchMaxT && (long long)T * k <= kAlignOneLaunchMaxP; }
 constexpr int kAlignMaxE = 1024;
 
 // Optional second output of the scatter: slot_w[s] = topk_w[sorted[s]] for the slots that hold a pair (the others are
