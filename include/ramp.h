@@ -182,6 +182,7 @@ int ramp_fused_moe_workspace_layout(const ramp_shape *shape, const ramp_config *
 int ramp_fp8_num_configs(const ramp_shape *shape);
 int ramp_fp8_get_config(const ramp_shape *shape, int idx, ramp_config *out);
 int ramp_fp8_config_wave_capacity(const ramp_config *cfg);
+int ramp_fp8_config_runtime_occupancy(const ramp_config *cfg, int *wg_per_cu /*host out [2]*/); /* as ramp_config_runtime_occupancy */
 size_t ramp_fp8_pack_bytes(const ramp_shape *shape);
 int ramp_fp8_pack_weights(const ramp_shape *shape, const void *W_gate, const void *W_up, const void *W_down /*dev bf16*/,
                           void *packed_fp8 /*dev, 256 B aligned*/, void *stream);

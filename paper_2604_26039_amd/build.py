@@ -29,13 +29,15 @@ KERNEL_SOURCES = ["gemm_group0.hip", "gemm_group1.hip", "gemm_group2.hip", "gemm
                   "gemm_group5.hip", "gemm_group6.hip", "gemm_group7.hip", "stream_group0.hip", "stream_group1.hip",
                   "stream_group2.hip"]
 SOURCES = ["align.hip", "select.hip", "pack.hip", "fused.hip", "fp8.hip"] + KERNEL_SOURCES + ["cost_model.cpp"]
+RESOURCE_SOURCES = KERNEL_SOURCES + ["fp8.hip"]  # hold projection kernels of a tile family
 HEADERS = ["ramp_internal.h", "moe_gemm.h", "moe_pingpong.h", "moe_stream.h", "moe_decode.h", "moe_fp8_pingpong.h", "moe_fp8_stream.h", "fp8_format.h", "align_tiny.h", "config_list.h", os.path.join(ROOT, "include", "ramp.h")]
 
 COMMON = ["-O3", "-fPIC", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-ffp-contract=off"]
 # packed fp32 ops are disabled on purpose: some of their forms have produced wrong results on this hardware
 HIP_FLAGS = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
              "-Wno-unused-command-line-argument"]
-FAMILIES = ("moe_gemm_kernel", "moe_pingpong_kernel", "moe_stream_kernel")
+FAMILIES = ("moe_gemm_kernel", "moe_pingpong_kernel", "moe_stream_kernel", "moe_fp8_kernel", "moe_fp8_pingpong_kernel",
+            "moe_fp8_stream_kernel")
 
 
 def _hipcc() -> str:
@@ -84,7 +86,7 @@ def _compile(src: str, force: bool, hdr_time: float) -> str:
     path = os.path.join(CSRC, src)
     obj = os.path.join(OBJ_DIR, src + ".o")
     res_json = os.path.join(OBJ_DIR, src + ".resources.json")
-    is_kernel = src in KERNEL_SOURCES
+    is_kernel = src in RESOURCE_SOURCES
     if (not force and os.path.exists(obj) and os.path.getmtime(obj) > max(os.path.getmtime(path), hdr_time)
             and (not is_kernel or os.path.exists(res_json))):
         return obj
@@ -111,7 +113,7 @@ def _compile(src: str, force: bool, hdr_time: float) -> str:
 def _resource_table() -> str:
     """Writes _build/kernel_resources.inc from the per-source resource records; returns its path."""
     lines = []
-    for src in KERNEL_SOURCES:
+    for src in RESOURCE_SOURCES:
         with open(os.path.join(OBJ_DIR, src + ".resources.json")) as f:
             for e in json.load(f):
                 targs = list(e["targs"]) + [0] * (8 - len(e["targs"]))

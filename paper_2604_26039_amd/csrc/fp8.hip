@@ -21,6 +21,8 @@
 //   scale bytes:    [E][gate, up, down][feature block of 128][k block, row stride padded to 4 bytes]
 //   quantised activations: codes row-major [rows, K], scale bytes [rows][K/128 padded to 4]
 // Which feature sits in row r of row block rb is the interleave of the bf16 layout (packed_row_feature).
+#include <initializer_list>
+
 #include "moe_fp8_pingpong.h"
 #include "moe_fp8_stream.h"
 
@@ -354,7 +356,9 @@ __global__ __launch_bounds__(WM *WN * 64) void moe_fp8_kernel(GemmArgs a, Fp8Arg
 
 struct Fp8Kernel {
     ramp_config cfg;
-    int lds_bytes, waves_per_cu_limit;
+    const char *family;        // kernel template and the arguments of the stage-1 instantiation: the key into the compiler's
+    int targs[8], n_targs;     // per-kernel resource table
+    const void *kernel_fn[2];  // the two projection kernels, for occupancy queries
     void (*launch)(int stage, const GemmArgs &, const Fp8Args &, hipStream_t);
     void (*launch_pp)(int stage, const GemmArgs &, const Fp8PingPongArgs &, hipStream_t);  // persistent family, else NULL
     void (*launch_stream)(int stage, const GemmArgs &, const Fp8StreamArgs &, hipStream_t);  // weight-streaming family
@@ -373,18 +377,22 @@ void launch_fp8(int stage, const GemmArgs &a, const Fp8Args &f, hipStream_t stre
         hipLaunchKernelGGL((moe_fp8_kernel<2, BM, BN, WM, WN, NSTAGE>), grid, block, 0, stream, g, f);
 }
 
+template <class Kernel>
+void set_kernel(Fp8Kernel &k, const char *family, std::initializer_list<int> targs, Kernel *stage1, Kernel *stage2)
+{
+    k.family = family;
+    for (int v : targs) k.targs[k.n_targs++] = v;
+    k.kernel_fn[0] = reinterpret_cast<const void *>(stage1);
+    k.kernel_fn[1] = reinterpret_cast<const void *>(stage2);
+}
+
 template <int BM, int BN, int WM, int WN, int NSTAGE>
 Fp8Kernel make_fp8()
 {
-    using TT = TileTraits<BM, BN, 64, WM, WN, NSTAGE>;
     Fp8Kernel k = {};
     k.cfg = ramp_config{BM, BN, kGroup, WM * WN, NSTAGE, (WM - 1) | kModeFp8};
-    k.lds_bytes = TT::LDS_BYTES;
-    // workgroups per compute unit: LDS, and one wavefront per SIMD for the large register tiles
-    const int by_lds = kLdsBytesPerCU / TT::LDS_BYTES;
-    const int by_regs = (TT::ACC_REGS > 128 ? 1 : 2) * 4 / (WM * WN);
-    k.waves_per_cu_limit = by_lds < by_regs ? by_lds : by_regs;
-    if (k.waves_per_cu_limit < 1) k.waves_per_cu_limit = 1;
+    set_kernel(k, "moe_fp8_kernel", {1, BM, BN, WM, WN, NSTAGE}, &moe_fp8_kernel<1, BM, BN, WM, WN, NSTAGE>,
+               &moe_fp8_kernel<2, BM, BN, WM, WN, NSTAGE>);
     k.launch = &launch_fp8<BM, BN, WM, WN, NSTAGE>;
     return k;
 }
@@ -395,8 +403,7 @@ Fp8Kernel make_fp8_pingpong()
     using PT = Fp8PingPongTraits<1, NH>;
     Fp8Kernel k = {};
     k.cfg = ramp_config{PT::BM, PT::BN, kGroup, 8, PT::NW, 1 | kModePingPong | kModeFp8};
-    k.lds_bytes = PT::LDS_BYTES;
-    k.waves_per_cu_limit = 1;
+    set_kernel(k, "moe_fp8_pingpong_kernel", {1, NH}, &moe_fp8_pingpong_kernel<1, NH>, &moe_fp8_pingpong_kernel<2, NH>);
     k.launch_pp = &launch_fp8_pingpong<NH>;
     return k;
 }
@@ -407,9 +414,8 @@ Fp8Kernel make_fp8_stream()
     using ST = Fp8StreamTraits<BM, FBW, WF, WK, U>;
     Fp8Kernel k = {};
     k.cfg = ramp_config{BM, ST::BN, kGroup, WF * WK, 2 * U, kModeStream | WK | kModeFp8 | (DECODE ? kModeDecode : 0)};
-    k.lds_bytes = ST::RED_FLOATS * 4;
-    // 16 wavefronts per compute unit while two register batches take up to 128 registers, 8 beyond that
-    k.waves_per_cu_limit = (FBW == 2 && ST::NB * U == 1 ? 16 : 8) / (WF * WK);
+    set_kernel(k, "moe_fp8_stream_kernel", {1, BM, FBW, WF, WK, U}, &moe_fp8_stream_kernel<1, BM, FBW, WF, WK, U>,
+               &moe_fp8_stream_kernel<2, BM, FBW, WF, WK, U>);
     k.launch_stream = &launch_fp8_stream<BM, FBW, WF, WK, U>;
     if constexpr (DECODE) k.launch_decode_up = &launch_fp8_decode_up<BM, FBW, WF, WK, U>;
     return k;
@@ -582,7 +588,22 @@ extern "C" int ramp_fp8_config_wave_capacity(const ramp_config *cfg)
         set_error("fp8_config_wave_capacity: configuration not in the FP8 family");
         return RAMP_EUNSUPPORTED;
     }
-    return kNumCU * k->waves_per_cu_limit;
+    const int occ = occupancy_estimate(k->cfg, k->family, k->targs, k->n_targs);
+    if (occ <= 0) {
+        set_error("fp8_config_wave_capacity: no compiler resource record for this kernel (rebuild with paper_2604_26039_amd.build)");
+        return RAMP_EUNSUPPORTED;
+    }
+    return kNumCU * occ;
+}
+
+extern "C" int ramp_fp8_config_runtime_occupancy(const ramp_config *cfg, int *wg_per_cu)
+{
+    const Fp8Kernel *k = cfg && wg_per_cu ? find_fp8(*cfg) : nullptr;
+    if (!k) {
+        set_error("fp8_config_runtime_occupancy: NULL argument or configuration not in the FP8 family");
+        return RAMP_EUNSUPPORTED;
+    }
+    return runtime_occupancy(k->kernel_fn, k->cfg.waves * kWave, wg_per_cu);
 }
 
 extern "C" size_t ramp_fp8_pack_bytes(const ramp_shape *shape)

@@ -243,21 +243,35 @@ bool config_in_pool(const KernelInfo &ki, const ramp_shape &s)
     return true;
 }
 
-int occupancy_estimate(const KernelInfo &ki)
+int occupancy_estimate(const ramp_config &cfg, const char *family, const int *targs, int n_targs)
 {
     // Workgroups of this configuration resident on one compute unit, from what the compiler reported for its
     // up-projection kernel when the library was built: wavefronts per SIMD allowed by the register allocation
     // (4 SIMDs per unit, at most 8 wavefronts each), and 160 KB of LDS.  The persistent kernels launch one
     // workgroup per unit whatever would fit.
-    if (ki.cfg.mode & kModePingPong) return 1;
-    const KernelResources *r = find_resources(ki.family, ki.targs, ki.n_targs);
+    if (cfg.mode & kModePingPong) return 1;
+    const KernelResources *r = find_resources(family, targs, n_targs);
     if (!r) return 0;  // no record for this kernel: the library was not built by its build script
     int waves_per_simd = r->waves_per_simd < 8 ? r->waves_per_simd : 8;
     if (waves_per_simd < 1) waves_per_simd = 1;
-    int by_regs = waves_per_simd * 4 / ki.cfg.waves;
+    int by_regs = waves_per_simd * 4 / cfg.waves;
     const int by_lds = r->lds_bytes > 0 ? kLdsBytesPerCU / r->lds_bytes : 64;
     int occ = by_lds < by_regs ? by_lds : by_regs;
     return occ < 1 ? 1 : occ;
+}
+
+int runtime_occupancy(const void *const kernel_fn[2], int block_threads, int *wg_per_cu)
+{
+    for (int st = 0; st < 2; ++st) {
+        int n = 0;
+        hipError_t err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel_fn[st], block_threads, 0);
+        if (err != hipSuccess) {
+            set_error("config_runtime_occupancy: %s", hipGetErrorString(err));
+            return RAMP_EHIP;
+        }
+        wg_per_cu[st] = n;
+    }
+    return RAMP_OK;
 }
 
 int launch_combine(const float *Y, int y_bf16, const int32_t *ids, int T, int k, int E, int H, uint16_t *out,
@@ -345,7 +359,7 @@ extern "C" int ramp_config_wave_capacity(const ramp_config *cfg)
         set_error("config_wave_capacity: configuration not instantiated");
         return RAMP_EUNSUPPORTED;
     }
-    const int occ = occupancy_estimate(*ki);
+    const int occ = occupancy_estimate(ki->cfg, ki->family, ki->targs, ki->n_targs);
     if (occ <= 0) {
         set_error("config_wave_capacity: no compiler resource record for this kernel (rebuild with paper_2604_26039_amd.build)");
         return RAMP_EUNSUPPORTED;
@@ -364,16 +378,7 @@ extern "C" int ramp_config_runtime_occupancy(const ramp_config *cfg, int *wg_per
         set_error("config_runtime_occupancy: configuration not instantiated");
         return RAMP_EUNSUPPORTED;
     }
-    for (int st = 0; st < 2; ++st) {
-        int n = 0;
-        hipError_t err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, ki->kernel_fn[st], ki->block_threads, 0);
-        if (err != hipSuccess) {
-            set_error("config_runtime_occupancy: %s", hipGetErrorString(err));
-            return RAMP_EHIP;
-        }
-        wg_per_cu[st] = n;
-    }
-    return RAMP_OK;
+    return runtime_occupancy(ki->kernel_fn, ki->block_threads, wg_per_cu);
 }
 
 extern "C" size_t ramp_fused_moe_workspace_bytes(const ramp_shape *shape, const ramp_config *cfg)

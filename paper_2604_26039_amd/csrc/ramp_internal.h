@@ -208,7 +208,8 @@ const KernelInfo &kernel_info(int i);
 const KernelInfo *find_kernel(const ramp_config &cfg);
 bool config_valid_for_shape(const KernelInfo &ki, const ramp_shape &s);
 bool config_in_pool(const KernelInfo &ki, const ramp_shape &s);
-int occupancy_estimate(const KernelInfo &ki);
+int occupancy_estimate(const ramp_config &cfg, const char *family, const int *targs, int n_targs);
+int runtime_occupancy(const void *const kernel_fn[2], int block_threads, int *wg_per_cu);
 
 // sel != NULL: the launch leaves `out` untouched unless 0 <= *sel < n_cand (device-selected layer) and bit *sel of
 // skip_mask is clear (a candidate whose own launches write `out`).

@@ -116,6 +116,8 @@ def lib() -> ctypes.CDLL:
         L.ramp_fp8_get_config.argtypes = [sp, ci, cp]
         L.ramp_fp8_config_wave_capacity.restype = ci
         L.ramp_fp8_config_wave_capacity.argtypes = [cp]
+        L.ramp_fp8_config_runtime_occupancy.restype = ci
+        L.ramp_fp8_config_runtime_occupancy.argtypes = [cp, ctypes.POINTER(ci)]
         L.ramp_fp8_pack_bytes.restype = sz
         L.ramp_fp8_pack_bytes.argtypes = [sp]
         L.ramp_fp8_pack_weights.restype = ci
@@ -175,7 +177,7 @@ EXPORTS = [
     "ramp_align_capacity", "ramp_align_workspace_bytes", "ramp_moe_histogram", "ramp_moe_align", "ramp_pack_bytes",
     "ramp_pack_weights", "ramp_fused_moe_workspace_bytes", "ramp_fused_moe_workspace_layout", "ramp_fused_moe", "ramp_fused_moe_static",
     "ramp_fused_moe_selected_workspace_bytes", "ramp_fused_moe_selected",
-    "ramp_fp8_num_configs", "ramp_fp8_get_config", "ramp_fp8_config_wave_capacity", "ramp_fp8_pack_bytes", "ramp_fp8_pack_weights",
+    "ramp_fp8_num_configs", "ramp_fp8_get_config", "ramp_fp8_config_wave_capacity", "ramp_fp8_config_runtime_occupancy", "ramp_fp8_pack_bytes", "ramp_fp8_pack_weights",
     "ramp_fp8_pack_layout", "ramp_fp8_quantize_rows", "ramp_fused_moe_fp8_workspace_bytes", "ramp_fused_moe_fp8",
     "ramp_cost_model_fit", "ramp_cost_model_select", "ramp_cost_model_fit5", "ramp_cost_model_select5",
     "ramp_cost_model_fit_rounds", "ramp_cost_model_select_rounds", "ramp_config_rounds", "ramp_grid", "ramp_region_classify", "ramp_select_table_bytes", "ramp_select_table_build",
@@ -343,6 +345,13 @@ def fp8_config_wave_capacity(cfg: Config) -> int:
     if n < 0:
         _check(n)
     return n
+
+
+def fp8_config_runtime_occupancy(cfg: Config):
+    """(up-projection, down-projection) workgroups per compute unit according to the HIP runtime (needs a GPU)."""
+    out = (ctypes.c_int * 2)()
+    _check(lib().ramp_fp8_config_runtime_occupancy(ctypes.byref(cfg), out))
+    return int(out[0]), int(out[1])
 
 
 def fp8_pack_bytes(shape: Shape) -> int:

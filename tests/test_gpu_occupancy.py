@@ -23,3 +23,16 @@ def test_wave_capacity_agrees_with_the_runtime_occupancy():
             assert static == 1, key          # persistent kernels launch one workgroup per compute unit
         else:
             assert static == up, f"{key}: static {static}, runtime {up} (up-projection) / {down} (down-projection)"
+
+
+def test_fp8_wave_capacity_agrees_with_the_runtime_occupancy():
+    torch.zeros(1, device="cuda:0")
+    seen = {}
+    for s in synth.SHAPES.values():
+        for c in ramp.fp8_configs(ramp.Shape(1, s.k, s.E, s.H, s.I)):
+            seen.setdefault(c.key(), c)
+    assert len(seen) >= 14
+    for key, c in seen.items():
+        static = ramp.fp8_config_wave_capacity(c) // 256
+        up, down = ramp.fp8_config_runtime_occupancy(c)
+        assert static == (1 if c.mode & 0x400 else up), f"{key}: static {static}, runtime {up} / {down}"

@@ -1,6 +1,7 @@
 """Host-side checks of libramp.so that need no GPU: the library loads, exports every symbol the
 header declares, enumerates a sane configuration family, and its cost-model fit/select agree
 with the oracle (predictions and argmin; the raw b/c split is not identifiable)."""
+import json
 import os
 import re
 
@@ -8,7 +9,7 @@ import numpy as np
 import pytest
 
 from oracle import oracle
-from paper_2604_26039_amd import ramp, synth
+from paper_2604_26039_amd import build as lib_build, ramp, synth
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -66,6 +67,25 @@ def test_fp8_config_family(name):
     assert off[0] == 2 * sh.I * sh.H and off[1] == sh.I * sh.H and strides[0] % 4 == 0 and strides[0] >= sh.H // 128
     with pytest.raises(ramp.RampError):
         ramp.fp8_config_wave_capacity(ramp.configs(sh)[0])
+
+
+def test_fp8_wave_capacity_follows_from_the_registers_and_lds_of_the_kernels():
+    """W(c) / 256 by hand: 512 registers per SIMD lane (VGPRs and AGPRs, blocks of 8), 4 SIMDs, 160 KB of LDS; persistent: 1."""
+    with open(os.path.join(lib_build.OBJ_DIR, "fp8.hip.resources.json")) as f:
+        records = {(r["family"], tuple(r["targs"])): r for r in json.load(f)}
+    for c in ramp.fp8_configs(ramp.Shape(1, 1, 64, 2048, 1024)):
+        if c.mode & 0x400:
+            assert ramp.fp8_config_wave_capacity(c) == 256
+            continue
+        if c.mode & 0x100:                                  # streaming: mode low byte = WK, stages = 2 * U
+            wk, wf = c.mode & 0xff, c.waves // (c.mode & 0xff)
+            r = records["moe_fp8_stream_kernel", (1, c.bm, c.bn // 16 // wf, wf, wk, c.stages // 2)]
+        else:
+            wm = (c.mode & 0xff) + 1
+            r = records["moe_fp8_kernel", (1, c.bm, c.bn, wm, c.waves // wm, c.stages)]
+        registers = -(-(-(-r["vgprs"] // 4) * 4 + r["agprs"]) // 8) * 8
+        by_regs, by_lds = min(8, 512 // registers) * 4 // c.waves, 160 * 1024 // r["lds"]
+        assert ramp.fp8_config_wave_capacity(c) == 256 * max(1, min(by_regs, by_lds)), (c, r)
 
 
 def test_unknown_config_is_rejected():
