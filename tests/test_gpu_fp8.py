@@ -69,6 +69,67 @@ def test_activation_quantiser_edges():
         assert (got[:shift] == 99).all() and (got[shift + rows * K:] == 99).all()
 
 
+def quantise_bits(bits: np.ndarray):
+    """bf16 bit patterns [rows, K] -> codes and scale bytes of the quantising entry point."""
+    rows, K = bits.shape
+    X = torch.from_numpy(bits.view(np.int16).copy()).view(torch.bfloat16).to(DEV)
+    codes = torch.zeros((rows, K), dtype=torch.uint8, device=DEV)
+    scales = torch.zeros((rows, (K // 128 + 3) // 4 * 4), dtype=torch.uint8, device=DEV)
+    ramp.fp8_quantize_rows(X, codes, scales)
+    return codes.cpu().numpy(), scales.cpu().numpy()[:, :K // 128]
+
+
+# largest magnitude of a group, as bf16 bits: the smallest and largest subnormal and the smallest normal value, both sides of
+# the last mantissa of scale bytes 0, 1, 2, 126, 127, 128, and the largest values
+GROUP_MAXIMA = [0x0001, 0x007F, 0x0080, 0x03E1, 0x0460, 0x0461, 0x04E0, 0x04E1, 0x1F55, 0x4360, 0x4361, 0x43E0, 0x43E1, 0x4460,
+                0x5AAA, 0x7F60, 0x7F61, 0x7F7F]
+
+
+def test_activation_quantiser_every_finite_bf16_value():
+    """Every bf16 bit pattern up to each group maximum, both signs, in groups that hold the maximum."""
+    seen = set()
+    for top in GROUP_MAXIMA:
+        mag = np.arange(top + 1, dtype=np.uint16)
+        pats = np.concatenate([mag, mag | 0x8000])
+        groups = -(-len(pats) // 127)
+        bits = np.full((groups, 128), top, np.uint16)
+        body = np.full(groups * 127, top, np.uint16)
+        body[:len(pats)] = pats
+        bits[:, 1:] = body.reshape(groups, 127)
+        codes, scales = quantise_bits(bits)
+        want_c, want_s = ofp8.quantize_rows(synth.bits_to_f64(bits))
+        assert np.array_equal(scales, want_s), hex(top)
+        assert np.array_equal(codes, want_c), hex(top)
+        seen.update(scales.reshape(-1).tolist())
+    assert {0, 1, 2, 126, 127, 128, 246, 247} <= seen
+
+
+def test_activation_quantiser_infinities_and_nan():
+    """A NaN counts as no magnitude and becomes +-448; a group with an infinity, or of NaN only, has scale 1."""
+    rng = np.random.default_rng(3)
+    bits = rng.integers(0x2000, 0x5F00, (512, 256)).astype(np.uint16) | (rng.integers(0, 2, (512, 256)).astype(np.uint16) << 15)
+    special = np.array([0x7F80, 0xFF80, 0x7F81, 0x7FC0, 0x7FFF, 0xFFC1, 0xFFFF], np.uint16)
+    nan_only = special[2:]
+    for r in range(512):
+        some = special if r % 2 else nan_only
+        n = 1 + r % 5
+        bits[r, rng.choice(256, n, replace=False)] = rng.choice(some, n)
+    bits[7, :128] = rng.choice(nan_only, 128)
+    bits[8] = 0xFF80
+    bits[9, :128] = 0
+    bits[9, 3] = 0x7FC0
+    nan = (bits & 0x7FFF) > 0x7F80
+    with np.errstate(invalid="ignore"):
+        v = synth.bits_to_f64(bits)
+    G = np.where(nan, 0.0, np.abs(v)).reshape(512, 2, 128).max(2)
+    want_s = np.where(np.isinf(G), 127, ofp8.e8m0_bytes(np.where(np.isinf(G), 1.0, G))).astype(np.uint8)
+    value = np.where(nan, np.where(bits & 0x8000, -np.inf, np.inf), v)
+    want_c = ofp8.e4m3_encode(value / np.repeat(ofp8.e8m0_scale(want_s), 128, axis=1))
+    codes, scales = quantise_bits(bits)
+    assert np.array_equal(scales, want_s)
+    assert np.array_equal(codes, want_c)
+
+
 def row_feature(rb, r):
     """Feature held by row r of packed row block rb (interleave inside groups of four row blocks)."""
     return (rb // 4) * 64 + (r >> 2) * 16 + (rb % 4) * 4 + (r & 3)

@@ -41,6 +41,35 @@ def test_tile_edges(H, I, k):
         assert torch.equal(got.view(torch.int16), want.view(torch.int16)), f"H={H} I={I} {cfg}"
 
 
+def test_infinities_and_nan_in_the_quantised_activation():
+    """Rows of every magnitude up to the largest bf16: products past it, infinities that cancel to NaN, and NaN and infinities in
+    the hidden state.  The quantiser of the up-projection's epilogue has to agree with the quantising pass."""
+    s = synth.Shape("pp", 512, 384, 3, 1)
+    T = 3 * 140
+    L = Fp8Layer(s, T, seed=8)
+    scale = torch.exp2(torch.linspace(-60, 125, T // 3, device=DEV)).repeat_interleave(3)[:, None]
+    L.X[:] = (L.X.float() * scale).bfloat16()
+    L.X[3, 5] = float("nan")
+    L.X[4, 128:256] = float("nan")
+    L.X[5, 300] = float("inf")
+    L.X[6, 511] = float("-inf")
+    for W, f in ((L.Wg, 32.0), (L.Wu, 32.0), (L.Wd, 2.0 ** -12)):
+        W *= f                                                       # activations overflow, outputs do not
+    ramp.fp8_pack_weights(L.rs, L.Wg, L.Wu, L.Wd, L.packed)
+    g, u = (L.X[9::3].cpu().float() @ W[0].cpu().float() for W in (L.Wg, L.Wu))   # expert 0's tokens, without the quantisation
+    act = (torch.nn.functional.silu(g) * u).bfloat16()
+    assert torch.isnan(act[-8:]).any() and torch.isinf(act).any() and torch.isfinite(act[:40]).all()
+    ids = (np.arange(T, dtype=np.int32) % s.E).reshape(T, 1)
+    w = np.ones((T, 1), np.float32)
+    cfgs = ramp.fp8_configs(L.rs)
+    want = L.run(next(c for c in cfgs if c.bm == 64), ids, w).clone()
+    assert torch.isfinite(want.float()).all()
+    for cfg in [c for c in cfgs if c.mode & 0x400]:
+        print(f"case {cfg}", flush=True)
+        got = L.run(cfg, ids, w)
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16)), f"{cfg}"
+
+
 @pytest.mark.parametrize("T,beta", [(1, 1.0), (300, 1.0), (2050, 0.3)])
 def test_many_tiles_per_workgroup_and_bf16_pair_rows(T, beta):
     """One token; tiles fewer than workgroups; several tiles per workgroup with bf16 pair rows (T*k*H >= 8 Mi)."""
