@@ -99,11 +99,11 @@ __global__ __launch_bounds__(256) void quant_pack_kernel(QuantPackArgs a)
         const size_t e = bl / nf / nk;
         const uint16_t *s = p.src + (e * p.K + (size_t)(kb * kGroup + g * 8)) * p.F + (size_t)fb * kGroup + c * 8;
         union {
-            uint4 v;
+            UnalignedWords4 w;
             uint16_t h[8];
         } in[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) in[i].v = *reinterpret_cast<const uint4 *>(s + (size_t)i * p.F);
+        for (int i = 0; i < 8; ++i) in[i].w = *reinterpret_cast<const UnalignedWords4 *>(s + (size_t)i * p.F);
         float amax = 0.f;
 #pragma unroll
         for (int i = 0; i < 8; ++i)

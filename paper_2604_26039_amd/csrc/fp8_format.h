@@ -120,7 +120,6 @@ __device__ __forceinline__ uint32_t quantise_group(const uint32_t *w, uint32_t *
 // 8-byte store each, and the maximum is four lane exchanges.  The vector types carry the alignment of one value: the
 // quantising entry point takes any address.
 // first, step: group of the workgroup's first 16 lanes, and groups of the whole launch.
-typedef uint32_t UnalignedWords4 __attribute__((ext_vector_type(4), aligned(2)));
 typedef uint32_t UnalignedWords2 __attribute__((ext_vector_type(2), aligned(1)));
 __device__ __forceinline__ void quantise_rows(const QuantRows &q, size_t first, size_t step)
 {

@@ -74,11 +74,12 @@ __global__ __launch_bounds__(256) void pack_kernel(PackArgs a)
         const size_t e = bl / nf / nk;
         const uint16_t *s = p.src + (e * p.K + (size_t)(kb * kPackBlock + g * 8)) * p.F + (size_t)fb * kPackBlock + c * 8;
         union {
+            UnalignedWords4 w;
             uint4 v;
             uint16_t h[8];
         } in[8], o;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) in[i].v = *reinterpret_cast<const uint4 *>(s + (size_t)i * p.F);
+        for (int i = 0; i < 8; ++i) in[i].w = *reinterpret_cast<const UnalignedWords4 *>(s + (size_t)i * p.F);
         const int ks = g >> 2, q = g & 3;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {

@@ -74,6 +74,8 @@ int launch_align_quant(const int32_t *ids, int T, int k, int E, int bm, int32_t 
                        int32_t *counts, int32_t *meta, AlignSlotWeights slot_weights, const QuantRows &q, hipStream_t stream);
 
 // ---- packed weights ----
+// 16 bytes of bf16 values at the alignment of one value: the caller's weights and rows to quantise may start anywhere
+typedef uint32_t UnalignedWords4 __attribute__((ext_vector_type(4), aligned(2)));
 // One fragment = 16 weight rows x 32 k-values = 512 bf16 = 1 KB, stored in the lane order
 // of the A operand of v_mfma_f32_16x16x32_bf16: element (row r, k = 8*q + j) at (q*16 + r)*8 + j.
 constexpr int kFragElems = 512;

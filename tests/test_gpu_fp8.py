@@ -149,10 +149,15 @@ def unpack_codes(buf: np.ndarray, F: int, K: int) -> np.ndarray:
     return out
 
 
-def test_weight_quantiser_and_packed_layout_bit_exact():
+@pytest.mark.parametrize("shift", [0, 1, 3])
+def test_weight_quantiser_and_packed_layout_bit_exact(shift):
+    """shift: elements by which the sources miss a 16-byte boundary."""
     s = synth.Shape("fp8pack", 256, 384, 3, 2)
     _, Wg, Wu, Wd = synth.layer_tensors(s, 1, seed=5, device=DEV)
     Wg[1, :128, 128:256] *= 32.0                          # block scales must differ
+    if shift:
+        Wg, Wu, Wd = (torch.cat([W.new_zeros(shift), W.flatten()])[shift:].view(W.shape) for W in (Wg, Wu, Wd))
+        assert Wg.data_ptr() % 16 and Wg.is_contiguous()
     rs = ramp.Shape(1, s.k, s.E, s.H, s.I)
     packed = torch.zeros(ramp.fp8_pack_bytes(rs), dtype=torch.uint8, device=DEV)
     ramp.fp8_pack_weights(rs, Wg, Wu, Wd, packed)
