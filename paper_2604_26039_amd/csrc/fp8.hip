@@ -522,12 +522,12 @@ Fp8Workspace fp8_workspace(const ramp_shape &s, const ramp_config &c)
     w.align_ws = take(w.align_ws_bytes);
     w.xs_stride = pp ? (int)align_up(s.H / kGroup, 16) : scale_stride(s.H);
     w.as_stride = pp ? (int)align_up(s.I / kGroup, 16) : scale_stride(s.I);
-    // the weight-streaming kernels quantise in registers: no codes in memory; their two-launch form indexes A by pair
+    // the weight-streaming kernels quantise in registers: no codes in memory; their two-launch form has a row of A per pair, of
+    // which there are never more than slots
     const bool stream = (c.mode & kModeStream) != 0;
-    const size_t rows = (stream && (size_t)s.T * s.k > w.cap) ? (size_t)s.T * s.k : w.cap;
     w.xq = stream ? off : take((size_t)s.T * s.H);
     w.xs = stream ? off : take((size_t)s.T * w.xs_stride);
-    w.a_buf = pp ? off : take(rows * (size_t)s.I * 2);  // the persistent up-projection writes the codes itself
+    w.a_buf = pp ? off : take(w.cap * (size_t)s.I * 2);  // the persistent up-projection writes the codes itself
     w.aq = stream ? off : take(w.cap * (size_t)s.I);
     w.as = stream ? off : take(w.cap * (size_t)w.as_stride);
     w.y_buf = take((size_t)s.T * s.k * s.H * 4);
@@ -765,7 +765,7 @@ extern "C" int ramp_fused_moe_fp8(const ramp_shape *shape, const ramp_config *cf
         g.F = s.I;
         g.n_tiles = 2 * s.I / cfg->bn;
         if (k->launch_decode_up && g.P <= kDecodeMaxPairs && 16 % s.k == 0) {
-            const DecodeArgs da = {topk_ids, s.E, cfg->bm, (int)w.cap, sorted, tile_expert, tile_rows, counts, meta};
+            const DecodeArgs da = {topk_ids, s.E, (int)w.cap, sorted, tile_expert, tile_rows, counts, meta};
             k->launch_decode_up(g, up, da, st);
             if (int rc = check_launch("moe_fp8_decode_up_kernel")) return rc;
             DecodeDownArgs dd = {};

@@ -22,26 +22,8 @@ __device__ __forceinline__ uint32_t e8m0_of_amax(float amax)
 // 2^(127-b): the factor that brings a block into the E4M3 range.
 __device__ __forceinline__ float inv_scale_of(uint32_t b) { return __builtin_bit_cast(float, (254u - b) << 23); }
 
-// fp32 -> E4M3 code: round to nearest, ties to even, saturate at 448.
-__device__ __forceinline__ uint32_t e4m3_of_f32(float v)
-{
-    const uint32_t u = __builtin_bit_cast(uint32_t, v);
-    const uint32_t sign = (u >> 24) & 0x80u;
-    uint32_t a = u & 0x7fffffffu;
-    if (a > 0x43e00000u) a = 0x43e00000u;  // 448
-    if (a >= 0x3c800000u) {                // >= 2^-6: normal code; keep 3 mantissa bits
-        const uint32_t r = a + 0x7ffffu + ((a >> 20) & 1u);
-        uint32_t code = (r >> 20) - (120u << 3);
-        if (code > 0x7eu) code = 0x7eu;
-        return sign | code;
-    }
-    // subnormal range: multiples of 2^-9 (8 of them reach the smallest normal value, code 8)
-    const float f = __builtin_bit_cast(float, a) * 512.0f;
-    return sign | (uint32_t)__builtin_rintf(f);
-}
-
-// Four of them, in one 32-bit word, by the conversion instruction of the chip (v_cvt_pk_fp8_f32): the same rounding, ties
-// included; it turns values past 448 into NaN, so they are saturated first.
+// Four fp32 -> E4M3 codes in one 32-bit word: round to nearest, ties to even, saturate at 448 (NaN too).  v_cvt_pk_fp8_f32
+// rounds that way, but turns values past 448 into NaN, so they are saturated first.
 __device__ __forceinline__ uint32_t e4m3x4_of_f32(const float *v)
 {
     float s[4];
@@ -70,9 +52,10 @@ __device__ __forceinline__ ushortx2 max_bf16_bits(ushortx2 m, uint32_t two)
 }
 
 // Quantises the 2 * NW values of this lane; its group of 128 lies in the lanes that differ in the bits D0 ... DEND/2 of the lane
-// index.  Codes in order, one scale byte, the same bits as e8m0_of_amax and e4m3_of_f32 give.  v_cvt_scalef32_pk_fp8_bf16 divides two bf16 by a power of two
-// and converts them; for finite groups nothing exceeds 448 after that and its results are e4m3_of_f32's (compared for every
-// bf16 value and scale bytes over the whole range), at a third of the instructions of unpacking, scaling and saturating.
+// index.  Codes in order, one scale byte, the same bits as e8m0_of_amax and e4m3x4_of_f32 give.  v_cvt_scalef32_pk_fp8_bf16
+// divides two bf16 by a power of two and converts them; for finite groups nothing exceeds 448 after that and the codes are the
+// same (tests/test_gpu_fp8.py: every bf16 value, scale bytes of the whole range), at a third of the instructions of unpacking,
+// scaling and saturating.
 // A group with an infinity or NaN takes the general conversion: NaN counts as no magnitude and converts to +-448.
 template <int NW, int D0, int DEND>
 __device__ __forceinline__ uint32_t quantise_group(const uint32_t *w, uint32_t *codes)

@@ -218,7 +218,7 @@ int runtime_occupancy(const void *const kernel_fn[2], int block_threads, int *wg
 // Two-launch form for decode-sized calls (moe_decode.h, instantiated in stream_group2.hip)
 struct DecodeArgs {
     const int32_t *ids;      // [T*k]
-    int E, bm, cap;
+    int E, cap;
     int32_t *sorted, *tile_expert, *tile_rows, *counts, *meta;  // align result, written by workgroup 0
 };
 struct DecodeDownArgs {
