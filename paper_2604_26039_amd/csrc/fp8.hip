@@ -765,7 +765,7 @@ extern "C" int ramp_fused_moe_fp8(const ramp_shape *shape, const ramp_config *cf
         g.F = s.I;
         g.n_tiles = 2 * s.I / cfg->bn;
         if (k->launch_decode_up && g.P <= kDecodeMaxPairs && 16 % s.k == 0) {
-            const DecodeArgs da = {topk_ids, s.E, (int)w.cap, sorted, tile_expert, tile_rows, counts, meta};
+            const DecodeArgs da = {topk_ids, s.E, cfg->bm, (int)w.cap, sorted, tile_expert, tile_rows, counts, meta};
             k->launch_decode_up(g, up, da, st);
             if (int rc = check_launch("moe_fp8_decode_up_kernel")) return rc;
             DecodeDownArgs dd = {};

@@ -492,7 +492,7 @@ int enqueue_projections(const ramp_shape &s, const ramp_config &cfg, const Kerne
         g.m_tiles_cap = (int)(w.cap / (size_t)cfg.bm);
         g.pred = pred;
         g.pred_value = pred_value;
-        DecodeArgs da = {topk_ids, s.E, (int)w.cap, sorted, tile_expert, tile_rows, counts, meta};
+        DecodeArgs da = {topk_ids, s.E, cfg.bm, (int)w.cap, sorted, tile_expert, tile_rows, counts, meta};
         {
             ProbeScope probe(2, st);
             ki.launch_decode_up(g, da, st);
