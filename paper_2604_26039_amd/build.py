@@ -37,7 +37,7 @@ COMMON = ["-O3", "-fPIC", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I
 HIP_FLAGS = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
              "-Wno-unused-command-line-argument"]
 FAMILIES = ("moe_gemm_kernel", "moe_pingpong_kernel", "moe_stream_kernel", "moe_fp8_kernel", "moe_fp8_pingpong_kernel",
-            "moe_fp8_stream_kernel")
+            "moe_fp8_stream_kernel", "moe_fp8_decode_up_kernel", "moe_fp8_decode_down_kernel")
 
 
 def _hipcc() -> str:
@@ -56,7 +56,7 @@ def _newest_header() -> float:
 
 
 def _parse_resources(stderr: str) -> list:
-    """[{family, targs, vgprs, agprs, lds, waves_per_simd}] from hipcc's kernel-resource-usage remarks."""
+    """[{family, targs, vgprs, agprs, scratch, lds, waves_per_simd}] from hipcc's kernel-resource-usage remarks."""
     out, cur = [], None
     for line in stderr.splitlines():
         m = re.search(r"remark:\s+Function Name: (\S+)", line)
@@ -74,7 +74,7 @@ def _parse_resources(stderr: str) -> list:
         if cur is None:
             continue
         for key, pat in (("vgprs", r"remark:\s+VGPRs: (\d+)"), ("agprs", r"remark:\s+AGPRs: (\d+)"),
-                         ("waves_per_simd", r"remark:\s+Occupancy \[waves/SIMD\]: (\d+)"),
+                         ("scratch", r"remark:\s+ScratchSize \[bytes/lane\]: (\d+)"), ("waves_per_simd", r"remark:\s+Occupancy \[waves/SIMD\]: (\d+)"),
                          ("lds", r"remark:\s+LDS Size \[bytes/block\]: (\d+)")):
             m = re.search(pat, line)
             if m:
@@ -103,7 +103,7 @@ def _compile(src: str, force: bool, hdr_time: float) -> str:
         raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{res.stdout}\n{res.stderr}")
     if is_kernel:
         entries = _parse_resources(res.stderr)
-        if not entries or any(len({"vgprs", "agprs", "lds", "waves_per_simd"} - set(e)) for e in entries):
+        if not entries or any(len({"vgprs", "agprs", "scratch", "lds", "waves_per_simd"} - set(e)) for e in entries):
             raise RuntimeError(f"{src}: could not read the compiler's kernel resource usage")
         with open(res_json, "w") as f:
             json.dump(entries, f)

@@ -88,6 +88,13 @@ def test_fp8_wave_capacity_follows_from_the_registers_and_lds_of_the_kernels():
         assert ramp.fp8_config_wave_capacity(c) == 256 * max(1, min(by_regs, by_lds)), (c, r)
 
 
+def test_fp8_kernels_keep_their_operands_in_registers():
+    with open(os.path.join(lib_build.OBJ_DIR, "fp8.hip.resources.json")) as f:
+        records = json.load(f)
+    assert {r["family"] for r in records} == {n for n in lib_build.FAMILIES if "fp8" in n}
+    assert not [r for r in records if r["scratch"]]
+
+
 def test_unknown_config_is_rejected():
     bad = ramp.Config(24, 64, 128, 2, 2, 0)  # bm=24 is not in the family
     with pytest.raises(ramp.RampError) as ei:
