@@ -16,9 +16,9 @@ ALL_FLAGS = ramp.CM_RELATIVE | ramp.CM_DISTINCT_TILES | ramp.CM_WAVE_FLOOR | ram
 NO_ROUNDS = ALL_FLAGS & ~ramp.CM_ROUNDS
 
 
-def family(name, T):
+def family(name, T, fp8=False):
     s = synth.SHAPES[name]
-    fam = tuner.Family.of(s, T)
+    fam = tuner.Family.of(s, T, fp8=fp8)
     return s, fam
 
 
@@ -102,6 +102,25 @@ def test_select_device_matches_oracle(name, T, beta, flags):
     b_h, p_h = ramp.cost_model_select(s.E, fam.cfgs, fam.ntiles, fam.wave_cap, theta, ref_counts, want_pred=True, flags=flags,
                                       rounds=fam.rounds if flags & ramp.CM_ROUNDS else None)
     assert b_h == b_o and np.array_equal(p_h, p_o)
+
+
+@pytest.mark.parametrize("name,T,beta", [("olmoe", 1, 1.0), ("qwen3", 512, 0.3), ("mixtral", 8192, 1.0), ("dsv3", 64, 1.0)])
+def test_fp8_dispatcher_matches_oracle(name, T, beta):
+    """Selection over the FP8 family: streaming tiles with their wave capacity, hand-out rounds of the persistent ones."""
+    s, fam = family(name, T, fp8=True)
+    assert any(c.mode & 0x400 for c in fam.cfgs) and all(c.mode & ramp.FP8_MODE for c in fam.cfgs)
+    disp = {seed: tuner.Dispatcher(fam, synthetic_theta(fam, seed), ALL_FLAGS, T, device=DEV) for seed in range(6)}
+    chosen = set()
+    for seed, d in disp.items():
+        ids, _ = synth.routing(T, s, beta, seed=seed)
+        counts = oracle_histogram(ids, s.k, s.E)
+        want, pred = oracle_select(fam, synthetic_theta(fam, seed), counts, ALL_FLAGS)
+        assert d.select(torch.from_numpy(ids.reshape(-1).astype(np.int32)).to(DEV)) == want
+        assert np.array_equal(d.last_counts(), counts)
+        _, pred_d, _ = device_select(ids, T, s, fam, synthetic_theta(fam, seed), ALL_FLAGS)
+        assert np.array_equal(pred_d, pred)
+        chosen.add(want)
+    assert len(chosen) > 1
 
 
 def test_select_device_empty_and_dropped_ids():

@@ -335,6 +335,11 @@ def test_config_rounds_and_the_rounds_model_against_the_oracle():
     assert list(ramp.config_rounds(q, ramp.Config(256, 256, 32, 8, 4, 1025))) == [40, 6, 32, 8]      # 32/6 = 5, 32/8 = 4
     o = shape_of("olmoe", 4096)
     assert list(ramp.config_rounds(o, ramp.Config(128, 256, 32, 8, 4, 1025))) == [32, 8, 32, 8]
+    # FP8: the persistent tiles as the bf16 ones, one M-tile for the others
+    for c in ramp.fp8_configs(sh):
+        up, down = 2 * sh.I // c.bn, sh.H // c.bn
+        assert list(ramp.config_rounds(sh, c)) == ([16, 16, 8, 28] if c.mode & 0x400 else [1, up, 1, down]), c
+    assert list(ramp.config_rounds(q, next(c for c in ramp.fp8_configs(q) if c.mode & 0x400))) == [40, 6, 32, 8]
     with pytest.raises(ramp.RampError):
         ramp.config_rounds(sh, ramp.Config(256, 0, 32, 8, 4, 1025))
     for name, T, beta in (("qwen3", 2048, 0.3), ("dsv3", 8192, 1.0), ("olmoe", 64, 0.2)):
