@@ -72,3 +72,32 @@ def test_fp8_pack_codes_every_bf16_value_up_to_the_largest_code():
         rb, ks, h, lane, j = np.ogrid[:F // 16, :K // 128, :2, :64, :16]
         want = want_c[ks * 128 + (lane // 16) * 32 + h * 16 + j, row_feature(rb, lane % 16)]
         assert np.array_equal(raw[off: off + K * F].reshape(want.shape), want)
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+def test_more_blocks_than_workgroups(fp8):
+    """A layer of more than 2^20 blocks of 128 x 128 weights: workgroups take a second one.  Experts repeat three different ones, so
+    the image has to repeat theirs."""
+    H = I = 2048
+    E = (1 << 20) // (3 * (H // 128) * (I // 128)) + 9
+    assert 3 * E * (H // 128) * (I // 128) > 1 << 20
+    gen = torch.Generator(device=DEV).manual_seed(1)
+    base = (torch.randn((3, H, I), generator=gen, device=DEV) * torch.tensor([1.0, 0.1, 3.0], device=DEV)[:, None, None]).bfloat16()
+    W = base.repeat(E // 3 + 1, 1, 1)[:E]
+    pack, size = (ramp.fp8_pack_weights, ramp.fp8_pack_bytes) if fp8 else (ramp.pack_weights, ramp.pack_bytes)
+    small, large = ramp.Shape(1, 1, 3, H, I), ramp.Shape(1, 1, E, H, I)
+    want = torch.zeros(size(small), dtype=torch.uint8, device=DEV)
+    pack(small, base, base, base, want)
+    got = torch.zeros(size(large), dtype=torch.uint8, device=DEV)
+    pack(large, W, W, W, got)
+    one = 2 * H * I * (1 if fp8 else 2)                            # gate and up of an expert; half as much of down
+    sections = [(0, 0, one), (3 * one, E * one, one // 2)]         # offset in the small and the large image, bytes of an expert
+    if fp8:
+        (_, _, _, _, sc3, sce), _ = ramp.fp8_pack_layout(small)
+        (_, _, _, _, scE, _), _ = ramp.fp8_pack_layout(large)
+        sections.append((sc3, scE, sce))
+    for o3, oE, n in sections:
+        w = want[o3:o3 + 3 * n].view(3, n)
+        g = got[oE:oE + E * n].view(E, n)
+        for e in range(E):
+            assert torch.equal(g[e], w[e % 3]), (e, n)
