@@ -476,14 +476,6 @@ bool fp8_valid_for_shape(const Fp8Kernel &k, const ramp_shape &s)
     return true;
 }
 
-// Pool membership, as config_in_pool: the weight-streaming tiles are enumerated up to 32 pairs per expert of the layer.  Past
-// that every tile of theirs reads weights that another one has read too, with any routing (Mixtral-shaped, 32 pairs per expert:
-// 397 us, 317 us with the 128-row tile; at 16 pairs 294 against 315), and profiling them would only cost time.
-bool fp8_in_pool(const Fp8Kernel &k, const ramp_shape &s)
-{
-    return fp8_valid_for_shape(k, s) && (!k.launch_stream || (size_t)s.T * s.k <= (size_t)s.E * 32);
-}
-
 const Fp8Kernel *find_fp8(const ramp_config &c)
 {
     int n = 0;
@@ -558,7 +550,7 @@ extern "C" int ramp_fp8_num_configs(const ramp_shape *shape)
     }
     int n = 0, cnt = 0;
     const Fp8Kernel *t = fp8_kernels(&n);
-    for (int i = 0; i < n; ++i) cnt += fp8_in_pool(t[i], *shape) ? 1 : 0;
+    for (int i = 0; i < n; ++i) cnt += fp8_valid_for_shape(t[i], *shape) ? 1 : 0;
     return cnt;
 }
 
@@ -571,7 +563,7 @@ extern "C" int ramp_fp8_get_config(const ramp_shape *shape, int idx, ramp_config
     int n = 0, cnt = 0;
     const Fp8Kernel *t = fp8_kernels(&n);
     for (int i = 0; i < n; ++i) {
-        if (!fp8_in_pool(t[i], *shape)) continue;
+        if (!fp8_valid_for_shape(t[i], *shape)) continue;
         if (cnt++ == idx) {
             *out = t[i].cfg;
             return RAMP_OK;

@@ -69,6 +69,20 @@ def test_fp8_config_family(name):
         ramp.fp8_config_wave_capacity(ramp.configs(sh)[0])
 
 
+def test_fp8_family_and_its_table_do_not_depend_on_the_batch_size(tmp_path):
+    """One table serves every batch size, as in bf16: fitted (and saved) with one T, loaded and indexed with another."""
+    from paper_2604_26039_amd import tuner
+    path = str(tmp_path / "fp8.json")
+    for s in (synth.SHAPES[n] for n in ("olmoe", "qwen3", "mixtral", "dsv3")):
+        fam = tuner.Family.of(s, 1, fp8=True)
+        theta = np.random.default_rng(0).uniform(1, 2, (len(fam.cfgs), 4)).astype(np.float32)
+        tuner.save_model(path, fam, theta, tuner.MI355X_MODEL)
+        for T in (32, 64, 700, 8192):
+            other = tuner.Family.of(s, T, fp8=True)
+            assert [c.key() for c in other.cfgs] == [c.key() for c in fam.cfgs], (s.name, T)
+            assert np.array_equal(tuner.load_model(path, other)[0], theta)
+
+
 def test_fp8_wave_capacity_follows_from_the_registers_and_lds_of_the_kernels():
     """W(c) / 256 by hand: 512 registers per SIMD lane (VGPRs and AGPRs, blocks of 8), 4 SIMDs, 160 KB of LDS; persistent: 1."""
     with open(os.path.join(lib_build.OBJ_DIR, "fp8.hip.resources.json")) as f:
