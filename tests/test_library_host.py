@@ -83,6 +83,18 @@ def test_fp8_family_and_its_table_do_not_depend_on_the_batch_size(tmp_path):
             assert np.array_equal(tuner.load_model(path, other)[0], theta)
 
 
+def test_fp8_tuner_family_leaves_out_what_the_persistent_tiles_replace():
+    from paper_2604_26039_amd import tuner
+    keys = lambda cfgs: [c.key() for c in cfgs]
+    staged = lambda c: not c.mode & 0x500
+    for s, persistent in ((synth.SHAPES["qwen3"], True), (synth.Shape("short", 256, 512, 8, 2), False), (synth.Shape("odd", 1152, 896, 48, 6), False)):
+        every = ramp.fp8_configs(ramp.Shape(64, s.k, s.E, s.H, s.I))
+        assert any(c.mode & 0x400 for c in every) == persistent
+        left_out = [c for c in every if persistent and staged(c) and c.bm >= 64]
+        assert bool(left_out) == persistent
+        assert keys(tuner.Family.of(s, 64, fp8=True).cfgs) == [k for k in keys(every) if k not in keys(left_out)]
+
+
 def test_fp8_wave_capacity_follows_from_the_registers_and_lds_of_the_kernels():
     """W(c) / 256 by hand: 512 registers per SIMD lane (VGPRs and AGPRs, blocks of 8), 4 SIMDs, 160 KB of LDS; persistent: 1."""
     with open(os.path.join(lib_build.OBJ_DIR, "fp8.hip.resources.json")) as f:
