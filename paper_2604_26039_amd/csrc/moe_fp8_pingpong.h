@@ -23,9 +23,13 @@
 // maxima meet in LDS across the four wavefronts of a token row (one barrier), codes and scale bytes are stored in the
 // order the down-projection loads them, and the activation never exists in bf16 in memory.
 //
-// Measured (kernel trace): Mixtral-shaped layer, T = 8192 (5.8 TFLOP): up-projection 2082 us = 1.85 PFLOP/s and down-projection
-// 961 us = 2.0 PFLOP/s, against 3073 + 320 (quantising pass) + 1302 us of the 128 x 256 tile with one barrier per slice; layer
-// 4818 -> 3129 us.  Qwen3-shaped, T = 512, 39 active experts (128-row tile): 46 + 32 us against 59 + 10 + 36 us, layer 101 -> 85 us.
+// Measured: Mixtral-shaped layer, T = 8192 (5.8 TFLOP), 256-row tile: up-projection 2114 us = 1.82 PFLOP/s and down-projection
+// 974 us = 1.98 PFLOP/s (kernel trace), against 3073 + 320 (quantising pass) + 1302 us of the 128 x 256 tile with one barrier per
+// slice; layer 4800 -> 3100 to 3350 us from box to box.  The matrix pipes are busy 43 % (up) and 52 % (down) of the
+// time, wavefronts wait for 48 and 46 % of theirs, and the up-projection's reads of token rows from LDS meet at banks (504 thousand
+// of its 4.4 million clocks per unit; 19 thousand in the down-projection, whose rows come in fragment order).
+// Qwen3-shaped, T = 512, 39 active experts, three copies of the weights in turn: layer 102.6 -> 78 us; with one copy, which the
+// memory-side cache holds, 28 + 29 us of projections (128-row tile).
 #pragma once
 
 #include <type_traits>

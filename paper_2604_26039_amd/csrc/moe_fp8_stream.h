@@ -8,9 +8,10 @@
 // trips through memory, are gone, for about 60 instructions per 16 rows and slice that hide under the weight loads.
 //
 // Measured (layer, best configuration of each family, against the best LDS-staged or persistent FP8 tile): OLMoE-shaped T = 1
-// 36 -> 17 us (two launches instead of six), Qwen3-shaped T = 8 80 -> 61 us, Mixtral-shaped T = 1 222 -> 75 us and T = 8
-// 297 -> 252 us (5.6 TB/s of weights), DeepSeek-V3-shaped T = 16 844 -> 786 us (6.05 TB/s).  From about 16 rows per expert on
-// the tiles with shared operands are the better ones (Mixtral-shaped T = 128: 317 us against 397).
+// 36 -> 17 us (two launches instead of six; 20 us with the weights out of the memory-side cache), Qwen3-shaped T = 8 77 -> 56 us,
+// Mixtral-shaped T = 1 221 -> 71 us and T = 32 293 -> 264 us (5.3 TB/s of weights), DeepSeek-V3-shaped T = 64 1652 -> 1573 us
+// (6.5 TB/s).  Between 24 and 32 rows per expert the tiles with shared operands become the better ones (Mixtral-shaped: 16 rows
+// 287 us against 307, 24 rows 303 against 306, 32 rows 452 against 315).
 #pragma once
 
 #include "align_tiny.h"

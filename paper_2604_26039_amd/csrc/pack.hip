@@ -46,8 +46,8 @@ namespace {
 // transposition to "8 consecutive k of one feature" stays inside the lane), then through LDS, where the block has the order
 // of its 32 output fragments, so that stores are whole runs of 4 KB (the four k-steps of a row block).  The 16-byte chunk
 // index inside a fragment is XOR-ed with its k-quarter: the eight writes of a lane then meet each bank no more often than the
-// linear reads do.  OLMoE-shaped layer (1.61 GB moved): 432 -> 302 us (5.3 TB/s; a large copy reaches 4.9), against one
-// lane gathering its chunk as eight 2-byte loads a row apart and three launches.
+// linear reads do.  OLMoE-shaped layer (1.61 GB moved): 435 -> 291 us, 303 on another box (5.5 and 5.3 TB/s; a copy
+// of 1 to 2 GiB reaches 4.9 to 5.2), against one lane gathering its chunk as eight 2-byte loads a row apart and three launches.
 struct PackPart {
     const uint16_t *src;
     uint16_t *dst;
