@@ -467,7 +467,12 @@ bool fp8_valid_for_shape(const Fp8Kernel &k, const ramp_shape &s)
     if ((2 * s.I) % k.cfg.bn || s.H % k.cfg.bn) return false;
     const size_t cap = ramp_align_capacity(s.T, s.k, s.E, k.cfg.bm);
     if ((cap + 16) * (size_t)s.I >= (1ull << 32) || (size_t)s.T * s.H >= (1ull << 32)) return false;
-    if (k.launch_stream && 2ull * s.I * s.H >= (1ull << 32)) return false;  // 32-bit byte offsets inside an expert
+    if (k.launch_stream) {
+        if (2ull * s.I * s.H >= (1ull << 32)) return false;  // 32-bit byte offsets inside an expert
+        // a workgroup per tile, in one launch: less than 2^32 threads
+        const size_t n_tiles = (size_t)(2 * s.I > s.H ? 2 * s.I : s.H) / k.cfg.bn;
+        if (n_tiles * (cap / k.cfg.bm) * (size_t)(k.cfg.waves * kWave) >= (1ull << 32)) return false;
+    }
     if (k.launch_pp) {
         // its load stream runs two slices ahead, across one tile boundary at most; 32-bit offsets inside an expert
         constexpr int least = Fp8PingPongTraits<1, 1>::MIN_SLICES;

@@ -83,6 +83,21 @@ def test_fp8_family_and_its_table_do_not_depend_on_the_batch_size(tmp_path):
             assert np.array_equal(tuner.load_model(path, other)[0], theta)
 
 
+def test_fp8_streaming_tiles_end_where_their_launch_would_pass_2_32_threads():
+    s = synth.SHAPES["mixtral"]
+    every = ramp.fp8_configs(shape_of("mixtral", 1))
+    seen = set()
+    for T in (8192, 50000, 70000, 100000, 140000):
+        listed = {c.key() for c in ramp.fp8_configs(shape_of("mixtral", T))}
+        for c in every:
+            threads = max(2 * s.I, s.H) // c.bn * (ramp.align_capacity(T, s.k, s.E, c.bm) // c.bm) * c.waves * 64
+            runs = not c.mode & 0x100 or threads < 2 ** 32
+            assert (c.key() in listed) == runs, (T, c)
+            seen.add(runs)
+        assert any(c.mode & 0x400 and c.key() in listed for c in every)
+    assert seen == {True, False}
+
+
 def test_fp8_tuner_family_leaves_out_what_the_persistent_tiles_replace():
     from paper_2604_26039_amd import tuner
     keys = lambda cfgs: [c.key() for c in cfgs]
