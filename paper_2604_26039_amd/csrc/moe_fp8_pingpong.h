@@ -249,6 +249,12 @@ __global__ __launch_bounds__(512, 1) void moe_fp8_pingpong_kernel(GemmArgs a, Fp
                 acc[i][h * 4 + nb] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(wf[i], xf[nb], acc[i][h * 4 + nb], 0, 0, 0,
                                                                                       i < 2 ? s0 : s1, 0, sb);
         }
+        // (no instruction) keeps the products in this phase: the compiler otherwise sinks them past the barrier, behind the
+        // branches of the next M phase, where nothing runs beside them
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(acc[i][h * 4 + nb]));
     };
     // token blocks with a real row (they come first) among those of this wavefront in a half
     auto blocks_of_half = [&](int rows, int h) __attribute__((always_inline)) {
