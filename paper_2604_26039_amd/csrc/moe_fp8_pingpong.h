@@ -148,7 +148,8 @@ __global__ __launch_bounds__(512, 1) void moe_fp8_pingpong_kernel(GemmArgs a, Fp
             if (h * 128 + (wave + 8 * t) * 8 >= rows) return 0u;  // nothing but padding: one cache line for all lanes
             const uint32_t p = pair < (uint32_t)a.P ? pair : 0u;
             const uint32_t tok = (uint32_t)(((unsigned long long)p * a.topk_magic) >> 40);
-            return tok * (uint32_t)a.K + (uint32_t)(((lane & 7) ^ ((row >> 1) & 7)) * 16);
+            const uint32_t c = (uint32_t)((lane & 7) ^ ((row >> 1) & 7));  // piece 2*(c % 4) + c/4 of the row
+            return tok * (uint32_t)a.K + ((c & 3u) * 2u + (c >> 2)) * 16u;
         }
         const int blk = h * 8 + ((wave + 8 * t) >> 1);
         const uint32_t l = (uint32_t)lane * 16u;
@@ -216,10 +217,10 @@ __global__ __launch_bounds__(512, 1) void moe_fp8_pingpong_kernel(GemmArgs a, Fp
         }
     };
     // token block nb of this wavefront inside a half is block 2*nb + wm (blocks are dealt to the two wavefront rows)
-    const int xlane = (STAGE == 1) ? (r16 >> 3) * 1024 + (r16 & 7) * 128 + (((2 * q) ^ ((r16 >> 1) & 7)) * 16) : lane * 16;
+    const int xlane = (STAGE == 1) ? (r16 >> 3) * 1024 + (r16 & 7) * 128 + ((q ^ ((r16 >> 1) & 7)) * 16) : lane * 16;
     auto read_x = [&](int buf) __attribute__((always_inline)) {
         const char *p = lds_x + buf * PT::XH_BYTES + wm * 2048;
-        const int lo = xlane, hi = (STAGE == 1) ? (xlane ^ 16) : xlane + 1024;
+        const int lo = xlane, hi = (STAGE == 1) ? (xlane ^ 64) : xlane + 1024;
 #pragma unroll
         for (int nb = 0; nb < 4; ++nb)
             xf[nb] = join(*reinterpret_cast<const intx4 *>(p + nb * 4096 + lo), *reinterpret_cast<const intx4 *>(p + nb * 4096 + hi));
