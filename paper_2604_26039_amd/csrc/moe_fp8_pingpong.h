@@ -96,17 +96,13 @@ __global__ __launch_bounds__(512, 1) void moe_fp8_pingpong_kernel(GemmArgs a, Fp
     const int KT = a.K >> 7;
     const int m_tiles = a.meta[1];
 
-    auto uniform_i32 = [](const int32_t *p) __attribute__((always_inline)) {
-        return *(const __attribute__((address_space(4))) int32_t *)p;  // wave-uniform, written by an earlier launch
-    };
-    auto next_tile = [&](int id, int &n_tile, int &m_tile) __attribute__((always_inline)) -> int {
-        for (; id < a.total_tiles; id += (int)gridDim.x) {
-            tile_of_id_rotated(a, id, n_tile, m_tile);
-            n_tile = __builtin_amdgcn_readfirstlane(n_tile);
-            m_tile = __builtin_amdgcn_readfirstlane(m_tile);
-            if (m_tile < m_tiles) return id;
-        }
-        return -1;
+    const TileWalk walk = tile_walk(a, m_tiles, a.tile_expert);
+    auto next_tile = [&](int slot, int &n_tile, int &m_tile) __attribute__((always_inline)) -> int {
+        if (slot >= walk.total) return -1;
+        tile_of_slot(a, walk, slot, n_tile, m_tile);
+        n_tile = __builtin_amdgcn_readfirstlane(n_tile);
+        m_tile = __builtin_amdgcn_readfirstlane(m_tile);
+        return slot;
     };
     auto phase_barrier = [&]() __attribute__((always_inline)) {
         __builtin_amdgcn_sched_barrier(0);
@@ -264,10 +260,10 @@ __global__ __launch_bounds__(512, 1) void moe_fp8_pingpong_kernel(GemmArgs a, Fp
     };
 
     int n_tile, m_tile;
-    int id = next_tile((int)blockIdx.x, n_tile, m_tile);
+    int id = next_tile((int)blockIdx.x >> 3, n_tile, m_tile);
     if (id < 0) return;
-    int rows = uniform_i32(a.tile_rows + m_tile);
-    TileSrc src = weights_of(n_tile, uniform_i32(a.tile_expert + m_tile));
+    int rows = load_uniform_i32(a.tile_rows + m_tile);
+    TileSrc src = weights_of(n_tile, load_uniform_i32(a.tile_expert + m_tile));
     int src_m = m_tile;       // tile the weight and scale loads are in
     uint32_t srow = 0;
     {
@@ -315,14 +311,14 @@ __global__ __launch_bounds__(512, 1) void moe_fp8_pingpong_kernel(GemmArgs a, Fp
     while (true) {
         // the following tile of this workgroup, whose first slices are loaded while this one finishes
         int n_next = n_tile, m_next = m_tile;
-        const int id_next = next_tile(id + (int)gridDim.x, n_next, m_next);
+        const int id_next = next_tile(id + ((int)gridDim.x >> 3), n_next, m_next);
         const bool has_next = id_next >= 0;
         if (!has_next) {
             n_next = n_tile;
             m_next = m_tile;
         }
-        const int rows_next = has_next ? uniform_i32(a.tile_rows + m_next) : 0;
-        TileSrc src_next = weights_of(n_next, uniform_i32(a.tile_expert + m_next));
+        const int rows_next = has_next ? load_uniform_i32(a.tile_rows + m_next) : 0;
+        TileSrc src_next = weights_of(n_next, load_uniform_i32(a.tile_expert + m_next));
         if (!has_next) src_next.w_lane = 0;
         uint32_t xoff_n[NH][2] = {}, srow_n = 0;
         if (STAGE == 1) {

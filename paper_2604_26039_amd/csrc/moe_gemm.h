@@ -215,6 +215,12 @@ __device__ __forceinline__ void wait_vmcnt()
     __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
 }
 
+// Read-only table entry at a wave-uniform address that no launch in flight writes.
+__device__ __forceinline__ int32_t load_uniform_i32(const int32_t *p)
+{
+    return *(const __attribute__((address_space(4))) int32_t *)(p);
+}
+
 // Workgroup -> tile.  Workgroups are handed to the 8 XCDs round robin (id % 8), each XCD has its own
 // 4 MB L2 and runs 32 workgroups of the large tiles at a time.  Consecutive workgroups of one XCD
 // therefore take a block of group_m M-tiles x group_n N-tiles: the token slices are shared by the
@@ -243,17 +249,55 @@ __device__ __forceinline__ void tile_of_id(const GemmArgs &a, int id, int &n_til
 // and 9: measured 7 % slower on such a layer).  The tiles an XCD works on at a time stay the same, who gets which
 // changes.  Same-box A/B of the layer: DeepSeek-V3 T = 2048 at 52 active experts (two tiles each) 2010 -> 1766 us,
 // Mixtral T = 8192 4980 -> 4880 us, T = 1024 1035 -> 1013 us, the other large points within +-1 %.
-__device__ __forceinline__ void tile_of_id_rotated(const GemmArgs &a, int id, int &n_tile, int &m_tile)
+//
+// The walk also knows the real number of M-tiles.
+struct TileWalk {
+    int full, total;   // slots of this XCD in the whole rounds, and in all
+    int m_full, tail0; // M-tiles of the whole rounds; first tile of this XCD's share of the rest
+    int xm, gm, gn;    // the round is split between xm x 8/xm XCDs; M-tiles x N-tiles of an XCD's block
+};
+__device__ __forceinline__ TileWalk tile_walk(const GemmArgs &a, int m_tiles, const int32_t *tile_expert)
 {
-    const int xcd = id & 7, s = id >> 3;
-    const int per_block = a.group_m * a.group_n;
+    TileWalk w;
+    const int xcd = (int)blockIdx.x & 7, per_round = 8 * a.group_m;
+    const int rounds = m_tiles / per_round, rest = (m_tiles - rounds * per_round) * a.n_tiles;
+    w.m_full = rounds * per_round;
+    w.full = rounds * a.group_m * a.n_tiles;
+    w.tail0 = xcd * rest / 8;
+    w.total = w.full + (xcd + 1) * rest / 8 - w.tail0;
+    w.xm = 8;
+    if (rounds > 0 && a.group_m_req == 0 && a.group_m <= 2) {
+        int same = 0;
+#pragma unroll
+        for (int i = 0; i < 7; ++i) same += load_uniform_i32(tile_expert + i) == load_uniform_i32(tile_expert + i + 1);
+        if (a.group_m == 1 && same >= 6 && a.n_tiles % 4 == 0) w.xm = 2;
+        else if (same >= 4 && a.n_tiles % 2 == 0) w.xm = 4;
+    }
+    w.gm = a.group_m * (8 / w.xm);
+    w.gn = a.group_n / (8 / w.xm);
+    return w;
+}
+// Tile of slot s < total.
+__device__ __forceinline__ void tile_of_slot(const GemmArgs &a, const TileWalk &w, int s, int &n_tile, int &m_tile)
+{
+    if (s >= w.full) {
+        const int f = w.tail0 + s - w.full;
+        const int m = f / a.n_tiles;
+        m_tile = w.m_full + m;
+        n_tile = f - m * a.n_tiles;
+        return;
+    }
+    const int xcd = (int)blockIdx.x & 7;
+    const int per_block = w.gm * w.gn;
     const int sb = s / per_block;
-    const int w = (s - sb * per_block + sb) % per_block;
-    const int dn = w / a.group_m, dm = w - dn * a.group_m;
-    const int nbn = a.n_tiles / a.group_n;
-    const int mb = sb / nbn, nbi = sb - mb * nbn;
-    n_tile = nbi * a.group_n + dn;
-    m_tile = (mb * 8 + ((xcd + 3 * mb) & 7)) * a.group_m + dm;
+    const int v = (s - sb * per_block + sb) % per_block;
+    const int dn = v / w.gm, dm = v - dn * w.gm;
+    const int blocks_n = a.n_tiles / (w.gn * (8 / w.xm));
+    const int mb = sb / blocks_n, nbi = sb - mb * blocks_n;
+    const int x = (xcd + 3 * mb) & 7;
+    const int xn = x / w.xm, xm = x - xn * w.xm;
+    n_tile = (nbi * (8 / w.xm) + xn) * w.gn + dn;
+    m_tile = (mb * w.xm + xm) * w.gm + dm;
 }
 
 __device__ __forceinline__ void tile_of_workgroup(const GemmArgs &a, int &n_tile, int &m_tile)

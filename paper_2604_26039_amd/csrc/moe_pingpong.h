@@ -75,12 +75,6 @@ struct PingPongTraits {
     static_assert(LDS_BYTES <= kLdsBytesPerCU, "tile does not fit in LDS");
 };
 
-// Read-only table entry at a wave-uniform address that no launch in flight writes.
-__device__ __forceinline__ int32_t load_uniform_i32(const int32_t *p)
-{
-    return *(const __attribute__((address_space(4))) int32_t *)(p);
-}
-
 // Wait until at most n vector-memory operations of this wavefront are outstanding (n wave-uniform).
 __device__ __forceinline__ void wait_vmcnt_upto(int n)
 {
@@ -133,18 +127,16 @@ __global__ __launch_bounds__(512, 1) void moe_pingpong_kernel(GemmArgs a)
     const int r16 = lane & 15, q = lane >> 4;
     const int m_tiles = a.meta[1];
 
-    // Tiles of this workgroup: ids blockIdx.x, + gridDim.x, ... (gridDim.x is a multiple of 8, so every tile of a
-    // workgroup maps to its own XCD); ids past the real M-tiles of this call are skipped.
-    auto next_tile = [&](int id, int &n_tile, int &m_tile) __attribute__((always_inline)) -> int {
-        for (; id < a.total_tiles; id += (int)gridDim.x) {
-            tile_of_id_rotated(a, id, n_tile, m_tile);
-            // wave-uniform by construction; saying so lets the per-tile table reads below be scalar loads, which do not
-            // count on vmcnt (a vector load would have to be waited for in order, behind every LDS-direct load in flight)
-            n_tile = __builtin_amdgcn_readfirstlane(n_tile);
-            m_tile = __builtin_amdgcn_readfirstlane(m_tile);
-            if (m_tile < m_tiles) return id;
-        }
-        return -1;
+    // Tiles of this workgroup: slots blockIdx.x / 8, + gridDim.x / 8, ... of its XCD's walk (gridDim.x is a multiple of 8).
+    const TileWalk walk = tile_walk(a, m_tiles, a.tile_expert);
+    auto next_tile = [&](int slot, int &n_tile, int &m_tile) __attribute__((always_inline)) -> int {
+        if (slot >= walk.total) return -1;
+        tile_of_slot(a, walk, slot, n_tile, m_tile);
+        // wave-uniform by construction; saying so lets the per-tile table reads below be scalar loads, which do not
+        // count on vmcnt (a vector load would have to be waited for in order, behind every LDS-direct load in flight)
+        n_tile = __builtin_amdgcn_readfirstlane(n_tile);
+        m_tile = __builtin_amdgcn_readfirstlane(m_tile);
+        return slot;
     };
 
     // ---- global element offsets of this lane's loads for k-slice 0 of a tile ----
@@ -358,7 +350,7 @@ __global__ __launch_bounds__(512, 1) void moe_pingpong_kernel(GemmArgs a)
     };
 
     int n_tile, m_tile;
-    int id = next_tile((int)blockIdx.x, n_tile, m_tile);
+    int id = next_tile((int)blockIdx.x >> 3, n_tile, m_tile);
     if (id < 0) return;
     int rows_cur = 0, rows_next = 0;
     tile_offsets(n_tile, m_tile, xoff, woff, wexp_w, rows_cur);
@@ -405,7 +397,7 @@ __global__ __launch_bounds__(512, 1) void moe_pingpong_kernel(GemmArgs a)
     while (true) {
         // following tile of this workgroup (its first slices are loaded while this one finishes)
         int n_next = 0, m_next = 0;
-        const int id_next = next_tile(id + (int)gridDim.x, n_next, m_next);
+        const int id_next = next_tile(id + ((int)gridDim.x >> 3), n_next, m_next);
         const bool has_next = id_next >= 0;
         if (has_next) {
             tile_offsets(n_next, m_next, xoff_n, woff_n, wexp_n, rows_next);
