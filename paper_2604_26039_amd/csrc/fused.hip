@@ -453,7 +453,7 @@ bool pair_rows_bf16(const ramp_shape &s)
 
 bool runs_two_launches(const KernelInfo &ki, const ramp_shape &s)
 {
-    return ki.launch_decode_up && s.T * s.k <= kDecodeMaxPairs && 16 % s.k == 0;
+    return ki.launch_decode_up && decode_in_two_launches(s.T, s.k);
 }
 
 // align(bm) + both projections of one configuration; `base` holds every workspace section but the per-pair rows,

@@ -169,7 +169,7 @@ __global__ __launch_bounds__(WF *WK * 64) void moe_decode_up_kernel(GemmArgs a, 
 }
 
 // grid = (H / (16*FBW)) * T workgroups of 16 wavefronts: wavefront w handles pair j = w / WK of the token over the
-// k-steps [wk*per, ...) with WK = 16 / k (k divides 16).
+// k-steps [wk*per, ...) with WK the largest power of two in 16 / k; wavefronts past the k-th pair's are idle.
 template <int FBW, int U>
 __global__ __launch_bounds__(1024) void moe_decode_down_kernel(DecodeDownArgs d)
 {
@@ -181,11 +181,11 @@ __global__ __launch_bounds__(1024) void moe_decode_down_kernel(DecodeDownArgs d)
     const PairWeight own_weight = load_pair_weight(d, t);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int WK = 16 / d.k;
+    const int WK = decode_pair_waves(d.k);
     const int j = wave / WK, wk = wave % WK;
     const int r16 = lane & 15, q = lane >> 4;
     const int pair = t * d.k + j;
-    const int e = d.ids[pair];
+    const int e = j < d.k ? d.ids[pair] : -1;
     const bool live = e >= 0 && e < d.E;
     const int KST = d.I / 32;
     const int per = (KST + WK - 1) / WK;

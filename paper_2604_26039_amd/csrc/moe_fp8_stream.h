@@ -257,7 +257,7 @@ __global__ __launch_bounds__(WF *WK * 64) void moe_fp8_decode_up_kernel(GemmArgs
 }
 
 // Second launch: down-projection, router weights and top-k sum of one token's 16 * FBW output features per workgroup, all of
-// its k pairs (moe_decode_down_kernel).  grid = (H / (16*FBW)) * T workgroups of 16 wavefronts, WK = 16 / k (k divides 16).
+// its k pairs (moe_decode_down_kernel).  grid = (H / (16*FBW)) * T workgroups of 16 wavefronts, WK as there.
 template <int FBW, int U>
 __global__ __launch_bounds__(1024) void moe_fp8_decode_down_kernel(DecodeDownArgs d, Fp8StreamArgs f)
 {
@@ -268,11 +268,11 @@ __global__ __launch_bounds__(1024) void moe_fp8_decode_down_kernel(DecodeDownArg
     const PairWeight own_weight = load_pair_weight(d, t);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int WK = 16 / d.k;
+    const int WK = decode_pair_waves(d.k);
     const int j = wave / WK, wk = wave % WK;
     const int r16 = lane & 15, q = lane >> 4;
     const int pair = t * d.k + j;
-    const int e = __builtin_amdgcn_readfirstlane(d.ids[pair]);
+    const int e = j < d.k ? __builtin_amdgcn_readfirstlane(d.ids[pair]) : -1;
     // To LDS here and not behind the slices: their batches leave no register for it under the 128 of sixteen wavefronts (it went
     // to scratch), and the wait for the id above, the younger load, has covered it.  Layer, T = 1: Mixtral-shaped 75.6 -> 73.6 us,
     // Qwen3-shaped 14.9 -> 14.7, OLMoE-shaped 17.1 as before; T = 8, OLMoE-shaped: 57.0 -> 56.7.
