@@ -65,6 +65,13 @@
     X(272, 256, 32, 2, 4, 4) \
     X(288, 256, 32, 2, 4, 4)
 
+// Ping-pong tiles that also run a hidden size of 256 * n + 128 (mode bit 0x20000 instead of 0x400;
+// the same kernels).
+#define RAMP_HALF_TILE_GROUP(X) \
+    X(128, 256, 32, 2, 4, 4) \
+    X(256, 256, 32, 2, 4, 4) \
+    X(288, 256, 32, 2, 4, 4)
+
 // Weight-streaming family (moe_stream.h): X(bm, FBW, WF, WK, U) ->
 // bn = WF*FBW*16 weight rows per tile, WF*WK wavefronts, K split WK ways inside the workgroup,
 // U k-steps per load batch.

@@ -398,11 +398,11 @@ Fp8Kernel make_fp8()
 }
 
 template <int NH>
-Fp8Kernel make_fp8_pingpong()
+Fp8Kernel make_fp8_pingpong(int family_bit)
 {
     using PT = Fp8PingPongTraits<1, NH>;
     Fp8Kernel k = {};
-    k.cfg = ramp_config{PT::BM, PT::BN, kGroup, 8, PT::NW, 1 | kModePingPong | kModeFp8};
+    k.cfg = ramp_config{PT::BM, PT::BN, kGroup, 8, PT::NW, 1 | family_bit | kModeFp8};
     set_kernel(k, "moe_fp8_pingpong_kernel", {1, NH}, &moe_fp8_pingpong_kernel<1, NH>, &moe_fp8_pingpong_kernel<2, NH>);
     k.launch_pp = &launch_fp8_pingpong<NH>;
     return k;
@@ -448,14 +448,16 @@ const Fp8Kernel *fp8_kernels(int *n)
 #define X(BM, BN, WM, WN, NS) make_fp8<BM, BN, WM, WN, NS>(),
         RAMP_FP8_CONFIGS(X)
 #undef X
-        make_fp8_pingpong<1>(),
-        make_fp8_pingpong<2>(),
+        make_fp8_pingpong<1>(kModePingPong),
+        make_fp8_pingpong<2>(kModePingPong),
 #define X(BM, FBW, WF, WK, U) make_fp8_stream<BM, FBW, WF, WK, U, false>(),
         RAMP_FP8_STREAM_CONFIGS(X)
 #undef X
 #define X(BM, FBW, WF, WK, U) make_fp8_stream<BM, FBW, WF, WK, U, true>(),
         RAMP_FP8_DECODE_CONFIGS(X)
 #undef X
+        make_fp8_pingpong<1>(kModeHalfTile),
+        make_fp8_pingpong<2>(kModeHalfTile),
     };
     *n = (int)(sizeof(table) / sizeof(table[0]));
     return table;
@@ -464,7 +466,7 @@ const Fp8Kernel *fp8_kernels(int *n)
 bool fp8_valid_for_shape(const Fp8Kernel &k, const ramp_shape &s)
 {
     if (!moe_shape_ok(s)) return false;
-    if ((2 * s.I) % k.cfg.bn || s.H % k.cfg.bn) return false;
+    if (!bn_tiles_shape(k.cfg, s)) return false;
     const size_t cap = ramp_align_capacity(s.T, s.k, s.E, k.cfg.bm);
     if ((cap + 16) * (size_t)s.I >= (1ull << 32) || (size_t)s.T * s.H >= (1ull << 32)) return false;
     if (k.launch_stream) {
@@ -513,7 +515,7 @@ Fp8Workspace fp8_workspace(const ramp_shape &s, const ramp_config &c)
     w.tile_rows = take((w.cap / (size_t)c.bm) * 4);
     w.counts = take((size_t)s.E * 4);
     w.meta = take(16);
-    const bool pp = (c.mode & kModePingPong) != 0;
+    const bool pp = mode_persistent(c.mode);
     w.slot_w = pp ? take(w.cap * 4) : off;
     w.align_ws_bytes = ramp_align_workspace_bytes(s.T, s.k, s.E);
     w.align_ws = take(w.align_ws_bytes);
@@ -841,7 +843,7 @@ extern "C" int ramp_fused_moe_fp8(const ramp_shape *shape, const ramp_config *cf
         p.w_stride = L.stride2;
         g.K = s.I;
         g.F = s.H;
-        g.n_tiles = s.H / cfg->bn;
+        g.n_tiles = (s.H + cfg->bn - 1) / cfg->bn;
         k->launch_pp(2, g, p, st);
         if (int rc = check_launch("moe_fp8_pingpong_kernel<2>")) return rc;
         return launch_combine(y_buf, g.y_bf16, topk_ids, s.T, s.k, s.E, s.H, static_cast<uint16_t *>(out), st);

@@ -14,6 +14,7 @@ void register_group4(KernelInfo *, int *);
 void register_group5(KernelInfo *, int *);
 void register_group6(KernelInfo *, int *);
 void register_group7(KernelInfo *, int *);
+void register_half_tile_group(KernelInfo *, int *);
 void register_stream_group0(KernelInfo *, int *);
 void register_stream_group1(KernelInfo *, int *);
 void register_stream_group2(KernelInfo *, int *);
@@ -38,6 +39,7 @@ void init_registry()
         register_stream_group0(g_kernels, &g_num_kernels);
         register_stream_group1(g_kernels, &g_num_kernels);
         register_stream_group2(g_kernels, &g_num_kernels);
+        register_half_tile_group(g_kernels, &g_num_kernels);
     });
 }
 
@@ -165,7 +167,7 @@ Workspace workspace_layout(const ramp_shape &s, const ramp_config &c)
     w.counts = take((size_t)s.E * 4);
     w.meta = take(16);
     // router weight per sorted slot, for the kernels that read it by slot (persistent ping-pong down-projection)
-    w.slot_w = (c.mode & kModePingPong) ? take(w.cap * 4) : off;
+    w.slot_w = mode_persistent(c.mode) ? take(w.cap * 4) : off;
     w.align_ws_bytes = ramp_align_workspace_bytes(s.T, s.k, s.E);
     w.align_ws = take(w.align_ws_bytes);
     w.a_buf = take(align_up(w.cap, 16) * (size_t)s.I * 2);  // fragment-major: whole blocks of 16 slots
@@ -219,14 +221,14 @@ bool config_valid_for_shape(const KernelInfo &ki, const ramp_shape &s)
     const ramp_config &c = ki.cfg;
     if (!shape_ok(s)) return false;
     if (s.H % c.bk || s.I % c.bk) return false;      // whole k-slices
-    if ((2 * s.I) % c.bn || s.H % c.bn) return false;  // whole feature tiles in both projections
+    if (!bn_tiles_shape(c, s)) return false;
     // 32-bit element offsets inside the kernels
     const size_t cap = ramp_align_capacity(s.T, s.k, s.E, c.bm);
     if ((cap + 16) * (size_t)s.I >= (1ull << 32) || (size_t)s.T * s.H >= (1ull << 32)) return false;
     if (2ull * s.I * s.H >= (1ull << 32)) return false;
     // the ping-pong kernel keeps stages-1 slices in flight across tile boundaries: a tile must be at least that long
     // (and the up-projection loads its token batches up to four slices ahead)
-    if ((c.mode & kModePingPong) && (s.H / c.bk < (c.stages > 4 ? c.stages : 4) || s.I / c.bk < c.stages)) return false;
+    if (mode_persistent(c.mode) && (s.H / c.bk < (c.stages > 4 ? c.stages : 4) || s.I / c.bk < c.stages)) return false;
 
     return true;
 }
@@ -249,7 +251,7 @@ int occupancy_estimate(const ramp_config &cfg, const char *family, const int *ta
     // up-projection kernel when the library was built: wavefronts per SIMD allowed by the register allocation
     // (4 SIMDs per unit, at most 8 wavefronts each), and 160 KB of LDS.  The persistent kernels launch one
     // workgroup per unit whatever would fit.
-    if (cfg.mode & kModePingPong) return 1;
+    if (mode_persistent(cfg.mode)) return 1;
     const KernelResources *r = find_resources(family, targs, n_targs);
     if (!r) return 0;  // no record for this kernel: the library was not built by its build script
     int waves_per_simd = r->waves_per_simd < 8 ? r->waves_per_simd : 8;
@@ -341,8 +343,8 @@ extern "C" int ramp_config_rounds(const ramp_shape *shape, const ramp_config *cf
         int gm = 1, gn = 1;
         // only the persistent kernels walk the map with a fixed set of workgroups; the others are dispatched
         // tile by tile as compute units free up
-        if (cfg->mode & kModePingPong) xcd_block_shape(nt[s], group_m_of_mode(cfg->mode), &gm, &gn);
-        out[2 * s] = (cfg->mode & kModePingPong) ? 8 * gm : 1;
+        if (mode_persistent(cfg->mode)) xcd_block_shape(nt[s], group_m_of_mode(cfg->mode), &gm, &gn);
+        out[2 * s] = mode_persistent(cfg->mode) ? 8 * gm : 1;
         out[2 * s + 1] = nt[s];
     }
     return RAMP_OK;
@@ -512,7 +514,7 @@ int enqueue_projections(const ramp_shape &s, const ramp_config &cfg, const Kerne
     if (!aligned) {
         ProbeScope probe(1, st);
         AlignSlotWeights sw = {nullptr, nullptr};
-        if (cfg.mode & kModePingPong) sw = AlignSlotWeights{topk_w, reinterpret_cast<float *>(base + w.slot_w)};
+        if (mode_persistent(cfg.mode)) sw = AlignSlotWeights{topk_w, reinterpret_cast<float *>(base + w.slot_w)};
         rc = launch_align(topk_ids, s.T, s.k, s.E, cfg.bm, sorted, tile_expert, tile_rows, counts, meta, base + w.align_ws,
                           w.align_ws_bytes, st, pred, pred_value, sw);
     }
@@ -520,7 +522,7 @@ int enqueue_projections(const ramp_shape &s, const ramp_config &cfg, const Kerne
 
     GemmArgs g = {};
     g.sorted = sorted;
-    g.slot_w = (cfg.mode & kModePingPong) ? reinterpret_cast<const float *>(base + w.slot_w) : nullptr;
+    g.slot_w = mode_persistent(cfg.mode) ? reinterpret_cast<const float *>(base + w.slot_w) : nullptr;
     g.tile_expert = tile_expert;
     g.tile_rows = tile_rows;
     g.topk_magic = topk_magic_of(s.k);
@@ -558,7 +560,7 @@ int enqueue_projections(const ramp_shape &s, const ramp_config &cfg, const Kerne
     g.up_offset = 0;
     g.K = s.I;
     g.F = s.H;
-    g.n_tiles = s.H / cfg.bn;
+    g.n_tiles = (s.H + cfg.bn - 1) / cfg.bn;
     {
         ProbeScope probe(3, st);
         ki.launch(2, g, st);
@@ -701,7 +703,7 @@ extern "C" int ramp_fused_moe_selected(const ramp_shape *shape, int n_cand, cons
     for (int c = 0; c < n_cand; ++c) {
         if (runs_two_launches(*ki[c], s)) continue;
         const Workspace w = workspace_layout(s, cfgs[c]);
-        choices.c[c] = AlignChoice{cfgs[c].bm, (int32_t)w.cap, (cfgs[c].mode & kModePingPong) ? 1 : 0, w.sorted, w.tile_expert,
+        choices.c[c] = AlignChoice{cfgs[c].bm, (int32_t)w.cap, mode_persistent(cfgs[c].mode) ? 1 : 0, w.sorted, w.tile_expert,
                                    w.tile_rows, w.counts, w.meta, w.slot_w};
         ++aligns;
     }

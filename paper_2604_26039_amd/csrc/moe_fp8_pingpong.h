@@ -116,6 +116,7 @@ __global__ __launch_bounds__(512, 1) void moe_fp8_pingpong_kernel(GemmArgs a, Fp
         const uint8_t *w;        // codes of row block wave/2 of the tile, half-fragment wave%2, slice 0
         const uint8_t *ws;       // weight scale row of the tile (gate, or down)
         uint32_t w_lane;         // lane * 16, or 0 past the last tile
+        uint32_t w_second, s_second;  // from the first eight row blocks, and their scale row, to the other eight
     };
     auto weights_of = [&](int n_tile, int e) __attribute__((always_inline)) {
         TileSrc s;
@@ -123,6 +124,10 @@ __global__ __launch_bounds__(512, 1) void moe_fp8_pingpong_kernel(GemmArgs a, Fp
               (size_t)((wave & 1) * 1024);
         s.ws = f.wscale + (size_t)e * f.wscale_expert_stride + (size_t)(n_tile * (FEAT / 128)) * (size_t)f.w_stride;
         s.w_lane = (uint32_t)lane * 16u;
+        // stage 1: the up rows; stage 2: the tile's other 128 features, or the same ones again where a last tile has none
+        const bool second = STAGE == 1 || n_tile * FEAT + 128 < a.F;
+        s.w_second = STAGE == 1 ? f.up_offset : second ? (uint32_t)KT * (8u * 2048u) : 0u;
+        s.s_second = STAGE == 1 ? f.wscale_up_offset : second ? (uint32_t)f.w_stride : 0u;
         return s;
     };
     // row block wave/2 + 4*s: stage 1 holds 8 gate row blocks, then the 8 up row blocks of the same features
@@ -131,7 +136,7 @@ __global__ __launch_bounds__(512, 1) void moe_fp8_pingpong_kernel(GemmArgs a, Fp
         const uint32_t rb4 = (uint32_t)KT * (4u * 2048u);
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-            const uint32_t off = (STAGE == 1) ? (uint32_t)(s & 1) * rb4 + (s >= 2 ? f.up_offset : 0u) : (uint32_t)s * rb4;
+            const uint32_t off = (uint32_t)(s & 1) * rb4 + (s >= 2 ? src.w_second : 0u);
             load_to_lds_16B(base + off + src.w_lane, lds_w + buf * PT::W_BYTES + (wave + 8 * s) * 1024);
         }
     };
@@ -178,8 +183,7 @@ __global__ __launch_bounds__(512, 1) void moe_fp8_pingpong_kernel(GemmArgs a, Fp
             int word = chunk * 4 + (lane & 3);
             const int last = (KT - 1) >> 2;
             word = word < last ? word : last;
-            const uint32_t second = (STAGE == 1) ? f.wscale_up_offset : (uint32_t)f.w_stride;
-            const uint8_t *p = src.ws + ((lane & 4) ? second : 0u) + (uint32_t)word * 4u;
+            const uint8_t *p = src.ws + ((lane & 4) ? src.s_second : 0u) + (uint32_t)word * 4u;
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)p,
                                              (__attribute__((address_space(3))) void *)(dst + BM * 16), 4, 0, 0);
         } else if (STAGE == 2 && chunk == 0 && (role == 5 || role == 6)) {
@@ -472,7 +476,7 @@ __global__ __launch_bounds__(512, 1) void moe_fp8_pingpong_kernel(GemmArgs a, Fp
             char *stg = lds_e + wave * (SR * 128);
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
-                if ((nb & 3) >= nbh[nb >> 2]) continue;
+                if ((nb & 3) >= nbh[nb >> 2] || f0 >= a.F) continue;  // (f0: the empty half of a last tile)
                 const int row0 = (nb >> 2) * 128 + ((nb & 3) * 2 + wm) * 16;
                 const float wgt = wgts[row0 + er];
                 if (a.y_bf16) {

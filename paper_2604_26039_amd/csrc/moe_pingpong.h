@@ -174,7 +174,8 @@ __global__ __launch_bounds__(512, 1) void moe_pingpong_kernel(GemmArgs a)
                 base = (rb < half) ? (uint32_t)(f0 / 16 + rb) * (uint32_t)KST * kFragElems
                                    : (uint32_t)a.up_offset + (uint32_t)(f0 / 16 + rb - half) * (uint32_t)KST * kFragElems;
             } else {
-                base = (uint32_t)(f0 / 16 + rb) * (uint32_t)KST * kFragElems;
+                const int rbx = f0 + rb * 16 < a.F ? rb : rb - TT::RB / 2;  // past the features of half a last tile
+                base = (uint32_t)(f0 / 16 + rbx) * (uint32_t)KST * kFragElems;
             }
             wo[s] = base + (uint32_t)ks * kFragElems + (uint32_t)lane * 8;
         }
@@ -546,7 +547,9 @@ __global__ __launch_bounds__(512, 1) void moe_pingpong_kernel(GemmArgs a)
             }
             slot_par ^= 1;
         }
-        if (STAGE == 2 && a.y_bf16) {
+        const bool no_features = STAGE == 2 && f0 + wn * (FB * 16) >= a.F;  // the empty half of a last tile
+        if (no_features) {
+        } else if (STAGE == 2 && a.y_bf16) {
             // bf16 per-pair rows leave through LDS: a lane holds 16 consecutive features of one token, but a store
             // instruction should cover whole 128-byte lines.  Per chunk of two token blocks the wavefront writes its
             // 32 x 64 weighted results into its own 4 KB staging area (row-major, 16-byte chunk index XOR-ed with
@@ -599,7 +602,7 @@ __global__ __launch_bounds__(512, 1) void moe_pingpong_kernel(GemmArgs a)
         }
 #pragma unroll
         for (int t = 0; t < TAILB; ++t) {
-            if (t >= tail_n) continue;
+            if (t >= tail_n || no_features) continue;
             if (STAGE == 1)
                 store_token_row<1, 1>(a, &acc_t[2 * t], &acc_t[2 * t + 1], 1, (size_t)(m_tile * BM + BMAIN + t * 16 + r16), f0 / 16 + wn * FB + wm, q, 1.0f);
             else if (tail_pair[t] < a.P)
@@ -643,13 +646,13 @@ void launch_pingpong(int stage, const GemmArgs &a, hipStream_t stream)
 }
 
 template <int BM, int BN, int BK, int WM, int WN, int NSTAGE>
-KernelInfo make_pingpong_info(int group_bits = 0)
+KernelInfo make_pingpong_info(int family_bits = kModePingPong)
 {
     using TT = typename PingPongTraits<1, BM, BN, BK, WM, WN, NSTAGE>::TT;
     constexpr int l1 = PingPongTraits<1, BM, BN, BK, WM, WN, NSTAGE>::LDS_BYTES;
     constexpr int l2 = PingPongTraits<2, BM, BN, BK, WM, WN, pingpong_down_stages<BM, WM, NSTAGE>()>::LDS_BYTES;
     KernelInfo ki = {};
-    ki.cfg = ramp_config{BM, BN, BK, WM * WN, NSTAGE, (WM - 1) | kModePingPong | (group_bits << kModeGroupShift)};
+    ki.cfg = ramp_config{BM, BN, BK, WM * WN, NSTAGE, (WM - 1) | family_bits};
     ki.wm = WM;
     ki.wn = WN;
     ki.lds_bytes = l1 > l2 ? l1 : l2;

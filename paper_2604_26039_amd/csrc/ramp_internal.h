@@ -152,6 +152,12 @@ constexpr int kModePingPong = 0x400;  // persistent ping-pong kernel (moe_pingpo
 // spans all N-tiles (the token rows of its M-tiles stay in L2 instead).
 constexpr int kModeDecode = 0x2000;   // with kModeStream: calls of at most 64 pairs run the two-launch form (moe_decode.h)
 constexpr int kModeFp8 = 0x10000;     // W8A8 FP8 family (fp8.hip), listed by ramp_fp8_get_config
+// in place of kModePingPong: a 256-wide persistent tile for H = 256 * n + 128.  The down-projection's last N-tile holds 128
+// features; its other half re-reads the weights of the first (loads that hit, products that are not stored).  H = 1152, I = 896, E = 48, k = 6, against
+// the best tile of 128 features (bf16 256 x 128, FP8 32 x 128): bf16 T = 1024 111 -> 103 us, 4096 230 -> 199, 8192 381 -> 330;
+// FP8 T = 256 72 -> 60 us, 1024 140 -> 83, 8192 711 -> 259.  Below some 64 rows per expert the narrow tiles stay the better ones.
+constexpr int kModeHalfTile = 0x20000;
+constexpr bool mode_persistent(int mode) { return (mode & (kModePingPong | kModeHalfTile)) != 0; }
 constexpr int kModeGroupShift = 12;
 constexpr int kModeGroupMask = 0xF << kModeGroupShift;
 inline int group_m_of_mode(int mode) { const int v = (mode & kModeGroupMask) >> kModeGroupShift; return v ? (1 << v) : 0; }
@@ -209,6 +215,11 @@ int num_kernels();
 const KernelInfo &kernel_info(int i);
 const KernelInfo *find_kernel(const ramp_config &cfg);
 bool config_valid_for_shape(const KernelInfo &ki, const ramp_shape &s);
+// bn divides the features of both projections, or leaves half a tile of the down-projection's for a configuration made for that
+inline bool bn_tiles_shape(const ramp_config &c, const ramp_shape &s)
+{
+    return (2 * s.I) % c.bn == 0 && s.H % c.bn == ((c.mode & kModeHalfTile) ? c.bn / 2 : 0);
+}
 bool config_in_pool(const KernelInfo &ki, const ramp_shape &s);
 int occupancy_estimate(const ramp_config &cfg, const char *family, const int *targs, int n_targs);
 int runtime_occupancy(const void *const kernel_fn[2], int block_threads, int *wg_per_cu);
