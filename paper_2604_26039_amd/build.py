@@ -28,7 +28,7 @@ OBJ_DIR = os.path.join(PKG, "_build")
 KERNEL_SOURCES = ["gemm_group0.hip", "gemm_group1.hip", "gemm_group2.hip", "gemm_group3.hip", "gemm_group4.hip",
                   "gemm_group5.hip", "gemm_group6.hip", "gemm_group7.hip", "stream_group0.hip", "stream_group1.hip",
                   "stream_group2.hip"]
-SOURCES = ["align.hip", "select.hip", "pack.hip", "fused.hip", "fp8.hip"] + KERNEL_SOURCES + ["cost_model.cpp"]
+SOURCES = ["align.hip", "select.hip", "pack.hip", "fused.hip", "fp8.hip", "stream_selected.hip"] + KERNEL_SOURCES + ["cost_model.cpp"]
 RESOURCE_SOURCES = KERNEL_SOURCES + ["fp8.hip"]  # hold projection kernels of a tile family
 HEADERS = ["ramp_internal.h", "moe_gemm.h", "moe_pingpong.h", "moe_stream.h", "moe_decode.h", "moe_fp8_pingpong.h", "moe_fp8_stream.h", "fp8_format.h", "align_tiny.h", "config_list.h", os.path.join(ROOT, "include", "ramp.h")]
 

@@ -100,6 +100,25 @@
     X(16, 2, 2, 4, 4)         \
     X(16, 2, 2, 2, 4)
 
+// The stream tiles that one launch of the device-selected layer can hold together (moe_stream_selected.hip): 8 or 4 wavefronts whose
+// operands and sums fit 128 registers, or nearly.
+#define RAMP_STREAM_SELECTED_GROUP(X) \
+    X(4, 2, 1, 8, 2)          \
+    X(8, 2, 1, 8, 2)          \
+    X(16, 2, 1, 8, 2)         \
+    X(16, 2, 1, 4, 2)         \
+    X(16, 2, 2, 4, 2)         \
+    X(16, 2, 4, 2, 2)         \
+    X(16, 2, 4, 1, 4)         \
+    X(16, 4, 2, 2, 2)         \
+    X(16, 4, 4, 1, 2)         \
+    X(32, 2, 1, 8, 2)         \
+    X(32, 2, 2, 4, 2)         \
+    X(32, 2, 4, 1, 2)         \
+    X(16, 2, 2, 4, 4)         \
+    X(16, 2, 2, 2, 4)         \
+    X(16, 2, 1, 8, 4)
+
 // Stream configurations that also have the two-launch form for calls of at most 64 pairs (moe_decode.h):
 // X(bm, FBW, WF, WK, U) as above; listed as separate configurations (mode bit 0x2000).
 #define RAMP_DECODE_GROUP(X) \

@@ -31,23 +31,15 @@ struct StreamTraits {
     static_assert(LDS_BYTES <= 64 * 1024, "reduction buffer too large");
 };
 
+// Work of one workgroup (or one of several that share a block) on M-tile x feature tile.
 template <int STAGE, int BM, int FBW, int WF, int WK, int U>
-__global__ __launch_bounds__(WF *WK * 64) void moe_stream_kernel(GemmArgs a)
+__device__ __forceinline__ void stream_tile(const GemmArgs &a, float *red, int n_tile, int m_tile, int wave, int lane)
 {
     using ST = StreamTraits<BM, FBW, WF, WK, U>;
     constexpr int NB = ST::NB;
     constexpr int FEAT_PER_TILE = (STAGE == 1) ? ST::BN / 2 : ST::BN;
     constexpr int FPW = (STAGE == 1) ? FBW / 2 : FBW;  // feature blocks per wavefront in the output
 
-    __shared__ __attribute__((aligned(16))) float red[ST::RED_FLOATS > 0 ? ST::RED_FLOATS : 4];
-
-    if (launch_deselected(a.pred, a.pred_value)) return;
-    const int n_tile = blockIdx.x % a.n_tiles;
-    const int m_tile = blockIdx.x / a.n_tiles;
-    if (m_tile >= a.meta[1]) return;
-
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
     const int wf = wave % WF, wk = wave / WF;
     const int r16 = lane & 15, q = lane >> 4;
     const int e = a.tile_expert[m_tile];
@@ -172,6 +164,18 @@ __global__ __launch_bounds__(WF *WK * 64) void moe_stream_kernel(GemmArgs a)
             store_token_row<2, FPW>(a, &acc[0][nb], &acc[0][nb], NB, (size_t)pair * a.F, f0 / 16, q, a.topk_w[pair]);
         }
     }
+}
+
+template <int STAGE, int BM, int FBW, int WF, int WK, int U>
+__global__ __launch_bounds__(WF *WK * 64) void moe_stream_kernel(GemmArgs a)
+{
+    using ST = StreamTraits<BM, FBW, WF, WK, U>;
+    __shared__ __attribute__((aligned(16))) float red[ST::RED_FLOATS > 0 ? ST::RED_FLOATS : 4];
+    if (launch_deselected(a.pred, a.pred_value)) return;
+    const int n_tile = blockIdx.x % a.n_tiles;
+    const int m_tile = blockIdx.x / a.n_tiles;
+    if (m_tile >= a.meta[1]) return;
+    stream_tile<STAGE, BM, FBW, WF, WK, U>(a, red, n_tile, m_tile, threadIdx.x >> 6, threadIdx.x & 63);
 }
 
 template <int BM, int FBW, int WF, int WK, int U>

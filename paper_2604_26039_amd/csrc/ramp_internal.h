@@ -185,6 +185,22 @@ inline void xcd_block_shape(int n_tiles, int group_m_req, int *group_m, int *gro
     }
 }
 
+// The stream candidates of a device-selected call, for one launch per projection (moe_stream_selected.hip): the position of a
+// candidate's tile in RAMP_STREAM_SELECTED_GROUP, or -1, and what differs between the candidates' arguments (byte offsets).
+struct StreamChoice {
+    int32_t shape, bn;
+    size_t sorted, tile_expert, meta, a_buf;
+};
+struct StreamChoices {
+    StreamChoice c[kMaxCandidates];
+};
+int stream_selected_shape(const ramp_config &cfg);  // -1: not a tile of that launch
+// args: those of the candidates, without what `choices` holds; features: 2 * I, or H
+int launch_stream_selected(int stage, const GemmArgs &args, char *base, int features, int n_cand, const StreamChoices &choices,
+                           unsigned blocks, hipStream_t stream);
+// Workgroups of a block of that launch's kernel for a tile of `waves` wavefronts
+constexpr int stream_selected_per_block(int waves) { return 8 / waves; }
+
 struct DecodeArgs;
 struct DecodeDownArgs;
 struct KernelInfo {
