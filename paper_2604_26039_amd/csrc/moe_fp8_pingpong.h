@@ -94,15 +94,21 @@ __global__ __launch_bounds__(512, 1) void moe_fp8_pingpong_kernel(GemmArgs a, Fp
     const int wm = wave >> 2, wn = wave & 3;  // wm is also the phase group
     const int r16 = lane & 15, q = lane >> 4;
     const int KT = a.K >> 7;
-    const int m_tiles = a.meta[1];
+    const int m_tiles = load_uniform_i32(a.meta + 1);
 
-    const TileWalk walk = tile_walk(a, m_tiles, a.tile_expert);
-    auto next_tile = [&](int slot, int &n_tile, int &m_tile) __attribute__((always_inline)) -> int {
-        if (slot >= walk.total) return -1;
-        tile_of_slot(a, walk, slot, n_tile, m_tile);
+    // As in the bf16 kernel, but only a down-projection tile of 128 rows is cut, in halves: the 128 features of an up-projection tile
+    // are quantised together, and the tile of 256 rows has no register to spare for it.
+    constexpr bool CUTS = STAGE == 2 && NH == 1;
+    const TileWalk walk = tile_walk(a, m_tiles, a.tile_expert, CUTS ? 2 : 1);
+    auto tile_at = [&](int pos, int &n_tile, int &m_tile) __attribute__((always_inline)) -> bool {
+        if (pos >= walk.whole) return false;
+        tile_of_slot(a, walk, pos < 0 ? walk.whole + (walk.wg >> walk.cut) : pos, n_tile, m_tile);
         n_tile = __builtin_amdgcn_readfirstlane(n_tile);
         m_tile = __builtin_amdgcn_readfirstlane(m_tile);
-        return slot;
+        return true;
+    };
+    auto column_works = [&](int pos, int column) __attribute__((always_inline)) -> bool {
+        return !CUTS || pos >= 0 || column / 2 == walk.part;
     };
     auto phase_barrier = [&]() __attribute__((always_inline)) {
         __builtin_amdgcn_sched_barrier(0);
@@ -118,14 +124,22 @@ __global__ __launch_bounds__(512, 1) void moe_fp8_pingpong_kernel(GemmArgs a, Fp
         uint32_t w_lane;         // lane * 16, or 0 past the last tile
         uint32_t w_second, s_second;  // from the first eight row blocks, and their scale row, to the other eight
     };
-    auto weights_of = [&](int n_tile, int e) __attribute__((always_inline)) {
+    auto weights_of = [&](int pos, int n_tile, int e) __attribute__((always_inline)) {
         TileSrc s;
         s.w = f.wq + (size_t)e * f.expert_stride + (size_t)(n_tile * (FEAT / 16) + (wave >> 1)) * (size_t)(KT * 2048) +
               (size_t)((wave & 1) * 1024);
         s.ws = f.wscale + (size_t)e * f.wscale_expert_stride + (size_t)(n_tile * (FEAT / 128)) * (size_t)f.w_stride;
         s.w_lane = (uint32_t)lane * 16u;
         // stage 1: the up rows; stage 2: the tile's other 128 features, or the same ones again where a last tile has none
-        const bool second = STAGE == 1 || n_tile * FEAT + 128 < a.F;
+        // or, of a cut tile, where a workgroup has 128 of them
+        bool second = STAGE == 1 || n_tile * FEAT + 128 < a.F;
+        if (CUTS && pos < 0) {
+            if (walk.part && second) {
+                s.w += (size_t)KT * (8 * 2048);
+                s.ws += f.w_stride;
+            }
+            second = false;
+        }
         s.w_second = STAGE == 1 ? f.up_offset : second ? (uint32_t)KT * (8u * 2048u) : 0u;
         s.s_second = STAGE == 1 ? f.wscale_up_offset : second ? (uint32_t)f.w_stride : 0u;
         return s;
@@ -264,10 +278,14 @@ __global__ __launch_bounds__(512, 1) void moe_fp8_pingpong_kernel(GemmArgs a, Fp
     };
 
     int n_tile, m_tile;
-    int id = next_tile((int)blockIdx.x >> 3, n_tile, m_tile);
-    if (id < 0) return;
+    auto opaque = [](int v) __attribute__((always_inline)) -> int {
+        asm volatile("" : "+s"(v));
+        return v;
+    };
+    int pos = opaque(walk_first(walk));
+    if (!tile_at(pos, n_tile, m_tile)) return;
     int rows = load_uniform_i32(a.tile_rows + m_tile);
-    TileSrc src = weights_of(n_tile, load_uniform_i32(a.tile_expert + m_tile));
+    TileSrc src = weights_of(pos, n_tile, load_uniform_i32(a.tile_expert + m_tile));
     int src_m = m_tile;       // tile the weight and scale loads are in
     uint32_t srow = 0;
     {
@@ -315,14 +333,14 @@ __global__ __launch_bounds__(512, 1) void moe_fp8_pingpong_kernel(GemmArgs a, Fp
     while (true) {
         // the following tile of this workgroup, whose first slices are loaded while this one finishes
         int n_next = n_tile, m_next = m_tile;
-        const int id_next = next_tile(id + ((int)gridDim.x >> 3), n_next, m_next);
-        const bool has_next = id_next >= 0;
+        const int pos_next = opaque(walk_next(walk, pos));
+        const bool has_next = tile_at(pos_next, n_next, m_next);
         if (!has_next) {
             n_next = n_tile;
             m_next = m_tile;
         }
         const int rows_next = has_next ? load_uniform_i32(a.tile_rows + m_next) : 0;
-        TileSrc src_next = weights_of(n_next, load_uniform_i32(a.tile_expert + m_next));
+        TileSrc src_next = weights_of(pos_next, n_next, load_uniform_i32(a.tile_expert + m_next));
         if (!has_next) src_next.w_lane = 0;
         uint32_t xoff_n[NH][2] = {}, srow_n = 0;
         if (STAGE == 1) {
@@ -468,7 +486,7 @@ __global__ __launch_bounds__(512, 1) void moe_fp8_pingpong_kernel(GemmArgs a, Fp
                     if (wn == 0 && eq == 0) f.as_out[(size_t)(m_tile * BM + blk * 16 + er) * (size_t)f.as_stride + n_tile] = (uint8_t)b;
                 }
             }
-        } else {
+        } else if (n_tile * FEAT + wn * 64 < a.F && column_works(pos, wn)) {  // (not the empty half of a last tile, nor what others have of a cut one)
             const int *pairs = reinterpret_cast<const int *>(lds_slot + slot_cur * PT::SLOT_BYTES);
             const float *wgts = reinterpret_cast<const float *>(pairs + BM);
             const int f0 = n_tile * FEAT + wn * 64;
@@ -476,7 +494,7 @@ __global__ __launch_bounds__(512, 1) void moe_fp8_pingpong_kernel(GemmArgs a, Fp
             char *stg = lds_e + wave * (SR * 128);
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
-                if ((nb & 3) >= nbh[nb >> 2] || f0 >= a.F) continue;  // (f0: the empty half of a last tile)
+                if ((nb & 3) >= nbh[nb >> 2]) continue;
                 const int row0 = (nb >> 2) * 128 + ((nb & 3) * 2 + wm) * 16;
                 const float wgt = wgts[row0 + er];
                 if (a.y_bf16) {
@@ -510,7 +528,7 @@ __global__ __launch_bounds__(512, 1) void moe_fp8_pingpong_kernel(GemmArgs a, Fp
             }
         }
         if (!has_next) break;
-        id = id_next;
+        pos = pos_next;
         n_tile = n_next;
         m_tile = m_next;
         rows = rows_next;

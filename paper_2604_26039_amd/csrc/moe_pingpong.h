@@ -125,22 +125,34 @@ __global__ __launch_bounds__(512, 1) void moe_pingpong_kernel(GemmArgs a)
     const int group = wave >> 2;
     const int K = a.K, KST = K / 32, KT = K / BK;
     const int r16 = lane & 15, q = lane >> 4;
-    const int m_tiles = a.meta[1];
+    const int m_tiles = load_uniform_i32(a.meta + 1);
 
-    // Tiles of this workgroup: slots blockIdx.x / 8, + gridDim.x / 8, ... of its XCD's walk (gridDim.x is a multiple of 8).
-    const TileWalk walk = tile_walk(a, m_tiles, a.tile_expert);
-    auto next_tile = [&](int slot, int &n_tile, int &m_tile) __attribute__((always_inline)) -> int {
-        if (slot >= walk.total) return -1;
-        tile_of_slot(a, walk, slot, n_tile, m_tile);
+    // Tiles of this workgroup: its part of a cut tile, then slots blockIdx.x / 8, + gridDim.x / 8, ... of its XCD's walk (gridDim.x
+    // is a multiple of 8).  False when there are no more.
+    const TileWalk walk = tile_walk(a, m_tiles, a.tile_expert, WN);
+    auto tile_at = [&](int pos, int &n_tile, int &m_tile) __attribute__((always_inline)) -> bool {
+        if (pos >= walk.whole) return false;
+        tile_of_slot(a, walk, pos < 0 ? walk.whole + (walk.wg >> walk.cut) : pos, n_tile, m_tile);
         // wave-uniform by construction; saying so lets the per-tile table reads below be scalar loads, which do not
         // count on vmcnt (a vector load would have to be waited for in order, behind every LDS-direct load in flight)
         n_tile = __builtin_amdgcn_readfirstlane(n_tile);
         m_tile = __builtin_amdgcn_readfirstlane(m_tile);
-        return slot;
+        return true;
+    };
+    // Columns of wavefronts that work on a tile: all WN, or of a cut tile WN >> cut of them.  The others do as the rest do, with
+    // whatever lies in LDS, and store nothing (they are alone on their SIMDs: a condition on their products would cost the tile loop
+    // its registers and gain nothing); loads of weights that nobody needs fetch 16 bytes of a line that somebody does.
+    auto column_works = [&](int pos, int column) __attribute__((always_inline)) -> bool {
+        return pos >= 0 || (column << walk.cut) / WN == walk.part;
+    };
+    // opaque: the compiler would otherwise make a copy of the tile loop for the first tile, and spill across both
+    auto opaque = [](int v) __attribute__((always_inline)) -> int {
+        asm volatile("" : "+s"(v));
+        return v;
     };
 
     // ---- global element offsets of this lane's loads for k-slice 0 of a tile ----
-    auto tile_offsets = [&](int n_tile, int m_tile, uint32_t *xo, uint32_t *wo, const uint16_t *&wexp, int &rows) __attribute__((always_inline)) {
+    auto tile_offsets = [&](int pos, int n_tile, int m_tile, uint32_t *xo, uint32_t *wo, const uint16_t *&wexp, int &rows) __attribute__((always_inline)) {
         // the two per-tile table entries (written by the align launch before this one) through the constant address
         // space: m_tile is wave-uniform, so these become scalar loads, which do not count on vmcnt
         rows = load_uniform_i32(a.tile_rows + m_tile);  // real rows of the tile (they come first, the sentinel padding after them)
@@ -167,7 +179,10 @@ __global__ __launch_bounds__(512, 1) void moe_pingpong_kernel(GemmArgs a)
 #pragma unroll
         for (int s = 0; s < WSLOTS; ++s) {
             const int widx = wave + s * NWAVE;
-            const int rb = widx / KS, ks = widx % KS;
+            const int ks = widx % KS;
+            int rb = widx / KS;
+            const bool works = column_works(pos, (STAGE == 1 ? rb % (TT::RB / 2) : rb) / FB);
+            if (!works) rb = walk.part * (WN >> walk.cut) * FB;
             uint32_t base;
             if (STAGE == 1) {
                 const int half = TT::RB / 2;
@@ -177,7 +192,7 @@ __global__ __launch_bounds__(512, 1) void moe_pingpong_kernel(GemmArgs a)
                 const int rbx = f0 + rb * 16 < a.F ? rb : rb - TT::RB / 2;  // past the features of half a last tile
                 base = (uint32_t)(f0 / 16 + rbx) * (uint32_t)KST * kFragElems;
             }
-            wo[s] = base + (uint32_t)ks * kFragElems + (uint32_t)lane * 8;
+            wo[s] = base + (uint32_t)ks * kFragElems + (works ? (uint32_t)lane * 8 : 0u);
         }
     };
     // pair indices (as loaded by tile_offsets) -> element offsets of the token rows (token = pair / k by multiplication)
@@ -351,10 +366,10 @@ __global__ __launch_bounds__(512, 1) void moe_pingpong_kernel(GemmArgs a)
     };
 
     int n_tile, m_tile;
-    int id = next_tile((int)blockIdx.x >> 3, n_tile, m_tile);
-    if (id < 0) return;
+    int pos = opaque(walk_first(walk));
+    if (!tile_at(pos, n_tile, m_tile)) return;
     int rows_cur = 0, rows_next = 0;
-    tile_offsets(n_tile, m_tile, xoff, woff, wexp_w, rows_cur);
+    tile_offsets(pos, n_tile, m_tile, xoff, woff, wexp_w, rows_cur);
     token_offsets(xoff);
     nb_valid = blocks_valid(rows_cur);
     tail_n = tail_blocks(rows_cur);
@@ -398,10 +413,10 @@ __global__ __launch_bounds__(512, 1) void moe_pingpong_kernel(GemmArgs a)
     while (true) {
         // following tile of this workgroup (its first slices are loaded while this one finishes)
         int n_next = 0, m_next = 0;
-        const int id_next = next_tile(id + ((int)gridDim.x >> 3), n_next, m_next);
-        const bool has_next = id_next >= 0;
+        const int pos_next = opaque(walk_next(walk, pos));
+        const bool has_next = tile_at(pos_next, n_next, m_next);
         if (has_next) {
-            tile_offsets(n_next, m_next, xoff_n, woff_n, wexp_n, rows_next);
+            tile_offsets(pos_next, n_next, m_next, xoff_n, woff_n, wexp_n, rows_next);
             txv_n = token_loads(rows_next);
         }
         // stage 2: destination pair and router weight of this lane's token rows
@@ -547,7 +562,8 @@ __global__ __launch_bounds__(512, 1) void moe_pingpong_kernel(GemmArgs a)
             }
             slot_par ^= 1;
         }
-        const bool no_features = STAGE == 2 && f0 + wn * (FB * 16) >= a.F;  // the empty half of a last tile
+        // the empty half of a last tile, a column of wavefronts without a part in a cut one
+        const bool no_features = (STAGE == 2 && f0 + wn * (FB * 16) >= a.F) || !column_works(pos, wn);
         if (no_features) {
         } else if (STAGE == 2 && a.y_bf16) {
             // bf16 per-pair rows leave through LDS: a lane holds 16 consecutive features of one token, but a store
@@ -609,7 +625,7 @@ __global__ __launch_bounds__(512, 1) void moe_pingpong_kernel(GemmArgs a)
                 store_token_row<2, 2>(a, &acc_t[2 * t], &acc_t[2 * t], 1, (size_t)tail_pair[t] * a.F, f0 / 16 + wn * FB + 2 * wm, q, tail_wgt[t]);
         }
         if (!has_next) break;
-        id = id_next;
+        pos = pos_next;
         n_tile = n_next;
         m_tile = m_next;
         rows_cur = rows_next;

@@ -133,10 +133,16 @@ struct GemmArgs {
     int group_m_req;            // GROUP_M of the configuration (mode bits 12-15): M-tiles per XCD block, 0 = automatic
     int group_m, group_n;       // M-tiles x N-tiles per XCD block of the workgroup->tile map (set by the launcher)
     int total_tiles;            // persistent kernels: tile ids to walk (set by the launcher)
+    int blocks_n;               // n_tiles / group_n
+    // their divisors as multipliers (div_magic, set by the launcher): group_m * group_n, group_m, n_tiles, blocks_n
+    unsigned long long block_magic, gm_magic, n_magic, bn_magic;
     int a_row_major;            // stage 1: A is written row-major [slot, I] instead of fragment-major (FP8 path)
     const int32_t *pred;        // device-side predicate: the launch does nothing unless *pred == pred_value (NULL: always runs)
     int pred_value;
 };
+// x / d as (x * ceil(2^40 / d)) >> 40: exact for x * d < 2^40, x < 2^24.  Of wave-uniform values it stays in scalar registers.
+constexpr unsigned long long div_magic(int d) { return ((1ull << 40) + (unsigned)d - 1) / (unsigned)d; }
+__device__ __forceinline__ int div_by(int x, unsigned long long magic) { return (int)(((unsigned long long)(unsigned)x * magic) >> 40); }
 // True when a predicated launch is not the one selected on the device.
 __device__ __forceinline__ bool launch_deselected(const int32_t *pred, int pred_value)
 {
