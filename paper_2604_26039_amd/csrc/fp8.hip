@@ -174,12 +174,15 @@ __global__ __launch_bounds__(WM *WN * 64) void moe_fp8_kernel(GemmArgs a, Fp8Arg
     if (launch_deselected(a.pred, a.pred_value)) return;
     int n_tile, m_tile;
     tile_of_workgroup(a, n_tile, m_tile);
-    if (m_tile >= a.meta[1]) return;
+    if (m_tile >= a.m_tiles_cap) return;  // overlaunched grid
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave / WN, wn = wave % WN;
-    const int e = a.tile_expert[m_tile];
+    m_tile = __builtin_amdgcn_readfirstlane(m_tile);
+    const int e = load_uniform_i32(a.tile_expert + m_tile);  // -1: past the real tiles (one round trip for both, as in moe_gemm_kernel)
+    const int rows = load_uniform_i32(a.tile_rows + m_tile);
+    if (e < 0) return;
     const int K = a.K, KT = K / kGroup;
     const int f0 = n_tile * FEAT_PER_TILE;
     const uint8_t *wexp = f.wq + (size_t)e * f.expert_stride;
@@ -233,13 +236,8 @@ __global__ __launch_bounds__(WM *WN * 64) void moe_fp8_kernel(GemmArgs a, Fp8Arg
         }
     };
 
-    int nb_valid = 0;
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        const int tr0 = (wm * NB + nb) * 16;
-        if (tr0 < BM && a.sorted[m_tile * BM + tr0] < a.P) nb_valid = nb + 1;
-    }
-    nb_valid = __builtin_amdgcn_readfirstlane(nb_valid);
+    int nb_valid = (rows + 15) / 16 - wm * NB;
+    nb_valid = nb_valid < 0 ? 0 : nb_valid > NB ? NB : nb_valid;
 
     // ---- scale bytes, four k-blocks per 32-bit load (scale rows are padded to multiples of four bytes).
     // Tokens: one row of scale bytes per lane and token block; weights: one row per scale block of the wavefront's
@@ -275,7 +273,6 @@ __global__ __launch_bounds__(WM *WN * 64) void moe_fp8_kernel(GemmArgs a, Fp8Arg
         for (int nb = 0; nb < NB; ++nb) {
             const int tr = (wm * NB + nb) * 16 + r16;
             out_pair[nb] = (tr < BM && nb < nb_valid) ? a.sorted[m_tile * BM + tr] : a.P;
-            out_wgt[nb] = (out_pair[nb] < a.P) ? a.topk_w[out_pair[nb]] : 0.0f;
         }
     }
 
@@ -314,6 +311,10 @@ __global__ __launch_bounds__(WM *WN * 64) void moe_fp8_kernel(GemmArgs a, Fp8Arg
 #pragma unroll
     for (int s = 0; s < NSTAGE - 1; ++s)
         if (s < KT) issue_slice(s);
+    if (STAGE == 2) {  // behind the first slices, which would otherwise wait for the pairs
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) out_wgt[nb] = (out_pair[nb] < a.P) ? a.topk_w[out_pair[nb]] : 0.0f;
+    }
 
     int buf_cur = 0, buf_issue = NSTAGE - 1;
     for (int kt = 0; kt < KT; ++kt) {

@@ -753,8 +753,9 @@ extern "C" int ramp_fused_moe_selected(const ramp_shape *shape, int n_cand, cons
         streams.c[c].shape = !shared_align || runs_two_launches(*ki[c], s) ? -1 : stream_selected_shape(cfgs[c]);
         if (streams.c[c].shape < 0) continue;
         const Workspace w = workspace_layout(s, cfgs[c]);
-        streams.c[c] = StreamChoice{streams.c[c].shape, cfgs[c].bn, w.sorted, w.tile_expert, w.meta, w.a_buf};
-        const size_t m_tiles = w.cap / (size_t)cfgs[c].bm, per_block = stream_selected_per_block(cfgs[c].waves);
+        const size_t m_tiles = w.cap / (size_t)cfgs[c].bm;
+        streams.c[c] = StreamChoice{streams.c[c].shape, cfgs[c].bn, (int32_t)m_tiles, w.sorted, w.tile_expert, w.a_buf};
+        const size_t per_block = stream_selected_per_block(cfgs[c].waves);
         const size_t tiles[2] = {m_tiles * (size_t)(2 * s.I / cfgs[c].bn), m_tiles * (size_t)(s.H / cfgs[c].bn)};
         for (int st2 = 0; st2 < 2; ++st2) {
             const unsigned blocks = (unsigned)((tiles[st2] + per_block - 1) / per_block);

@@ -187,17 +187,23 @@ __global__ __launch_bounds__(WF *WK * 64) void moe_fp8_stream_kernel(GemmArgs a,
     constexpr int NB = ST::NB;
     __shared__ __attribute__((aligned(16))) float red[ST::RED_FLOATS > 0 ? ST::RED_FLOATS : 4];
     const int n_tile = blockIdx.x % a.n_tiles, m_tile = blockIdx.x / a.n_tiles;
-    if (m_tile >= a.meta[1]) return;
     const int lane = threadIdx.x & 63, r16 = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int e = __builtin_amdgcn_readfirstlane(a.tile_expert[m_tile]);
     int pair_of[NB];
     uint32_t act_row[NB];
+    // rows and expert on their way together; -1: past the real tiles (as in moe_stream_kernel)
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        const int tr = nb * 16 + r16;
+        pair_of[nb] = a.sorted[m_tile * BM + (tr < BM ? tr : BM - 1)];
+    }
+    const int e = load_uniform_i32(a.tile_expert + m_tile);
+    if (e < 0) return;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
         const int tr = nb * 16 + r16;
         const int slot = m_tile * BM + (tr < BM ? tr : BM - 1);
-        const int pair = a.sorted[slot];
+        const int pair = pair_of[nb];
         pair_of[nb] = tr < BM ? pair : a.P;
         act_row[nb] = (STAGE == 1) ? (uint32_t)(((unsigned long long)(uint32_t)pair * a.topk_magic) >> 40) : (uint32_t)slot;
     }

@@ -364,12 +364,17 @@ __global__ __launch_bounds__(WM *WN * 64, (TileTraits<BM, BN, BK, WM, WN, NSTAGE
     if (launch_deselected(a.pred, a.pred_value)) return;
     int n_tile, m_tile;
     tile_of_workgroup(a, n_tile, m_tile);
-    if (m_tile >= a.meta[1]) return;  // overlaunched grid: surplus workgroups leave at once
+    if (m_tile >= a.m_tiles_cap) return;  // overlaunched grid: whole rounds of the map
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave / WN, wn = wave % WN;
-    const int e = a.tile_expert[m_tile];
+    m_tile = __builtin_amdgcn_readfirstlane(m_tile);
+    // Expert and real rows of the tile in two scalar loads at once (-1: past the real tiles), instead of the number of tiles, the
+    // expert and the first slot of every token block in turn: round trips in front of the first weights.
+    const int e = load_uniform_i32(a.tile_expert + m_tile);
+    const int rows = load_uniform_i32(a.tile_rows + m_tile);
+    if (e < 0) return;
     const int K = a.K, KST = K / 32;
     const int f0 = n_tile * FEAT_PER_TILE;
     const uint16_t *wexp = a.wpacked + (size_t)e * a.expert_stride;
@@ -429,16 +434,11 @@ __global__ __launch_bounds__(WM *WN * 64, (TileTraits<BM, BN, BK, WM, WN, NSTAGE
     // Padding sits at the end of a tile, so this wavefront's token blocks are real up to some
     // block and sentinel-only after it: the products of all-padding blocks are skipped (the ragged
     // last tile of an expert then costs its loads but only the MFMAs of its real rows).
-    int nb_valid = 0;
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        const int tr0 = (wm * NB + nb) * 16;
-        if (tr0 < BM && a.sorted[m_tile * BM + tr0] < a.P) nb_valid = nb + 1;
-    }
-    nb_valid = __builtin_amdgcn_readfirstlane(nb_valid);
+    int nb_valid = (rows + 15) / 16 - wm * NB;
+    nb_valid = nb_valid < 0 ? 0 : nb_valid > NB ? NB : nb_valid;
 
     // stage 2: destination pair and router weight of this lane's token rows, fetched now so the
-    // epilogue does not end on two dependent global loads
+    // epilogue does not end on two dependent global loads; the weights behind the first slices, so that these don't wait for the pairs
     int out_pair[NB];
     float out_wgt[NB];
     if (STAGE == 2) {
@@ -446,9 +446,13 @@ __global__ __launch_bounds__(WM *WN * 64, (TileTraits<BM, BN, BK, WM, WN, NSTAGE
         for (int nb = 0; nb < NB; ++nb) {
             const int tr = (wm * NB + nb) * 16 + r16;
             out_pair[nb] = (tr < BM && nb < nb_valid) ? a.sorted[m_tile * BM + tr] : a.P;
-            out_wgt[nb] = (out_pair[nb] < a.P) ? a.topk_w[out_pair[nb]] : 0.0f;
         }
     }
+    auto load_pair_weights = [&]() __attribute__((always_inline)) {
+        if (STAGE != 2) return;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) out_wgt[nb] = (out_pair[nb] < a.P) ? a.topk_w[out_pair[nb]] : 0.0f;
+    };
 
     auto compute_slice = [&](int buf) {
         const uint16_t *xs = &lds[buf * TT::BUF_ELEMS + lane * 8];
@@ -516,6 +520,7 @@ __global__ __launch_bounds__(WM *WN * 64, (TileTraits<BM, BN, BK, WM, WN, NSTAGE
 #pragma unroll
         for (int s = 0; s < NSTAGE; ++s)
             if (s < KT) issue_slice(s);
+        load_pair_weights();
         wait_for_next(min(NSTAGE - 1, KT - 1));
         __builtin_amdgcn_s_barrier();
         read_frags(0, 0, 0);
@@ -544,6 +549,7 @@ __global__ __launch_bounds__(WM *WN * 64, (TileTraits<BM, BN, BK, WM, WN, NSTAGE
 #pragma unroll
     for (int s = 0; s < NSTAGE - 1; ++s)
         if (s < KT) issue_slice(s);
+    load_pair_weights();  // (younger than the slices: the waits below, counted in slices, can only be stricter for them)
 
     int buf_cur = 0, buf_issue = NSTAGE - 1;
     for (int kt = 0; kt < KT; ++kt) {

@@ -42,7 +42,16 @@ __device__ __forceinline__ void stream_tile(const GemmArgs &a, float *red, int n
 
     const int wf = wave % WF, wk = wave / WF;
     const int r16 = lane & 15, q = lane >> 4;
-    const int e = a.tile_expert[m_tile];
+    // The tile's rows and its expert are on their way together, and a tile past the real ones (the grid is an upper bound) is told by its
+    // expert, -1: a round trip less in front of the weights than with the number of tiles, the expert and the rows in turn.
+    int pair_of[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        const int tr = nb * 16 + r16;
+        pair_of[nb] = a.sorted[m_tile * BM + (tr < BM ? tr : BM - 1)];
+    }
+    const int e = load_uniform_i32(a.tile_expert + m_tile);
+    if (e < 0) return;
     const int K = a.K, KST = K / 32;
     const int f0 = n_tile * FEAT_PER_TILE + wf * FPW * 16;  // first output feature of this wavefront
     const uint16_t *wexp = a.wpacked + (size_t)e * a.expert_stride;
@@ -54,14 +63,13 @@ __device__ __forceinline__ void stream_tile(const GemmArgs &a, float *red, int n
 
     // activation row offsets (elements), one per token block
     uint32_t xoff[NB];
-    int pair_of[NB];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
         int tr = nb * 16 + r16;
         const bool live = tr < BM;
         if (!live) tr = BM - 1;
         const int slot = m_tile * BM + tr;
-        const int pair = a.sorted[slot];
+        const int pair = pair_of[nb];
         pair_of[nb] = live ? pair : a.P;
         if (STAGE == 1) xoff[nb] = ((pair < a.P) ? (uint32_t)(pair / a.topk) : 0u) * (uint32_t)K + (uint32_t)(q * 8);
         else xoff[nb] = act_elem((uint32_t)slot, (uint32_t)(q * 8), (uint32_t)KST);  // fragment-major, written by stage 1
@@ -174,7 +182,6 @@ __global__ __launch_bounds__(WF *WK * 64) void moe_stream_kernel(GemmArgs a)
     if (launch_deselected(a.pred, a.pred_value)) return;
     const int n_tile = blockIdx.x % a.n_tiles;
     const int m_tile = blockIdx.x / a.n_tiles;
-    if (m_tile >= a.meta[1]) return;
     stream_tile<STAGE, BM, FBW, WF, WK, U>(a, red, n_tile, m_tile, threadIdx.x >> 6, threadIdx.x & 63);
 }
 

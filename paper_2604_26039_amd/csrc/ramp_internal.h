@@ -194,8 +194,8 @@ inline void xcd_block_shape(int n_tiles, int group_m_req, int *group_m, int *gro
 // The stream candidates of a device-selected call, for one launch per projection (moe_stream_selected.hip): the position of a
 // candidate's tile in RAMP_STREAM_SELECTED_GROUP, or -1, and what differs between the candidates' arguments (byte offsets).
 struct StreamChoice {
-    int32_t shape, bn;
-    size_t sorted, tile_expert, meta, a_buf;
+    int32_t shape, bn, m_tiles_cap;
+    size_t sorted, tile_expert, a_buf;
 };
 struct StreamChoices {
     StreamChoice c[kMaxCandidates];

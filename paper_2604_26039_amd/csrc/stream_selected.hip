@@ -38,18 +38,16 @@ __global__ __launch_bounds__(512, 4) void moe_stream_selected_kernel(GemmArgs a,
     if (c.shape < 0) return;
     a.sorted = reinterpret_cast<const int32_t *>(base + c.sorted);
     a.tile_expert = reinterpret_cast<const int32_t *>(base + c.tile_expert);
-    a.meta = reinterpret_cast<const int32_t *>(base + c.meta);
     a.n_tiles = features / c.bn;
     uint16_t *act = reinterpret_cast<uint16_t *>(base + c.a_buf);
     if (STAGE == 1) a.a_out = act;
     else a.act = act;
-    const int m_tiles = a.meta[1];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     auto run = [&](auto tile, int waves, int red_floats) __attribute__((always_inline)) {
         const int part = wave / waves;  // workgroup of the block
         const int id = (int)blockIdx.x * (8 / waves) + part;
         const int m_tile = id / a.n_tiles, n_tile = id - m_tile * a.n_tiles;
-        if (m_tile >= m_tiles) return;
+        if (m_tile >= c.m_tiles_cap) return;  // (the grid is the largest candidate's)
         tile(red + part * red_floats, n_tile, m_tile, wave - part * waves);
     };
     switch (c.shape) {
