@@ -798,19 +798,12 @@ extern "C" int ramp_fused_moe_fp8(const ramp_shape *shape, const ramp_config *cf
     AlignSlotWeights sw = {nullptr, nullptr};
     if (k->launch_pp) sw = AlignSlotWeights{topk_w, reinterpret_cast<float *>(base + w.slot_w)};
     const QuantRows qx = {static_cast<const uint16_t *>(X), s.T, s.H, xq, xs, w.xs_stride};
-    if (align_is_one_launch(s.T, s.k)) {
-        // neither needs the other's result: one launch as long as the align is one (past that the align is two, and the hidden
-        // state large enough that a launch more is under a hundredth of the layer).  Up to 64 pairs too, where an align of its own is
-        // one wavefront: 0.3 to 2 us shorter than the two launches at T = 1 to 32 of four shapes (OLMoE-shaped T = 8, 128-row
-        // persistent tile 70.9 against 72.8 us)
-        if (int rc = launch_align_quant(topk_ids, s.T, s.k, s.E, cfg->bm, sorted, tile_expert, tile_rows, counts, meta, sw, qx, st))
-            return rc;
-    } else {
-        if (int rc = launch_align(topk_ids, s.T, s.k, s.E, cfg->bm, sorted, tile_expert, tile_rows, counts, meta, base + w.align_ws,
-                                  w.align_ws_bytes, st, nullptr, 0, sw))
-            return rc;
-        if (int rc = launch_quant_rows(qx, nullptr, st)) return rc;
-    }
+    // Neither the align nor the codes of the hidden state need the other's result: the quantiser goes along with the align launch, or
+    // with the second of two.  Up to 64 pairs too, where an align of its own is one wavefront: 0.3 to 2 us shorter than two
+    // launches at T = 1 to 32 of four shapes (OLMoE-shaped T = 8, 128-row persistent tile 70.9 against 72.8 us).
+    if (int rc = launch_align_quant(topk_ids, s.T, s.k, s.E, cfg->bm, sorted, tile_expert, tile_rows, counts, meta, base + w.align_ws,
+                                    w.align_ws_bytes, sw, qx, st))
+        return rc;
 
     if (k->launch_pp) {
         g.slot_w = sw.slot_w;

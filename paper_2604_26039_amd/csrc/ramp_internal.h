@@ -69,9 +69,11 @@ struct QuantRows {
     uint8_t *codes, *sb;
     int stride;  // scale bytes per row
 };
-// Align of 1 .. kAlignOneLaunchMaxP pairs and, by the other workgroups of the same launch, the quantised hidden state.
+// Align of at least one pair and, by other workgroups of its only or its second launch, the quantised hidden state.  (A call of at
+// most 64 pairs too takes the form of one launch.)
 int launch_align_quant(const int32_t *ids, int T, int k, int E, int bm, int32_t *sorted, int32_t *tile_expert, int32_t *tile_rows,
-                       int32_t *counts, int32_t *meta, AlignSlotWeights slot_weights, const QuantRows &q, hipStream_t stream);
+                       int32_t *counts, int32_t *meta, void *ws, size_t ws_bytes, AlignSlotWeights slot_weights, const QuantRows &q,
+                       hipStream_t stream);
 
 // ---- packed weights ----
 // 16 bytes of bf16 values at the alignment of one value: the caller's weights and rows to quantise may start anywhere
