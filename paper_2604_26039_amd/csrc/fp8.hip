@@ -423,7 +423,7 @@ Fp8Kernel make_fp8_stream()
 }
 
 // The weight-streaming tiles: X(bm, FBW, WF, WK, U), bn = 16 * FBW * WF; those of RAMP_FP8_DECODE_CONFIGS run calls of at most
-// 64 pairs (k up to 16) in two launches.  Measured and left out, never the fastest of 21 batches of the five shapes of the
+// 64 pairs in two launches (decode_in_two_launches).  Measured and left out, never the fastest of 21 batches of the five shapes of the
 // tests: bm 8, 32-row tiles of two weight blocks, U = 2 with WK = 4.
 #define RAMP_FP8_STREAM_CONFIGS(X) \
     X(16, 2, 1, 4, 1)              \
@@ -764,7 +764,7 @@ extern "C" int ramp_fused_moe_fp8(const ramp_shape *shape, const ramp_config *cf
         g.K = s.H;
         g.F = s.I;
         g.n_tiles = 2 * s.I / cfg->bn;
-        if (k->launch_decode_up && decode_in_two_launches(s.T, s.k)) {
+        if (k->launch_decode_up && decode_in_two_launches(s)) {
             const DecodeArgs da = {topk_ids, s.E, cfg->bm, (int)w.cap, sorted, tile_expert, tile_rows, counts, meta};
             k->launch_decode_up(g, up, da, st);
             if (int rc = check_launch("moe_fp8_decode_up_kernel")) return rc;

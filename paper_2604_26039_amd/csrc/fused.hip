@@ -455,7 +455,7 @@ bool pair_rows_bf16(const ramp_shape &s)
 
 bool runs_two_launches(const KernelInfo &ki, const ramp_shape &s)
 {
-    return ki.launch_decode_up && decode_in_two_launches(s.T, s.k);
+    return ki.launch_decode_up && decode_in_two_launches(s);
 }
 
 // align(bm) + both projections of one configuration; `base` holds every workspace section but the per-pair rows,

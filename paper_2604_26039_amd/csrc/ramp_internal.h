@@ -311,10 +311,16 @@ __device__ __forceinline__ float sum_of_pairs(int WK, const PairWeights &p, Part
 }
 constexpr int kDecodeMaxPairs = 64;
 // The two-launch form takes calls of at most 64 pairs whose tokens have at most 16: one wavefront or more of its down-projection
-// to a pair.  One token of a layer with H = 1152, I = 896, k = 6, whose 16 wavefronts are 6 x 2 and four idle ones, against
-// align, two projections and combine: bf16 23.2 -> 18.5 us, FP8 20.6 -> 16.4 us (two
-// tokens 28.9 -> 24.7, 23.0 -> 18.9; from four on within 10 % either way, the configuration without the form is there too).
-inline bool decode_in_two_launches(int T, int k) { return k <= 16 && (long long)T * k <= kDecodeMaxPairs; }
+// to a pair.  Where k does not divide 16 some of the 16 wavefronts are idle, and every pair reads its expert's weights for itself where the
+// general form reads them once per expert: it is the faster one while the down-projection's H / 16 * T workgroups fit on the units at
+// once, and loses past that (both builds, all decode configurations, twelve layers of H = 1024 ... 7168 and k = 3 ... 15, with 16 to 64
+// experts and with every token at all k of them): T * H <= 4096 0.57 to 0.99 of the general form's time (H = 1152, I = 896, k = 6, one
+// token bf16 18.9 -> 14.1 us, FP8 17.6 -> 13.8), above it up to 1.7 of it (k = 6, T = 10 27.6 -> 39.1; H = 4096, E = 16, k = 5,
+// T = 12 1.5 of it).
+inline bool decode_in_two_launches(const ramp_shape &s)
+{
+    return s.k <= 16 && (long long)s.T * s.k <= kDecodeMaxPairs && (16 % s.k == 0 || (long long)s.T * s.H <= 16 * kNumCU);
+}
 // Wavefronts that share the reduction of one pair: the largest power of two that k pairs leave of 16.
 __device__ __forceinline__ int decode_pair_waves(int k)
 {
