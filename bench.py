@@ -67,7 +67,8 @@ def geomean(v):
 
 
 def kernel_name(cfg):
-    fam = "moe_pingpong_kernel<1>" if cfg.mode & 0x400 else "moe_stream_kernel<1>" if cfg.mode & 0x100 else "moe_gemm_kernel<1>"
+    from paper_2604_26039_amd import ramp
+    fam = "moe_pingpong_kernel<1>" if cfg.mode & ramp.PERSISTENT else "moe_stream_kernel<1>" if cfg.mode & 0x100 else "moe_gemm_kernel<1>"
     return fam + " (up-projection + SwiGLU)"
 
 

@@ -64,7 +64,10 @@ typedef struct {
  *          bk is then the k-extent of one register load batch); 0x200 = LDS-staged path with
  *          the register-pipelined main loop; 0x400 = persistent ping-pong kernel for the
  *          large tiles (one workgroup per compute unit walks its share of the tiles, two
- *          groups of four wavefronts alternate memory and MFMA phases); bits 12-15 = v > 0: GROUP_M
+ *          groups of four wavefronts alternate memory and MFMA phases); 0x20000 in place of 0x400 = the
+ *          same kernel for H = 256 * n + 128, whose down-projection's last tile is half full;
+ *          with 0x100, 0x2000 = small calls of at most 64 pairs in two launches; bits 12-15 of a
+ *          persistent tile = v > 0: GROUP_M
  *          mode (Sec. 4.1, Eq. 4) in its XCD-aware form: the workgroups of one XCD (one L2) take
  *          blocks of 2^v M-tiles x about 32/2^v N-tiles, so the M-tiles of a block share the weight
  *          slices of a few N-tiles in L2; v = 0: a block spans all N-tiles and the token rows of its
@@ -80,7 +83,7 @@ const char *ramp_last_error(void);
 
 /* Number of configurations that are valid for this shape under gfx950 limits
  * (LDS 160 KB per CU, register budget, MFMA 16x16x32 alignment, H % 128 == 0,
- * I % 128 == 0, tile widths dividing 2*I and H).  Host only. */
+ * I % 128 == 0, tile widths dividing 2*I and H, or with mode bit 0x20000 leaving half a tile of H).  Host only. */
 int ramp_num_configs(const ramp_shape *shape);
 /* idx-th valid configuration, 0 <= idx < ramp_num_configs(). */
 int ramp_get_config(const ramp_shape *shape, int idx, ramp_config *out);
@@ -176,8 +179,8 @@ int ramp_fused_moe_workspace_layout(const ramp_shape *shape, const ramp_config *
  * accumulation is fp32 in the matrix pipe (v_mfma_scale_f32_16x16x128_f8f6f4, which applies the block scales).
  * ramp_fp8_pack_weights quantises bf16 boundary-layout weights (as ramp_pack_weights takes them) on the device and
  * lays the codes out in MFMA fragment order, followed by the scale bytes; outside the timed path.
- * The FP8 tile family is enumerated apart from the bf16 one (mode bit 0x10000, bk = 128; 0x400 with it = the persistent
- * ping-pong kernels, for H and I of at least 384); its configurations
+ * The FP8 tile family is enumerated apart from the bf16 one (mode bit 0x10000, bk = 128; 0x400 or 0x20000 with it = the
+ * persistent ping-pong kernels, for H and I of at least 384, as for bf16); its configurations
  * work with ramp_config_ntiles, ramp_grid, ramp_cost_model_fit / select like any other. */
 int ramp_fp8_num_configs(const ramp_shape *shape);
 int ramp_fp8_get_config(const ramp_shape *shape, int idx, ramp_config *out);

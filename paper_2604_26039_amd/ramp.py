@@ -19,6 +19,8 @@ LIB_PATH = os.path.join(_PKG, "libramp.so")
 
 OK, EINVAL, ENOSPC, EUNSUPPORTED, EHIP = 0, -1, -2, -3, -4
 CM_EQ6, CM_RELATIVE, CM_DISTINCT_TILES, CM_WAVE_FLOOR, CM_PAIRS, CM_ROUNDS = 0, 1, 2, 4, 8, 16
+# mode bits of a persistent tile: one whose width divides the hidden size, or one for H = 256 * n + 128
+PERSISTENT = 0x400 | 0x20000
 
 
 class Shape(ctypes.Structure):

@@ -159,11 +159,11 @@ class Family:
         """The bf16 tile family of the shape, or (fp8=True) the W8A8 FP8 one.  Where the persistent FP8 tiles run, the LDS-staged
         ones of 64 rows and more stay out of it: at 69 points (four shapes, T = 1 ... 8192, 12 to 100 % of the experts active) none
         of them was the fastest, the nearest 4 % behind it, and they took 31 to 50 % of the time of the LDS-staged and
-        persistent tiles together."""
+        persistent tiles together.  (They are 256 wide: for H = 256 * n + 128 there are none.)"""
         rs = ramp.Shape(T, s.k, s.E, s.H, s.I)
         cfgs = ramp.fp8_configs(rs) if fp8 else ramp.configs(rs)
-        if any(c.mode & ramp.FP8_MODE and c.mode & 0x400 for c in cfgs):
-            cfgs = [c for c in cfgs if c.mode & 0x500 or c.bm < 64]
+        if any(c.mode & ramp.FP8_MODE and c.mode & ramp.PERSISTENT for c in cfgs):
+            cfgs = [c for c in cfgs if c.mode & (0x100 | ramp.PERSISTENT) or c.bm < 64]
         cap = ramp.fp8_config_wave_capacity if fp8 else ramp.config_wave_capacity
         return Family(rs, cfgs, np.array([ramp.config_ntiles(rs, c) for c in cfgs], np.int32),
                       np.array([cap(c) for c in cfgs], np.int32))

@@ -35,7 +35,7 @@ def test_selected_layer(T):
     d_w = torch.from_numpy(np.ascontiguousarray(w, np.float32)).to(DEV)
     cfgs = tuner.Family.of(S, T).cfgs
     # a tile with per-slot weights, one without, and the smallest and the largest token block
-    cands = [next(c for c in cfgs if c.mode & 0x400), next(c for c in cfgs if not c.mode & 0x700),
+    cands = [next(c for c in cfgs if c.mode & ramp.PERSISTENT), next(c for c in cfgs if not c.mode & 0x700),
              min(cfgs, key=lambda c: c.bm), max(cfgs, key=lambda c: c.bm)]
     nbytes = ramp.fused_moe_selected_workspace_bytes(rs, cands)
     for pos, cfg in enumerate(cands):

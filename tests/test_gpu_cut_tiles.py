@@ -30,7 +30,7 @@ def test_every_element(m_tiles, E, H, I):
         plain = next(c for c in cfgs if not c.mode & 0x20700 and c.bm == (32 if fp8 else 128) and c.bn == 128)
         want = L.run(plain, ids, w).clone()
         mod.assert_close(want[at], L.oracle_rows(ids, w, rows=rows), f"{plain}")
-        persistent = [c for c in cfgs if c.mode & 0x20400]
+        persistent = [c for c in cfgs if c.mode & ramp.PERSISTENT]
         assert {128, 256} <= {c.bm for c in persistent}
         for c in persistent:
             print(f"case E={E} T={T} {c}", flush=True)

@@ -29,9 +29,9 @@ def test_tile_edges(H, I, k):
     T = ids.shape[0]
     L = Fp8Layer(s, T, seed=I, x_std=1.5)
     cfgs = ramp.fp8_configs(L.rs)
-    persistent = [c for c in cfgs if c.mode & 0x400]
+    persistent = [c for c in cfgs if c.mode & ramp.PERSISTENT]
     assert {c.bm for c in persistent} == {128, 256}
-    base = next(c for c in cfgs if c.bm == 128 and not c.mode & 0x400)
+    base = next(c for c in cfgs if c.bm == 128 and not c.mode & ramp.PERSISTENT)
     want = L.run(base, ids, w).clone()
     rows = sorted(np.random.default_rng(1).choice(T, 12, replace=False).tolist())
     assert_close(want[torch.tensor(rows, device=DEV)], L.oracle_rows(ids, w, rows=rows), f"H={H} I={I} {base}")
@@ -64,7 +64,7 @@ def test_infinities_and_nan_in_the_quantised_activation():
     cfgs = ramp.fp8_configs(L.rs)
     want = L.run(next(c for c in cfgs if c.bm == 64), ids, w).clone()
     assert torch.isfinite(want.float()).all()
-    for cfg in [c for c in cfgs if c.mode & 0x400]:
+    for cfg in [c for c in cfgs if c.mode & ramp.PERSISTENT]:
         print(f"case {cfg}", flush=True)
         got = L.run(cfg, ids, w)
         assert torch.equal(got.view(torch.int16), want.view(torch.int16)), f"{cfg}"
@@ -78,7 +78,7 @@ def test_many_tiles_per_workgroup_and_bf16_pair_rows(T, beta):
     ids, w = synth.routing(T, s, beta, seed=3)
     cfgs = ramp.fp8_configs(L.rs)
     want = L.run(next(c for c in cfgs if c.bm == 64), ids, w).clone()
-    for cfg in [c for c in cfgs if c.mode & 0x400]:
+    for cfg in [c for c in cfgs if c.mode & ramp.PERSISTENT]:
         print(f"case T={T} {cfg}", flush=True)
         for _ in range(2):
             got = L.run(cfg, ids, w)

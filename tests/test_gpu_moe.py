@@ -135,7 +135,7 @@ def test_smallest_dimensions_many_tiles(H, I, E, k, T, beta):
     ids, w = synth.routing(T, shape, beta, seed=T)
     ref = L.oracle_rows(ids, w)
     cfgs = ramp.configs(L.rs)
-    assert any(c.mode & 0x400 for c in cfgs) and any(c.mode & 0x100 for c in cfgs)
+    assert any(c.mode & ramp.PERSISTENT for c in cfgs) and any(c.mode & 0x100 for c in cfgs)
     for cfg in cfgs:
         assert_close(L.run(cfg, ids, w), ref, f"H={H} I={I} {cfg}")
 
@@ -156,7 +156,7 @@ def test_expert_row_counts_around_the_tile_and_tail_block_sizes():
     ids = ids.reshape(T, 1)
     w = rng.uniform(0.25, 1.0, size=(T, 1)).astype(np.float32)
     ref = L.oracle_rows(ids, w)
-    cfgs = [c for c in ramp.configs(L.rs) if c.mode & 0x400]
+    cfgs = [c for c in ramp.configs(L.rs) if c.mode & ramp.PERSISTENT]
     assert {256, 272, 288} <= {c.bm for c in cfgs}
     for cfg in cfgs:
         assert_close(L.run(cfg, ids, w), ref, f"{cfg}")
@@ -175,7 +175,7 @@ def test_persistent_workgroups_walk_several_tiles_every_row():
     rng = np.random.default_rng(5)
     w = rng.uniform(0.25, 1.0, size=w.shape).astype(np.float32)
     ref = L.oracle_rows(ids, w)
-    cfgs = [c for c in ramp.configs(L.rs) if c.mode & 0x400]
+    cfgs = [c for c in ramp.configs(L.rs) if c.mode & ramp.PERSISTENT]
     assert {256, 272, 288} <= {c.bm for c in cfgs}
     for cfg in cfgs:
         print(f"case {cfg}", flush=True)
@@ -196,7 +196,7 @@ def test_irregular_shapes_every_third_config(H, I, E, k, T, beta):
     ids, w = synth.routing(T, shape, beta, seed=E * 100 + k)
     ref = L.oracle_rows(ids, w)
     cfgs = ramp.configs(L.rs)
-    picked = cfgs[(H // 128) % 3::3] + [c for c in cfgs if c.mode & 0x400]
+    picked = cfgs[(H // 128) % 3::3] + [c for c in cfgs if c.mode & ramp.PERSISTENT]
     assert picked
     for cfg in picked:
         assert_close(L.run(cfg, ids, w), ref, f"H={H} I={I} E={E} k={k} T={T} {cfg}")
@@ -228,7 +228,7 @@ def test_randomized_shapes_sampled_rows(seed):
             continue
         cfgs = ramp.configs(L.rs)
         picked = [cfgs[i] for i in rng.choice(len(cfgs), min(len(cfgs), 10), replace=False)]
-        picked += [c for c in cfgs if c.mode & 0x400][:3]
+        picked += [c for c in cfgs if c.mode & ramp.PERSISTENT][:3]
         sel = torch.from_numpy(rows).to(DEV)
         for cfg in picked:
             assert_close(L.run(cfg, ids, w)[sel], ref, f"seed={seed} case={case} H={H} I={I} E={E} k={k} T={T} beta={beta} {cfg}")
@@ -242,7 +242,7 @@ def test_fused_layer_replays_from_a_hip_graph(olmoe_small):
     T = 96
     rs = ramp.Shape(T, L.s.k, L.s.E, L.s.H, L.s.I)
     cfgs = ramp.configs(rs)
-    picked = [cfgs[0]] + [c for c in cfgs if c.mode & 0x400][:1] + [c for c in cfgs if c.mode & 0x100][:1]
+    picked = [cfgs[0]] + [c for c in cfgs if c.mode & ramp.PERSISTENT][:1] + [c for c in cfgs if c.mode & 0x100][:1]
     for cfg in picked:
         d_ids = torch.zeros((T, L.s.k), dtype=torch.int32, device=DEV)
         d_w = torch.zeros((T, L.s.k), dtype=torch.float32, device=DEV)
@@ -412,7 +412,7 @@ def large_tile_configs(rs):
     """Every persistent ping-pong configuration valid for the shape (what the large batches dispatch), plus the
     first LDS-ring configuration of each large token block and one mid-size block."""
     cfgs = ramp.configs(rs)
-    picked = [c for c in cfgs if c.mode & 0x400]
+    picked = [c for c in cfgs if c.mode & ramp.PERSISTENT]
     assert any(c.key()[:5] == (256, 256, 32, 8, 3) for c in picked) and any(c.key()[:5] == (256, 256, 32, 8, 4) for c in picked)
     seen = set()
     for c in cfgs:
@@ -454,7 +454,7 @@ def test_largest_points_run_twice_bit_identical(name, T, beta):
     s = L.s
     ids, w = synth.routing(T, s, beta, seed=T + 9)
     rs = ramp.Shape(T, s.k, s.E, s.H, s.I)
-    for cfg in [c for c in ramp.configs(rs) if c.mode & 0x400]:
+    for cfg in [c for c in ramp.configs(rs) if c.mode & ramp.PERSISTENT]:
         print(f"case {name} T={T} beta={beta} {cfg}", flush=True)
         a = L.run(cfg, ids, w, T=T, poison=False).clone()
         b = L.run(cfg, ids, w, T=T, poison=True)

@@ -19,7 +19,7 @@ def test_wave_capacity_agrees_with_the_runtime_occupancy():
         static = ramp.config_wave_capacity(c) // 256
         up, down = ramp.config_runtime_occupancy(c)
         assert up >= 1 and down >= 1, key
-        if c.mode & 0x400:
+        if c.mode & ramp.PERSISTENT:
             assert static == 1, key          # persistent kernels launch one workgroup per compute unit
         else:
             assert static == up, f"{key}: static {static}, runtime {up} (up-projection) / {down} (down-projection)"
@@ -35,4 +35,4 @@ def test_fp8_wave_capacity_agrees_with_the_runtime_occupancy():
     for key, c in seen.items():
         static = ramp.fp8_config_wave_capacity(c) // 256
         up, down = ramp.fp8_config_runtime_occupancy(c)
-        assert static == (1 if c.mode & 0x400 else up), f"{key}: static {static}, runtime {up} / {down}"
+        assert static == (1 if c.mode & ramp.PERSISTENT else up), f"{key}: static {static}, runtime {up} / {down}"

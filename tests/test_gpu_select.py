@@ -108,7 +108,7 @@ def test_select_device_matches_oracle(name, T, beta, flags):
 def test_fp8_dispatcher_matches_oracle(name, T, beta):
     """Selection over the FP8 family: streaming tiles with their wave capacity, hand-out rounds of the persistent ones."""
     s, fam = family(name, T, fp8=True)
-    assert any(c.mode & 0x400 for c in fam.cfgs) and all(c.mode & ramp.FP8_MODE for c in fam.cfgs)
+    assert any(c.mode & ramp.PERSISTENT for c in fam.cfgs) and all(c.mode & ramp.FP8_MODE for c in fam.cfgs)
     disp = {seed: tuner.Dispatcher(fam, synthetic_theta(fam, seed), ALL_FLAGS, T, device=DEV) for seed in range(6)}
     chosen = set()
     for seed, d in disp.items():
@@ -206,7 +206,7 @@ def test_select_device_rejects_bad_arguments():
 def _candidates(fam):
     """One configuration of each kernel family, small and large token blocks."""
     pick = []
-    for want in (lambda c: c.mode & 0x100 and c.bm <= 16, lambda c: c.mode & 0x400 and c.bm == 256,
+    for want in (lambda c: c.mode & 0x100 and c.bm <= 16, lambda c: c.mode & ramp.PERSISTENT and c.bm == 256,
                  lambda c: not (c.mode & 0x700) and c.bm == 64, lambda c: c.mode & 0x200):
         pick += [c for c in fam.cfgs if want(c)][:1]
     return pick

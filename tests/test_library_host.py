@@ -94,20 +94,42 @@ def test_fp8_streaming_tiles_end_where_their_launch_would_pass_2_32_threads():
             runs = not c.mode & 0x100 or threads < 2 ** 32
             assert (c.key() in listed) == runs, (T, c)
             seen.add(runs)
-        assert any(c.mode & 0x400 and c.key() in listed for c in every)
+        assert any(c.mode & ramp.PERSISTENT and c.key() in listed for c in every)
     assert seen == {True, False}
 
 
 def test_fp8_tuner_family_leaves_out_what_the_persistent_tiles_replace():
+    """(The staged tiles of 64 rows and more are 256 wide: hidden sizes of 256 * n + 128 have none to leave out.)"""
     from paper_2604_26039_amd import tuner
     keys = lambda cfgs: [c.key() for c in cfgs]
-    staged = lambda c: not c.mode & 0x500
-    for s, persistent in ((synth.SHAPES["qwen3"], True), (synth.Shape("short", 256, 512, 8, 2), False), (synth.Shape("odd", 1152, 896, 48, 6), False)):
+    staged = lambda c: not c.mode & (0x100 | ramp.PERSISTENT)
+    for s, persistent in ((synth.SHAPES["qwen3"], True), (synth.Shape("short", 256, 512, 8, 2), False), (synth.Shape("odd", 1152, 896, 48, 6), True)):
         every = ramp.fp8_configs(ramp.Shape(64, s.k, s.E, s.H, s.I))
-        assert any(c.mode & 0x400 for c in every) == persistent
+        assert any(c.mode & ramp.PERSISTENT for c in every) == persistent
         left_out = [c for c in every if persistent and staged(c) and c.bm >= 64]
-        assert bool(left_out) == persistent
+        assert bool(left_out) == (persistent and s.H % 256 == 0)
         assert keys(tuner.Family.of(s, 64, fp8=True).cfgs) == [k for k in keys(every) if k not in keys(left_out)]
+
+
+@pytest.mark.parametrize("H", [1024, 1152])
+def test_what_the_mode_bits_of_the_persistent_tiles_stand_for(H):
+    """One of the two bits of ramp.PERSISTENT marks the tiles that walk with one workgroup per unit, whatever the hidden size: capacity
+    of 256, rounds of 8 * group_m M-tiles, and the kernel that the benchmark names."""
+    import bench
+    rs = ramp.Shape(64, 6, 48, H, 896)
+    half = H % 256 != 0
+    for cfgs, capacity in ((ramp.configs(rs), ramp.config_wave_capacity), (ramp.fp8_configs(rs), ramp.fp8_config_wave_capacity)):
+        marked = [c for c in cfgs if c.mode & ramp.PERSISTENT and c.bn == 256]
+        assert {128, 256} <= {c.bm for c in marked}
+        for c in cfgs:
+            persistent = bool(c.mode & ramp.PERSISTENT)
+            assert not (c.mode & 0x400 and c.mode & 0x20000)
+            assert (H % c.bn == 128 and bool(c.mode & 0x20000)) or (H % c.bn == 0 and not c.mode & 0x20000)
+            assert (ramp.config_rounds(rs, c)[0] > 1) == persistent
+            if persistent:
+                assert capacity(c) == 256 and bool(c.mode & 0x20000) == (half and c.bn == 256)
+            if not c.mode & ramp.FP8_MODE:
+                assert ("moe_pingpong_kernel" in bench.kernel_name(c)) == persistent
 
 
 def test_fp8_wave_capacity_follows_from_the_registers_and_lds_of_the_kernels():
@@ -115,7 +137,7 @@ def test_fp8_wave_capacity_follows_from_the_registers_and_lds_of_the_kernels():
     with open(os.path.join(lib_build.OBJ_DIR, "fp8.hip.resources.json")) as f:
         records = {(r["family"], tuple(r["targs"])): r for r in json.load(f)}
     for c in ramp.fp8_configs(ramp.Shape(1, 1, 64, 2048, 1024)):
-        if c.mode & 0x400:
+        if c.mode & ramp.PERSISTENT:
             assert ramp.fp8_config_wave_capacity(c) == 256
             continue
         if c.mode & 0x100:                                  # streaming: mode low byte = WK, stages = 2 * U
@@ -379,8 +401,8 @@ def test_config_rounds_and_the_rounds_model_against_the_oracle():
     # FP8: the persistent tiles as the bf16 ones, one M-tile for the others
     for c in ramp.fp8_configs(sh):
         up, down = 2 * sh.I // c.bn, sh.H // c.bn
-        assert list(ramp.config_rounds(sh, c)) == ([16, 16, 8, 28] if c.mode & 0x400 else [1, up, 1, down]), c
-    assert list(ramp.config_rounds(q, next(c for c in ramp.fp8_configs(q) if c.mode & 0x400))) == [40, 6, 32, 8]
+        assert list(ramp.config_rounds(sh, c)) == ([16, 16, 8, 28] if c.mode & ramp.PERSISTENT else [1, up, 1, down]), c
+    assert list(ramp.config_rounds(q, next(c for c in ramp.fp8_configs(q) if c.mode & ramp.PERSISTENT))) == [40, 6, 32, 8]
     with pytest.raises(ramp.RampError):
         ramp.config_rounds(sh, ramp.Config(256, 0, 32, 8, 4, 1025))
     for name, T, beta in (("qwen3", 2048, 0.3), ("dsv3", 8192, 1.0), ("olmoe", 64, 0.2)):
@@ -401,7 +423,7 @@ def test_config_rounds_and_the_rounds_model_against_the_oracle():
         for i, c in enumerate(cfgs):
             for j, h in enumerate(hists):
                 assert gr[i, j] == oracle.grid_rounds(h, c.bm, rounds[i])
-            if not c.mode & 0x400:
+            if not c.mode & ramp.PERSISTENT:
                 assert np.array_equal(gr[i], g[i])
         t = 20.0 + 3.0 * gr / wc[:, None] + 0.01 * u + 1e-3 * P[None, :] * rng.uniform(0.9, 1.1, (n, len(hists)))
         flags = ramp.CM_RELATIVE | ramp.CM_DISTINCT_TILES | ramp.CM_WAVE_FLOOR | ramp.CM_PAIRS | ramp.CM_ROUNDS

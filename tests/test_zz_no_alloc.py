@@ -29,7 +29,7 @@ def test_static_workspace_entry_point_matches_fused_moe():
     for cfg in ramp.configs(rs_max):
         if ramp.fused_moe_workspace_bytes(rs_max, cfg) > ramp.STATIC_WS_BYTES:
             continue
-        if checked % 4 and not (cfg.mode & 0x400):   # every fourth configuration plus the ping-pong ones
+        if checked % 4 and not (cfg.mode & ramp.PERSISTENT):   # every fourth configuration plus the ping-pong ones
             checked += 1
             continue
         checked += 1
