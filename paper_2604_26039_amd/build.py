@@ -30,7 +30,7 @@ KERNEL_SOURCES = ["gemm_group0.hip", "gemm_group1.hip", "gemm_group2.hip", "gemm
                   "stream_group2.hip"]
 SOURCES = ["align.hip", "select.hip", "pack.hip", "fused.hip", "fp8.hip", "stream_selected.hip"] + KERNEL_SOURCES + ["cost_model.cpp"]
 RESOURCE_SOURCES = KERNEL_SOURCES + ["fp8.hip"]  # hold projection kernels of a tile family
-HEADERS = ["ramp_internal.h", "moe_gemm.h", "moe_pingpong.h", "moe_stream.h", "moe_decode.h", "moe_fp8_pingpong.h", "moe_fp8_stream.h", "fp8_format.h", "align_tiny.h", "config_list.h", os.path.join(ROOT, "include", "ramp.h")]
+HEADERS = ["ramp_internal.h", "moe_gemm.h", "moe_pingpong.h", "moe_stream.h", "moe_decode.h", "moe_fp8_pingpong.h", "moe_fp8_stream.h", "fp8_format.h", "align_tiny.h", "tile_walk.h", "config_list.h", os.path.join(ROOT, "include", "ramp.h")]
 
 COMMON = ["-O3", "-fPIC", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-ffp-contract=off"]
 # packed fp32 ops are disabled on purpose: some of their forms have produced wrong results on this hardware

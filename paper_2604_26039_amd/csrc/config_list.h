@@ -100,7 +100,7 @@
     X(16, 2, 2, 4, 4)         \
     X(16, 2, 2, 2, 4)
 
-// The stream tiles that one launch of the device-selected layer can hold together (moe_stream_selected.hip): 8 or 4 wavefronts whose
+// The stream tiles that one launch of the device-selected layer can hold together (stream_selected.hip): 8 or 4 wavefronts whose
 // operands and sums fit 128 registers, or nearly.
 #define RAMP_STREAM_SELECTED_GROUP(X) \
     X(4, 2, 1, 8, 2)          \

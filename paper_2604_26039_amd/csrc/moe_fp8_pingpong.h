@@ -109,7 +109,7 @@ __global__ __launch_bounds__(512, 1) void moe_fp8_pingpong_kernel(GemmArgs a, Fp
     const TileWalk walk = tile_walk(a, m_tiles, a.tile_expert, CUTS ? 2 : 1);
     auto tile_at = [&](int pos, int &n_tile, int &m_tile) __attribute__((always_inline)) -> bool {
         if (pos >= walk.whole) return false;
-        tile_of_slot(a, walk, pos < 0 ? walk.whole + (walk.wg >> walk.cut) : pos, n_tile, m_tile);
+        tile_of_slot(a, walk, walk_slot(walk, pos), n_tile, m_tile);
         n_tile = __builtin_amdgcn_readfirstlane(n_tile);
         m_tile = __builtin_amdgcn_readfirstlane(m_tile);
         return true;
@@ -583,8 +583,8 @@ void launch_fp8_pingpong(int stage, const GemmArgs &a, const Fp8PingPongArgs &f,
 {
     if (a.n_tiles <= 0 || a.m_tiles_cap <= 0) return;
     GemmArgs g = a;
-    g.total_tiles = (int)xcd_grid(g);
-    const dim3 grid(g.total_tiles < kNumCU ? g.total_tiles : kNumCU), block(512);
+    const unsigned tiles = xcd_grid(g);
+    const dim3 grid(tiles < (unsigned)kNumCU ? tiles : (unsigned)kNumCU), block(512);
     if (stage == 1)
         hipLaunchKernelGGL((moe_fp8_pingpong_kernel<1, NH>), grid, block, 0, stream, g, f);
     else

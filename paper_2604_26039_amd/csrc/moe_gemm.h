@@ -239,97 +239,6 @@ __device__ __forceinline__ void tile_of_id(const GemmArgs &a, int id, int &n_til
     m_tile = (mb * 8 + xcd) * a.group_m + dm;
 }
 
-// The same map for the persistent kernels, whose workgroup c of an XCD walks slots c, c + 32, ...  With the static map
-// a workgroup gets the same position of every block and an XCD every eighth M-tile; where the experts have a full
-// M-tile followed by a ragged one (two tiles per expert: block positions and XCDs alternate full, ragged) half of the
-// workgroups, or half of the XCDs, then only ever get ragged tiles, finish early and run ahead of the siblings they
-// share weights with.  So the position inside the block moves on by one per block, and the XCD -> M-tile assignment
-// inside a round of 8 * group_m M-tiles by three per round: an XCD then steps through the M-tiles by 11 or 3 instead
-// of 8, which does not stay in phase with 2, 3, 4, 8 or 9 tiles per expert (a shift of one, steps of 9, does with 3
-// and 9: measured 7 % slower on such a layer).  The tiles an XCD works on at a time stay the same, who gets which
-// changes.  Same-box A/B of the layer: DeepSeek-V3 T = 2048 at 52 active experts (two tiles each) 2010 -> 1766 us,
-// Mixtral T = 8192 4980 -> 4880 us, T = 1024 1035 -> 1013 us, the other large points within +-1 %.
-//
-// The walk knows the real number of M-tiles (align's, on the device) and shares out three ways:
-// - What whole rounds of 8 * group_m M-tiles leave is dealt to all XCDs evenly, M-tile by M-tile.  With the rounds of the map alone
-//   13 M-tiles over rounds of 8 gave five XCDs twice the tiles of the other three (Mixtral-shaped, T = 1024 Zipf: up-projection
-//   625 -> 568 us with the next point; T = 512 Zipf 485 -> 394).
-// - Where M-tiles share an expert (told from the first eight entries of the tile table) a round is split so that an XCD's 32
-//   workgroups take up to 4 M-tiles x 8 N-tiles at a time, not 1 x 32 or 2 x 16: fewer bytes cross the fabric (FETCH_SIZE of the
-//   FP8 up-projection at Mixtral's T = 8192 8.3 -> 5.3 GB), and the power that saves is clock for kernels held by it: 1691 -> 1575 us,
-//   bf16 2903 -> 2780.  With one M-tile per expert nothing is shared and the default split is the better one (2016 against 2079
-//   to 2108 us in the DeepSeek-V3-shaped down-projection at T = 8192).
-// - Of fewer than three turns of an XCD's workgroups, the tiles that fill no whole turn are cut in two or four column parts where
-//   that many workgroups would idle, and come first: 36 M-tiles x 8 N-tiles on 256 units are one turn and 32 tiles (Qwen3-shaped,
-//   T = 509: down-projection 41 -> 38 us; Mixtral-shaped, T = 200 207 -> 181; H = 1152, T = 777, up 50 -> 46).  A part takes as
-//   many slices as a tile, with fewer weights, so behind three whole turns it gains under 1 %, and out of step with the tiles that
-//   share its weights it can cost as much.
-struct TileWalk {
-    int full, total;   // slots of this XCD in the whole rounds, and in all
-    int m_full, tail0; // M-tiles of the whole rounds; first tile of this XCD's share of the rest
-    int xm_log;        // log2 of xm: the round is split between xm x 8/xm XCDs
-    int wg, wgs;       // this workgroup of its XCD, and how many there are
-    int whole, cut;    // slots that the workgroups take one each, in whole turns; the others are cut in 1 << cut parts
-    int part;          // this workgroup's part of a cut tile
-};
-__device__ __forceinline__ TileWalk tile_walk(const GemmArgs &a, int m_tiles, const int32_t *tile_expert, int max_parts)
-{
-    TileWalk w;
-    const int xcd = (int)blockIdx.x & 7, per_round = 8 * a.group_m;
-    const int rounds = div_by(m_tiles >> 3, a.gm_magic), rest = (m_tiles - rounds * per_round) * a.n_tiles;
-    w.m_full = rounds * per_round;
-    w.full = rounds * a.group_m * a.n_tiles;
-    w.tail0 = (xcd * rest) >> 3;
-    w.total = w.full + (((xcd + 1) * rest) >> 3) - w.tail0;
-    w.xm_log = 3;
-    if (rounds > 0 && a.group_m_req == 0 && a.group_m <= 2) {
-        int same = 0;
-#pragma unroll
-        for (int i = 0; i < 7; ++i) same += load_uniform_i32(tile_expert + i) == load_uniform_i32(tile_expert + i + 1);
-        if (a.group_m == 1 && same >= 6 && a.n_tiles % 4 == 0) w.xm_log = 1;
-        else if (same >= 4 && a.n_tiles % 2 == 0) w.xm_log = 2;
-    }
-    w.wg = (int)blockIdx.x >> 3;
-    w.wgs = (int)gridDim.x >> 3;
-    const int left = __builtin_amdgcn_readfirstlane(w.total % w.wgs);
-    w.cut = 0;
-    if (left > 0 && w.total < 3 * w.wgs)
-        while ((2 << w.cut) <= max_parts && (left * 2 << w.cut) <= w.wgs) ++w.cut;
-    w.whole = w.cut > 0 ? w.total - left : w.total;
-    w.part = w.wg & ((1 << w.cut) - 1);
-    return w;
-}
-// What a workgroup takes: position -1 is its part of a cut tile, which comes first, s >= 0 the tile of slot s.
-__device__ __forceinline__ int walk_first(const TileWalk &w)
-{
-    return w.cut > 0 && w.wg < (w.total - w.whole) << w.cut ? -1 : w.wg;
-}
-__device__ __forceinline__ int walk_next(const TileWalk &w, int pos) { return pos < 0 ? w.wg : pos + w.wgs; }
-// Tile of slot s < total.
-__device__ __forceinline__ void tile_of_slot(const GemmArgs &a, const TileWalk &w, int s, int &n_tile, int &m_tile)
-{
-    if (s >= w.full) {
-        const int f = w.tail0 + s - w.full;
-        const int m = div_by(f, a.n_magic);
-        m_tile = w.m_full + m;
-        n_tile = f - m * a.n_tiles;
-        return;
-    }
-    const int xcd = (int)blockIdx.x & 7;
-    // an XCD's block: gm M-tiles x gn N-tiles
-    const int xn_log = 3 - w.xm_log, gm = a.group_m << xn_log, gn = a.group_n >> xn_log;
-    const int per_block = a.group_m * a.group_n;
-    const int sb = div_by(s, a.block_magic);
-    const int turn = s - sb * per_block + sb;
-    const int v = turn - div_by(turn, a.block_magic) * per_block;
-    const int dn = div_by(v >> xn_log, a.gm_magic), dm = v - dn * gm;
-    const int mb = div_by(sb, a.bn_magic), nbi = sb - mb * a.blocks_n;
-    const int x = (xcd + 3 * mb) & 7;
-    const int xn = x >> w.xm_log, xm = x & ((1 << w.xm_log) - 1);
-    n_tile = ((nbi << xn_log) + xn) * gn + dn;
-    m_tile = ((mb << w.xm_log) + xm) * gm + dm;
-}
-
 __device__ __forceinline__ void tile_of_workgroup(const GemmArgs &a, int &n_tile, int &m_tile)
 {
     tile_of_id(a, (int)blockIdx.x, n_tile, m_tile);
@@ -338,15 +247,21 @@ __device__ __forceinline__ void tile_of_workgroup(const GemmArgs &a, int &n_tile
 // Picks the block shape for the launch and returns the (overlaunched) number of tile ids that tile_of_id expects.
 inline unsigned xcd_grid(GemmArgs &g)
 {
-    xcd_block_shape(g.n_tiles, g.group_m_req, &g.group_m, &g.group_n);
-    g.blocks_n = g.n_tiles / g.group_n;
-    g.block_magic = div_magic(g.group_m * g.group_n);
-    g.gm_magic = div_magic(g.group_m);
-    g.n_magic = div_magic(g.n_tiles);
-    g.bn_magic = div_magic(g.blocks_n);
+    tile_map(g);
     const int per_round = 8 * g.group_m;  // M-tiles handed out per round over the 8 XCDs
     const int rounds = (g.m_tiles_cap + per_round - 1) / per_round;
     return (unsigned)rounds * (unsigned)per_round * (unsigned)g.n_tiles;
+}
+
+// The walk of this workgroup of a persistent kernel over the m_tiles that the call has.
+__device__ __forceinline__ TileWalk tile_walk(const GemmArgs &a, int m_tiles, const int32_t *tile_expert, int max_parts)
+{
+    int same = 0;
+    if (m_tiles >= 8 * a.group_m && a.group_m_req == 0 && a.group_m <= 2) {
+#pragma unroll
+        for (int i = 0; i < 7; ++i) same += load_uniform_i32(tile_expert + i) == load_uniform_i32(tile_expert + i + 1);
+    }
+    return tile_walk(a, (int)blockIdx.x & 7, (int)blockIdx.x >> 3, (int)gridDim.x >> 3, m_tiles, same, max_parts);
 }
 
 template <int STAGE, int BM, int BN, int BK, int WM, int WN, int NSTAGE, int LOOP>

@@ -136,7 +136,7 @@ __global__ __launch_bounds__(512, 1) void moe_pingpong_kernel(GemmArgs a)
     const TileWalk walk = tile_walk(a, m_tiles, a.tile_expert, WN);
     auto tile_at = [&](int pos, int &n_tile, int &m_tile) __attribute__((always_inline)) -> bool {
         if (pos >= walk.whole) return false;
-        tile_of_slot(a, walk, pos < 0 ? walk.whole + (walk.wg >> walk.cut) : pos, n_tile, m_tile);
+        tile_of_slot(a, walk, walk_slot(walk, pos), n_tile, m_tile);
         // wave-uniform by construction; saying so lets the per-tile table reads below be scalar loads, which do not
         // count on vmcnt (a vector load would have to be waited for in order, behind every LDS-direct load in flight)
         n_tile = __builtin_amdgcn_readfirstlane(n_tile);
@@ -654,9 +654,9 @@ void launch_pingpong(int stage, const GemmArgs &a, hipStream_t stream)
 {
     if (a.n_tiles <= 0 || a.m_tiles_cap <= 0) return;
     GemmArgs g = a;
-    g.total_tiles = (int)xcd_grid(g);
+    const unsigned tiles = xcd_grid(g);
     // persistent: one workgroup per compute unit walks its share of the tiles (the count is a multiple of 8)
-    const dim3 grid(g.total_tiles < kNumCU ? g.total_tiles : kNumCU), block(512);
+    const dim3 grid(tiles < (unsigned)kNumCU ? tiles : (unsigned)kNumCU), block(512);
     // the down-projection stages tokens and weights per slice and needs LDS for its output rows: at most 4 stages
     constexpr int NS2 = pingpong_down_stages<BM, WM, NSTAGE>();
     if (stage == 1)

@@ -6,6 +6,7 @@
 #include <stdio.h>
 
 #include "ramp.h"
+#include "tile_walk.h"
 
 namespace ramp {
 
@@ -134,7 +135,6 @@ struct GemmArgs {
     int m_tiles_cap;            // launched M-tiles (upper bound)
     int group_m_req;            // GROUP_M of the configuration (mode bits 12-15): M-tiles per XCD block, 0 = automatic
     int group_m, group_n;       // M-tiles x N-tiles per XCD block of the workgroup->tile map (set by the launcher)
-    int total_tiles;            // persistent kernels: tile ids to walk (set by the launcher)
     int blocks_n;               // n_tiles / group_n
     // their divisors as multipliers (div_magic, set by the launcher): group_m * group_n, group_m, n_tiles, blocks_n
     unsigned long long block_magic, gm_magic, n_magic, bn_magic;
@@ -142,9 +142,6 @@ struct GemmArgs {
     const int32_t *pred;        // device-side predicate: the launch does nothing unless *pred == pred_value (NULL: always runs)
     int pred_value;
 };
-// x / d as (x * ceil(2^40 / d)) >> 40: exact for x * d < 2^40, x < 2^24.  Of wave-uniform values it stays in scalar registers.
-constexpr unsigned long long div_magic(int d) { return ((1ull << 40) + (unsigned)d - 1) / (unsigned)d; }
-__device__ __forceinline__ int div_by(int x, unsigned long long magic) { return (int)(((unsigned long long)(unsigned)x * magic) >> 40); }
 // True when a predicated launch is not the one selected on the device.
 __device__ __forceinline__ bool launch_deselected(const int32_t *pred, int pred_value)
 {
@@ -170,30 +167,7 @@ constexpr int kModeGroupShift = 12;
 constexpr int kModeGroupMask = 0xF << kModeGroupShift;
 inline int group_m_of_mode(int mode) { const int v = (mode & kModeGroupMask) >> kModeGroupShift; return v ? (1 << v) : 0; }
 
-// Block shape of the XCD-aware workgroup -> tile map of one launch: every XCD takes blocks of group_m M-tiles x
-// group_n N-tiles, the 8 XCDs 8 * group_m M-tiles per hand-out round.  group_m_req > 0: the GROUP_M mode of the
-// configuration (group_n = the largest divisor of n_tiles up to 32 / group_m).  Default: a block spans all N-tiles, so
-// the token rows of its few M-tiles (group_m * bm * K * 2 bytes) stay in the 4 MB L2 across the walk over N while the
-// 8 XCDs work on neighbouring M-tiles, i.e. mostly the same expert, and share its weights through the memory-side cache.
-inline void xcd_block_shape(int n_tiles, int group_m_req, int *group_m, int *group_n)
-{
-    if (group_m_req > 0) {
-        int gn = 32 / group_m_req;
-        if (gn < 1) gn = 1;
-        if (gn > n_tiles) gn = n_tiles;
-        while (n_tiles % gn) --gn;
-        *group_m = group_m_req;
-        *group_n = gn;
-    } else {
-        int gm = 32 / n_tiles;
-        if (gm < 1) gm = 1;
-        if (gm > 8) gm = 8;
-        *group_m = gm;
-        *group_n = n_tiles;
-    }
-}
-
-// The stream candidates of a device-selected call, for one launch per projection (moe_stream_selected.hip): the position of a
+// The stream candidates of a device-selected call, for one launch per projection (stream_selected.hip): the position of a
 // candidate's tile in RAMP_STREAM_SELECTED_GROUP, or -1, and what differs between the candidates' arguments (byte offsets).
 struct StreamChoice {
     int32_t shape, bn, m_tiles_cap;
