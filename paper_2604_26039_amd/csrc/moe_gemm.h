@@ -257,9 +257,13 @@ inline unsigned xcd_grid(GemmArgs &g)
 __device__ __forceinline__ TileWalk tile_walk(const GemmArgs &a, int m_tiles, const int32_t *tile_expert, int max_parts)
 {
     int same = 0;
-    if (m_tiles >= 8 * a.group_m && a.group_m_req == 0 && a.group_m <= 2) {
+    if (walk_looks_at_experts(a.group_m, a.group_m_req, m_tiles)) {
 #pragma unroll
-        for (int i = 0; i < 7; ++i) same += load_uniform_i32(tile_expert + i) == load_uniform_i32(tile_expert + i + 1);
+        for (int c = 0; c < kShareRuns; ++c) {
+            const int32_t *e = tile_expert + first_of_run(m_tiles, c);
+#pragma unroll
+            for (int i = 0; i < 7; ++i) same += load_uniform_i32(e + i) == load_uniform_i32(e + i + 1);
+        }
     }
     return tile_walk(a, (int)blockIdx.x & 7, (int)blockIdx.x >> 3, (int)gridDim.x >> 3, m_tiles, same, max_parts);
 }

@@ -17,11 +17,16 @@
 // - What whole rounds of 8 * group_m M-tiles leave is dealt to all XCDs evenly, M-tile by M-tile.  With the rounds of the map alone
 //   13 M-tiles over rounds of 8 gave five XCDs twice the tiles of the other three (Mixtral-shaped, T = 1024 Zipf: up-projection
 //   625 -> 568 us with the next point; T = 512 Zipf 485 -> 394).
-// - Where M-tiles share an expert (told from the first eight entries of the tile table) a round is split so that an XCD's 32
-//   workgroups take up to 4 M-tiles x 8 N-tiles at a time, not 1 x 32 or 2 x 16: fewer bytes cross the fabric (FETCH_SIZE of the
-//   FP8 up-projection at Mixtral's T = 8192 8.3 -> 5.3 GB), and the power that saves is clock for kernels held by it: 1691 -> 1575 us,
-//   bf16 2903 -> 2780.  With one M-tile per expert nothing is shared and the default split is the better one (2016 against 2079
-//   to 2108 us in the DeepSeek-V3-shaped down-projection at T = 8192).
+// - Where M-tiles share an expert a round is split so that an XCD's 32 workgroups take up to 4 M-tiles x 8 N-tiles at a time, not
+//   1 x 32 or 2 x 16: fewer bytes cross the fabric (FETCH_SIZE of the FP8 up-projection at Mixtral's T = 8192 8.3 -> 5.3 GB), and
+//   the power that saves is clock for kernels held by it: 1691 -> 1575 us, bf16 2903 -> 2780.  With one M-tile per expert nothing is
+//   shared and the default split is the better one (2016 against 2079 to 2108 us in the DeepSeek-V3-shaped down-projection at T = 8192).
+//   Blocks of two M-tiles gain less than blocks of one, 128-row tiles more than 256-row ones; one loses: 128-row tiles and a reduction as
+//   long as Mixtral's down-projection (K = 14336, T = 8192, default against split 1857 -> 1979 us), whose layer is the slower one all the same
+//   with that launch alone left unsplit (5527 -> 5578, 4024 -> 4054 us at T = 6000: the up-projection beside it runs at a lower clock then).
+//   The line lies at the share of M-tiles that have the expert of the one before: half of them, and for the split by four three quarters
+//   (layers of 4 and 2 M-tiles an expert).  Default against split, us: none 273 -> 278, 598 -> 618, a third 1049 -> 1062 and 574 -> 547,
+//   half 528 -> 530 and 273 -> 269, three quarters 3273 -> 3086 and 1727 -> 1645.
 // - Of fewer than three turns of an XCD's workgroups, the tiles that fill no whole turn are cut in two or four column parts where
 //   that many workgroups would idle, and come first: 36 M-tiles x 8 N-tiles on 256 units are one turn and 32 tiles (Qwen3-shaped,
 //   T = 509: down-projection 41 -> 38 us; Mixtral-shaped, T = 200 207 -> 181; H = 1152, T = 777, up 50 -> 46).  A part takes as
@@ -87,7 +92,17 @@ struct TileWalk {
     int whole, cut;    // slots that the workgroups take one each, in whole turns; the others are cut in 1 << cut parts
     int part;          // this workgroup's part of a cut tile
 };
-// same: how many of the first eight M-tiles have the expert of the one before
+// The sharing of experts is told from four runs of eight M-tiles, spread over the table: the first eight alone say nothing of a layer whose
+// first experts are rare and others heavy (eight experts of one M-tile in front of eight of eight, H = 4096, I = 14336, T = 8192: layer of
+// 128-row FP8 tiles 3310 -> 2969 us, 256-row 2514 -> 2485, bf16 6589 -> 5929 and 4981 -> 4830; in the opposite order as before).  Runs, not single pairs at
+// a stride, which would be in step with two or four tiles an expert; scalar loads: with a wavefront's vector loads over 256 pairs the
+// kernels spilled.  same counts those of their 28 pairs of neighbours that have one expert.
+constexpr int kShareRuns = 4;
+RAMP_WALK int first_of_run(int m_tiles, int c) { return (m_tiles - 8) * c / (kShareRuns - 1); }
+RAMP_WALK bool walk_looks_at_experts(int group_m, int group_m_req, int m_tiles)
+{
+    return m_tiles >= 8 * group_m && group_m_req == 0 && group_m <= 2;
+}
 template <class Map>
 RAMP_WALK TileWalk tile_walk(const Map &a, int xcd, int wg, int wgs, int m_tiles, int same, int max_parts)
 {
@@ -100,9 +115,10 @@ RAMP_WALK TileWalk tile_walk(const Map &a, int xcd, int wg, int wgs, int m_tiles
     w.tail0 = (xcd * rest) >> 3;
     w.total = w.full + (((xcd + 1) * rest) >> 3) - w.tail0;
     w.xm_log = 3;
-    if (rounds > 0 && a.group_m_req == 0 && a.group_m <= 2) {
-        if (a.group_m == 1 && same >= 6 && a.n_tiles % 4 == 0) w.xm_log = 1;
-        else if (same >= 4 && a.n_tiles % 2 == 0) w.xm_log = 2;
+    if (walk_looks_at_experts(a.group_m, a.group_m_req, m_tiles)) {
+        // (12: what the runs see of two tiles an expert at the worst; four tiles an expert show 20 to 24, three 16 to 20)
+        if (a.group_m == 1 && same >= 19 && a.n_tiles % 4 == 0) w.xm_log = 1;
+        else if (same >= 12 && a.n_tiles % 2 == 0) w.xm_log = 2;
     }
     w.wg = wg;
     w.wgs = wgs;

@@ -17,6 +17,8 @@ struct Map {
     int n_tiles, group_m_req, group_m, group_n, blocks_n;
     unsigned long long block_magic, gm_magic, n_magic, bn_magic;
 };
+extern "C" int first_of_run(int m_tiles, int c) { return ramp::first_of_run(m_tiles, c); }
+extern "C" int share_runs() { return ramp::kShareRuns; }
 // taken[m_tiles][n_tiles]: quarters of the tile that have been taken; info: xm_log, and per workgroup the quarters taken by the one
 // with the most and the least.  -1: a tile or a position out of range.
 extern "C" int walk(int n_tiles, int group_m_req, int m_cap, int m_tiles, int same, int max_parts, int32_t *taken, int32_t *info)
@@ -67,6 +69,7 @@ def walk(tmp_path_factory):
                       info.ctypes.data_as(ctypes.c_void_p))
         assert rc == 0, (n_tiles, group_m_req, m_tiles, same, max_parts)
         return taken[:m_tiles], info
+    run.lib = lib
     return run
 
 
@@ -77,7 +80,7 @@ M_TILES = [0, 1, 2, 3, 7, 8, 9, 13, 16, 17, 24, 31, 32, 33, 36, 40, 63, 64, 65, 
 def test_every_tile_is_taken_once(walk, n_tiles):
     for group_m_req in (0, 2, 4, 8):
         for m_tiles in M_TILES:
-            for same in (0, 4, 7):
+            for same in (0, 12, 28):
                 for max_parts in (1, 2, 4):
                     for m_cap in (m_tiles, m_tiles + 5 * n_tiles):
                         taken, info = walk(n_tiles, group_m_req, m_tiles, same, max_parts, m_cap)
@@ -101,6 +104,43 @@ def test_shares(walk, n_tiles, m_tiles, parts, longest, shortest):
 def test_split_of_a_round(walk):
     """4 M-tiles x 8 N-tiles (xm = 2) where an XCD's block is one M-tile, 4 x 8 (xm = 4) where it is two; never for a GROUP_M shape or less
     than a round."""
-    assert [walk(32, 0, 40, same)[1][0] for same in (0, 3, 4, 5, 6, 7)] == [3, 3, 2, 2, 1, 1]
-    assert [walk(16, 0, 40, same)[1][0] for same in (0, 3, 4, 7)] == [3, 3, 2, 2]
-    assert walk(32, 4, 40, 7)[1][0] == 3 and walk(32, 0, 7, 7)[1][0] == 3 and walk(8, 0, 40, 7)[1][0] == 3 and walk(33, 0, 40, 7)[1][0] == 3
+    assert [walk(32, 0, 40, same)[1][0] for same in (0, 11, 12, 18, 19, 28)] == [3, 3, 2, 2, 1, 1]
+    assert [walk(16, 0, 40, same)[1][0] for same in (0, 11, 12, 28)] == [3, 3, 2, 2]
+    assert walk(32, 4, 40, 28)[1][0] == 3 and walk(32, 0, 7, 28)[1][0] == 3 and walk(8, 0, 40, 28)[1][0] == 3
+    assert walk(33, 0, 40, 28)[1][0] == 3
+
+
+def same_of(walk, tiles_per_expert):
+    """What the kernels count on the tile table of these experts; every entry that they read exists."""
+    table = np.repeat(np.arange(len(tiles_per_expert)), tiles_per_expert)
+    same = 0
+    for c in range(walk.lib.share_runs()):
+        first = walk.lib.first_of_run(len(table), c)
+        assert 0 <= first and first + 8 <= len(table)
+        run = table[first:first + 8]
+        same += int((run[1:] == run[:-1]).sum())
+    return same, len(table)
+
+
+def test_split_does_not_depend_on_the_order_of_the_experts(walk):
+    """Rare experts in front of heavy ones, behind them and among them; the first eight M-tiles alone told these apart.  (Few heavy experts
+    among many rare ones: which of them the runs meet is chance.)"""
+    rng = np.random.default_rng(1)
+    for tiles, split in (([1] * 8 + [8] * 8, True), ([1] * 12 + [9] * 3, True), ([1] * 40 + [8], False), ([1] * 100 + [5] * 8, False)):
+        for order in [tiles, tiles[::-1]] + ([rng.permutation(tiles) for _ in range(20)] if split else []):
+            same, m_tiles = same_of(walk, order)
+            for n_tiles in (16, 112):
+                assert (walk(n_tiles, 0, m_tiles, same)[1][0] != 3) == split, (n_tiles, tiles, same)
+
+
+def test_split_by_tiles_per_expert(walk):
+    """Two M-tiles an expert and more: split; four and more: by four, wherever the runs begin.  One: not split."""
+    for lead in range(9):                                     # shifts the phase of the runs
+        for n in (9, 16, 33, 64, 200):
+            of = lambda t: walk(112, 0, *same_of(walk, [1 + lead % t] + [t] * n)[::-1])[1][0]
+            assert of(1) == 3 and of(2) == 2 and of(4) == of(5) == of(9) == 1, (lead, n)
+
+
+def test_table_reads_stay_inside(walk):
+    for m_tiles in list(range(8, 400)) + [4096, 1 << 20]:
+        assert [walk.lib.first_of_run(m_tiles, c) for c in (0, walk.lib.share_runs() - 1)] == [0, m_tiles - 8]
