@@ -29,7 +29,7 @@ KERNEL_SOURCES = ["gemm_group0.hip", "gemm_group1.hip", "gemm_group2.hip", "gemm
                   "gemm_group5.hip", "gemm_group6.hip", "gemm_group7.hip", "stream_group0.hip", "stream_group1.hip",
                   "stream_group2.hip"]
 SOURCES = ["align.hip", "select.hip", "pack.hip", "fused.hip", "fp8.hip", "stream_selected.hip"] + KERNEL_SOURCES + ["cost_model.cpp"]
-RESOURCE_SOURCES = KERNEL_SOURCES + ["fp8.hip"]  # hold projection kernels of a tile family
+RESOURCE_SOURCES = KERNEL_SOURCES + ["fp8.hip", "stream_selected.hip"]  # hold projection kernels
 HEADERS = ["ramp_internal.h", "moe_gemm.h", "moe_pingpong.h", "moe_stream.h", "moe_decode.h", "moe_fp8_pingpong.h", "moe_fp8_stream.h", "fp8_format.h", "align_tiny.h", "tile_walk.h", "config_list.h", os.path.join(ROOT, "include", "ramp.h")]
 
 COMMON = ["-O3", "-fPIC", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-ffp-contract=off"]
@@ -37,7 +37,8 @@ COMMON = ["-O3", "-fPIC", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I
 HIP_FLAGS = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
              "-Wno-unused-command-line-argument"]
 FAMILIES = ("moe_gemm_kernel", "moe_pingpong_kernel", "moe_stream_kernel", "moe_fp8_kernel", "moe_fp8_pingpong_kernel",
-            "moe_fp8_stream_kernel", "moe_fp8_decode_up_kernel", "moe_fp8_decode_down_kernel")
+            "moe_fp8_stream_kernel", "moe_fp8_decode_up_kernel", "moe_fp8_decode_down_kernel", "moe_decode_up_kernel",
+            "moe_decode_down_kernel", "moe_stream_selected0_kernel", "moe_stream_selected1_kernel")
 
 
 def _hipcc() -> str:

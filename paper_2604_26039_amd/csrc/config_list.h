@@ -100,24 +100,24 @@
     X(16, 2, 2, 4, 4)         \
     X(16, 2, 2, 2, 4)
 
-// The stream tiles that one launch of the device-selected layer can hold together (stream_selected.hip): 8 or 4 wavefronts whose
-// operands and sums fit 128 registers, or nearly.
-#define RAMP_STREAM_SELECTED_GROUP(X) \
-    X(4, 2, 1, 8, 2)          \
-    X(8, 2, 1, 8, 2)          \
-    X(16, 2, 1, 8, 2)         \
-    X(16, 2, 1, 4, 2)         \
-    X(16, 2, 2, 4, 2)         \
-    X(16, 2, 4, 2, 2)         \
-    X(16, 2, 4, 1, 4)         \
-    X(16, 4, 2, 2, 2)         \
-    X(16, 4, 4, 1, 2)         \
-    X(32, 2, 1, 8, 2)         \
-    X(32, 2, 2, 4, 2)         \
-    X(32, 2, 4, 1, 2)         \
-    X(16, 2, 2, 4, 4)         \
-    X(16, 2, 2, 2, 4)         \
+// The stream tiles that one launch of the device-selected layer can hold together (stream_selected.hip), in two groups: those that do as
+// well in 128 registers as in their own kernels, of eight wavefronts or four; and those of four wavefronts that need 138.
+#define RAMP_STREAM_SELECTED_GROUP0(X) \
+    X(4, 2, 1, 8, 2)                   \
+    X(8, 2, 1, 8, 2)                   \
+    X(16, 2, 1, 8, 2)                  \
+    X(16, 2, 1, 4, 2)                  \
+    X(16, 2, 2, 4, 2)                  \
+    X(16, 2, 4, 2, 2)                  \
+    X(32, 2, 1, 8, 2)                  \
+    X(32, 2, 2, 4, 2)                  \
+    X(16, 2, 2, 4, 4)                  \
     X(16, 2, 1, 8, 4)
+#define RAMP_STREAM_SELECTED_GROUP1(X) \
+    X(16, 2, 4, 1, 4)                  \
+    X(16, 4, 2, 2, 2)                  \
+    X(16, 4, 4, 1, 2)                  \
+    X(16, 2, 2, 2, 4)
 
 // Stream configurations that also have the two-launch form for calls of at most 64 pairs (moe_decode.h):
 // X(bm, FBW, WF, WK, U) as above; listed as separate configurations (mode bit 0x2000).

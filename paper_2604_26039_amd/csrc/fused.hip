@@ -568,9 +568,9 @@ int enqueue_projections(const ramp_shape &s, const ramp_config &cfg, const Kerne
     return check_launch("moe_gemm_kernel<2>");
 }
 
-// Both projections of the streaming candidates of a device-selected call whose align result is there.
-int enqueue_selected_streams(const ramp_shape &s, int n_cand, const StreamChoices &choices, const unsigned blocks[2], const void *X,
-                             const float *topk_w, const void *packed_weights, char *base, float *y_buf, const int32_t *sel,
+// Both projections of the streaming candidates of one group of a device-selected call whose align result is there.
+int enqueue_selected_streams(const ramp_shape &s, int group, int n_cand, const StreamChoices &choices, const unsigned blocks[2],
+                             const void *X, const float *topk_w, const void *packed_weights, char *base, float *y_buf, const int32_t *sel,
                              hipStream_t st)
 {
     const PackedLayout L = packed_layout(s);
@@ -590,7 +590,7 @@ int enqueue_selected_streams(const ramp_shape &s, int n_cand, const StreamChoice
     g.F = s.I;
     {
         ProbeScope probe(2, st);
-        if (int rc = launch_stream_selected(1, g, base, 2 * s.I, n_cand, choices, blocks[0], st)) return rc;
+        if (int rc = launch_stream_selected(group, 1, g, base, 2 * s.I, n_cand, choices, blocks[0], st)) return rc;
     }
     g.wpacked = packed + L.w2_base_elems;
     g.expert_stride = L.w2_expert_elems;
@@ -598,7 +598,7 @@ int enqueue_selected_streams(const ramp_shape &s, int n_cand, const StreamChoice
     g.K = s.I;
     g.F = s.H;
     ProbeScope probe(3, st);
-    return launch_stream_selected(2, g, base, s.H, n_cand, choices, blocks[1], st);
+    return launch_stream_selected(group, 2, g, base, s.H, n_cand, choices, blocks[1], st);
 }
 
 }  // namespace
@@ -745,30 +745,34 @@ extern "C" int ramp_fused_moe_selected(const ramp_shape *shape, int n_cand, cons
         ProbeScope probe(1, st);
         if (int rc = launch_align_selected(topk_ids, s.T * s.k, s.E, topk_w, base, selected_idx, n_cand, choices, st)) return rc;
     }
-    // The weight-streaming candidates in one launch per projection, if there are two of them.
+    // The weight-streaming candidates of a group in one launch per projection, if there are two of them.
     StreamChoices streams = {};
-    unsigned stream_blocks[2] = {0, 0};
-    int n_streams = 0;
+    unsigned stream_blocks[kStreamGroups][2] = {};
+    int in_group[kStreamGroups] = {};
     for (int c = 0; c < n_cand; ++c) {
         streams.c[c].shape = !shared_align || runs_two_launches(*ki[c], s) ? -1 : stream_selected_shape(cfgs[c]);
-        if (streams.c[c].shape < 0) continue;
+        const int group = stream_selected_group(streams.c[c].shape);
+        if (group < 0) continue;
         const Workspace w = workspace_layout(s, cfgs[c]);
         const size_t m_tiles = w.cap / (size_t)cfgs[c].bm;
         streams.c[c] = StreamChoice{streams.c[c].shape, cfgs[c].bn, (int32_t)m_tiles, w.sorted, w.tile_expert, w.a_buf};
-        const size_t per_block = stream_selected_per_block(cfgs[c].waves);
+        const size_t per_block = (size_t)(stream_selected_waves(group) / cfgs[c].waves);
         const size_t tiles[2] = {m_tiles * (size_t)(2 * s.I / cfgs[c].bn), m_tiles * (size_t)(s.H / cfgs[c].bn)};
         for (int st2 = 0; st2 < 2; ++st2) {
             const unsigned blocks = (unsigned)((tiles[st2] + per_block - 1) / per_block);
-            if (blocks > stream_blocks[st2]) stream_blocks[st2] = blocks;
+            if (blocks > stream_blocks[group][st2]) stream_blocks[group][st2] = blocks;
         }
-        ++n_streams;
+        ++in_group[group];
     }
-    if (n_streams > 1) {
-        if (int rc = enqueue_selected_streams(s, n_cand, streams, stream_blocks, X, topk_w, packed_weights, base, y_buf, selected_idx, st))
+    for (int group = 0; group < kStreamGroups; ++group) {
+        if (in_group[group] < 2) continue;
+        if (int rc = enqueue_selected_streams(s, group, n_cand, streams, stream_blocks[group], X, topk_w, packed_weights, base, y_buf,
+                                              selected_idx, st))
             return rc;
     }
     for (int c = 0; c < n_cand; ++c) {
-        if (n_streams > 1 && streams.c[c].shape >= 0) continue;
+        const int group = stream_selected_group(streams.c[c].shape);
+        if (group >= 0 && in_group[group] > 1) continue;
         const Workspace w = workspace_layout(s, cfgs[c]);
         bool wrote_out = false;
         if (int rc = enqueue_projections(s, cfgs[c], *ki[c], w, X, topk_ids, topk_w, packed_weights, base, y_buf, out,

@@ -31,8 +31,9 @@ struct StreamTraits {
     static_assert(LDS_BYTES <= 64 * 1024, "reduction buffer too large");
 };
 
-// Work of one workgroup (or one of several that share a block) on M-tile x feature tile.
-template <int STAGE, int BM, int FBW, int WF, int WK, int U>
+// Work of one workgroup, or of one of several that share a block (SHARED), on M-tile x feature tile.  The others of a block have tiles of
+// their own, of which one may be past the real ones: every wavefront of a block meets the same barriers whatever its tile is, one if WK > 1.
+template <bool SHARED, int STAGE, int BM, int FBW, int WF, int WK, int U>
 __device__ __forceinline__ void stream_tile(const GemmArgs &a, float *red, int n_tile, int m_tile, int wave, int lane)
 {
     using ST = StreamTraits<BM, FBW, WF, WK, U>;
@@ -51,7 +52,10 @@ __device__ __forceinline__ void stream_tile(const GemmArgs &a, float *red, int n
         pair_of[nb] = a.sorted[m_tile * BM + (tr < BM ? tr : BM - 1)];
     }
     const int e = load_uniform_i32(a.tile_expert + m_tile);
-    if (e < 0) return;
+    if (e < 0) {
+        if (SHARED && WK > 1) __syncthreads();
+        return;
+    }
     const int K = a.K, KST = K / 32;
     const int f0 = n_tile * FEAT_PER_TILE + wf * FPW * 16;  // first output feature of this wavefront
     const uint16_t *wexp = a.wpacked + (size_t)e * a.expert_stride;
@@ -182,7 +186,7 @@ __global__ __launch_bounds__(WF *WK * 64) void moe_stream_kernel(GemmArgs a)
     if (launch_deselected(a.pred, a.pred_value)) return;
     const int n_tile = blockIdx.x % a.n_tiles;
     const int m_tile = blockIdx.x / a.n_tiles;
-    stream_tile<STAGE, BM, FBW, WF, WK, U>(a, red, n_tile, m_tile, threadIdx.x >> 6, threadIdx.x & 63);
+    stream_tile<false, STAGE, BM, FBW, WF, WK, U>(a, red, n_tile, m_tile, threadIdx.x >> 6, threadIdx.x & 63);
 }
 
 template <int BM, int FBW, int WF, int WK, int U>

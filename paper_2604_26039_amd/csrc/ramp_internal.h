@@ -167,8 +167,8 @@ constexpr int kModeGroupShift = 12;
 constexpr int kModeGroupMask = 0xF << kModeGroupShift;
 inline int group_m_of_mode(int mode) { const int v = (mode & kModeGroupMask) >> kModeGroupShift; return v ? (1 << v) : 0; }
 
-// The stream candidates of a device-selected call, for one launch per projection (stream_selected.hip): the position of a
-// candidate's tile in RAMP_STREAM_SELECTED_GROUP, or -1, and what differs between the candidates' arguments (byte offsets).
+// The stream candidates of a device-selected call that share launches (stream_selected.hip): what differs between their arguments (byte
+// offsets), and the number of a candidate's tile, -1 for one with launches of its own.
 struct StreamChoice {
     int32_t shape, bn, m_tiles_cap;
     size_t sorted, tile_expert, a_buf;
@@ -176,12 +176,14 @@ struct StreamChoice {
 struct StreamChoices {
     StreamChoice c[kMaxCandidates];
 };
-int stream_selected_shape(const ramp_config &cfg);  // -1: not a tile of that launch
-// args: those of the candidates, without what `choices` holds; features: 2 * I, or H
-int launch_stream_selected(int stage, const GemmArgs &args, char *base, int features, int n_cand, const StreamChoices &choices,
-                           unsigned blocks, hipStream_t stream);
-// Workgroups of a block of that launch's kernel for a tile of `waves` wavefronts
-constexpr int stream_selected_per_block(int waves) { return 8 / waves; }
+constexpr int kStreamGroups = 2;  // tiles of one group can share a launch
+int stream_selected_shape(const ramp_config &cfg);  // -1: a tile of no group
+int stream_selected_group(int shape);               // -1 of -1
+// Wavefronts of a block of the group's kernel; a tile of fewer shares it with others
+constexpr int stream_selected_waves(int group) { return group == 0 ? 8 : 4; }
+// args: those of the candidates, without what `choices` holds; features: 2 * I, or H; blocks: the most that a candidate of the group needs
+int launch_stream_selected(int group, int stage, const GemmArgs &args, char *base, int features, int n_cand,
+                           const StreamChoices &choices, unsigned blocks, hipStream_t stream);
 
 struct DecodeArgs;
 struct DecodeDownArgs;

@@ -132,6 +132,42 @@ def test_what_the_mode_bits_of_the_persistent_tiles_stand_for(H):
                 assert ("moe_pingpong_kernel" in bench.kernel_name(c)) == persistent
 
 
+def all_resources():
+    out = {}
+    for src in lib_build.RESOURCE_SOURCES:
+        with open(os.path.join(lib_build.OBJ_DIR, src + ".resources.json")) as f:
+            out.update({(r["family"], tuple(r["targs"])): r for r in json.load(f)})
+    return out
+
+
+def test_scratch_of_the_projection_kernels():
+    """Bytes of scratch per lane that the compiler reported: the 288-row persistent tile and the staged down-projections of 256 x 256 x 64
+    keep a few values there, no other kernel any."""
+    most = {("moe_pingpong_kernel", (1, 288, 256, 32)): 20, ("moe_pingpong_kernel", (2, 288, 256, 32)): 24, ("moe_gemm_kernel", (2, 256, 256, 64)): 72}
+    for (family, targs), r in all_resources().items():
+        assert r["scratch"] <= most.get((family, targs[:4]), 0), (family, targs, r)
+
+
+def test_tiles_of_a_shared_launch_keep_their_wavefronts():
+    """The kernels that hold several streaming tiles (stream_selected.hip): wavefronts on a unit, by registers and LDS, against those of a
+    tile's own kernel; a tile of fewer (88 registers and four wavefronts, 20 on its own) was measured."""
+    res = all_resources()
+    text = open(os.path.join(lib_build.CSRC, "config_list.h")).read()
+    fit = lambda r, waves: min(r["waves_per_simd"] * 4 // waves, 160 * 1024 // max(r["lds"], 1)) * waves
+    seen = 0
+    for group, waves in ((0, 8), (1, 4)):
+        block = text.split(f"#define RAMP_STREAM_SELECTED_GROUP{group}(X)")[1].split("#define")[0]
+        for targs in re.findall(r"X\((\d+), (\d+), (\d+), (\d+), (\d+)\)", block):
+            targs = tuple(int(v) for v in targs)
+            assert waves % (targs[2] * targs[3]) == 0
+            for stage in (1, 2):
+                shared = fit(res[f"moe_stream_selected{group}_kernel", (stage,)], waves)
+                own = fit(res["moe_stream_kernel", (stage,) + targs], targs[2] * targs[3])
+                assert shared >= min(own, 16 if targs == (16, 2, 1, 4, 2) else 64, 12 if group == 1 else 64), (targs, stage)
+                seen += 1
+    assert seen == 28
+
+
 def test_fp8_wave_capacity_follows_from_the_registers_and_lds_of_the_kernels():
     """W(c) / 256 by hand: 512 registers per SIMD lane (VGPRs and AGPRs, blocks of 8), 4 SIMDs, 160 KB of LDS; persistent: 1."""
     with open(os.path.join(lib_build.OBJ_DIR, "fp8.hip.resources.json")) as f:
