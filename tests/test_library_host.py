@@ -587,3 +587,16 @@ def test_fitted_table_round_trip(tmp_path):
     other.cfgs = other.cfgs[1:] + other.cfgs[:1]
     with pytest.raises(ValueError):
         tuner.load_model(path, other)
+
+
+def test_stream_handles_with_and_without_the_raw_getter(monkeypatch):
+    """The current stream of the current device, by the handle or, in a torch without that function, by its object; explicit ones as given."""
+    import types
+    import torch
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    monkeypatch.setattr(ramp, "_raw_stream", lambda device: 1000 + device)
+    assert ramp._stream(None) == 1003
+    monkeypatch.setattr(ramp, "_raw_stream", None)
+    assert ramp._stream(None) == 77
+    assert ramp._stream(types.SimpleNamespace(cuda_stream=5)) == 5 and ramp._stream(9) == 9
