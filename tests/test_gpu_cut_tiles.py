@@ -16,6 +16,18 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("m_tiles", [1, 11, 32, 43, 45, 88, 107, 128, 132, 175, 260])
 @pytest.mark.parametrize("E,H,I", [(1, 768, 384), (3, 640, 384)])
 def test_every_element(m_tiles, E, H, I):
+    against_a_tile_that_is_not_cut(m_tiles, E, H, I)
+
+
+# Rounds that are split between the XCDs, with and without cut tiles behind them: 32 N-tiles of the up-projection (a block of one M-tile;
+# split by four) and 16 of the up- or the down-projection (a block of two), 128-row and 256-row tiles; one expert, and three
+@pytest.mark.parametrize("m_tiles,E,H,I", [(16, 1, 512, 4096), (18, 1, 512, 4096), (18, 3, 512, 4096), (34, 1, 512, 2048), (36, 3, 512, 2048),
+                                           (17, 1, 4096, 384), (34, 1, 4096, 384), (37, 3, 4096, 384), (64, 1, 4096, 384)])
+def test_every_element_of_split_rounds(m_tiles, E, H, I):
+    against_a_tile_that_is_not_cut(m_tiles, E, H, I)
+
+
+def against_a_tile_that_is_not_cut(m_tiles, E, H, I):
     s = synth.Shape("cut", H, I, E, 1)
     T = 128 * m_tiles - 37
     rng = np.random.default_rng(m_tiles)

@@ -44,3 +44,27 @@ def test_against_the_oracle(H, I, k, counts):
     for c in cfgs:
         print(f"case fp8 H={H} I={I} k={k} T={T} {c}", flush=True)
         assert torch.equal(F.run(c, ids, w).view(torch.int16), want.view(torch.int16)), f"{c}"
+
+
+def test_many_tiles_per_workgroup_run_twice():
+    """Three turns and more of 128-row tiles (fewer of the others) over two N-tiles, the second half empty: the loads of the next tile
+    follow a whole tile and half a one in turn.  Every element, twice: FP8 bit for bit, bf16 against a tile that divides H."""
+    s = synth.Shape("half", 384, 384, 24, 1)
+    T = 60_000
+    ids, w = synth.routing(T, s, 0.7, seed=3)
+    for fp8 in (False, True):
+        mod = test_gpu_fp8 if fp8 else test_gpu_moe
+        L = (mod.Fp8Layer if fp8 else mod.Layer)(s, T, seed=9, x_std=1.5)
+        cfgs = (ramp.fp8_configs if fp8 else ramp.configs)(L.rs)
+        plain = next(c for c in cfgs if c.bm == (32 if fp8 else 128) and c.bn == 128 and not c.mode & (0x700 | HALF))
+        want = L.run(plain, ids, w).clone()
+        rows = [0, 1, T // 2, T - 1]
+        mod.assert_close(want[torch.tensor(rows, device="cuda:0")], L.oracle_rows(ids, w, rows=rows), f"{plain}")
+        for c in [c for c in cfgs if c.mode & HALF]:
+            print(f"case fp8={fp8} {c}", flush=True)
+            outs = [L.run(c, ids, w).clone() for _ in range(2)]
+            assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16)), f"{c}"
+            if fp8:
+                assert torch.equal(outs[0].view(torch.int16), want.view(torch.int16)), f"{c}"
+            else:
+                assert (outs[0].float() - want.float()).norm() <= 5e-3 * want.float().norm(), f"{c}"

@@ -10,8 +10,8 @@ from test_gpu_moe import DEV, Layer
 pytestmark = pytest.mark.gpu
 
 
-# one and several tiles of a block's workgroups; an odd number of tiles for the blocks that hold two; dropped pairs
-@pytest.mark.parametrize("H,I,E,k,T", [(256, 128, 6, 3, 23), (384, 640, 24, 6, 41), (1152, 256, 3, 2, 300)])
+# one and several tiles of a block's workgroups; an odd number of tiles for the blocks that hold two; dropped pairs; bf16 pair rows (last)
+@pytest.mark.parametrize("H,I,E,k,T", [(256, 128, 6, 3, 23), (384, 640, 24, 6, 41), (1152, 256, 3, 2, 300), (4096, 128, 6, 4, 600)])
 def test_every_streaming_candidate(H, I, E, k, T):
     s = synth.Shape("streams", H, I, E, k)
     L = Layer(s, T, seed=H, x_std=1.5)
