@@ -39,12 +39,12 @@ FP8_PEAK_PFLOPS = 5.0    # dense FP8
 # per-kernel table.  Keyed by (model, T, beta), one entry per tile configuration (bm, bn, bk, waves, stages) that was
 # profiled; other workloads, or another dispatched configuration, report null.
 RECORDED_TRAFFIC = {
-    ("dsv3", 8192, "1.0"): [(16.24e9 + 286.7e6, (288, 256, 32, 8, 4), "profiles/dsv3_T8192_uniform_pingpong_288x256_272x256_256x256_trace_traffic_sq.md"),
-                            (17.98e9 + 278.7e6, (272, 256, 32, 8, 4), "profiles/dsv3_T8192_uniform_pingpong_288x256_272x256_256x256_trace_traffic_sq.md")],
-    ("dsv3", 2048, "0.2"): [(5.43e9 + 68.8e6, (256, 256, 32, 8, 4), "profiles/dsv3_T2048_beta02_and_mixtral_T8192_pingpong_256x256_trace_traffic_sq.md")],
-    ("mixtral", 8192, "1.0"): [(16.56e9 + 471.6e6, (256, 256, 32, 8, 4), "profiles/dsv3_T2048_beta02_and_mixtral_T8192_pingpong_256x256_trace_traffic_sq.md")],
-    ("qwen3", 8192, "1.0"): [(1.69e9 + 104.0e6, (272, 256, 32, 8, 4), "profiles/qwen3_T8192_and_olmoe_T4096_pingpong_trace_traffic_sq.md")],
-    ("olmoe", 4096, "1.0"): [(1.14e9 + 68.1e6, (256, 256, 32, 8, 4), "profiles/qwen3_T8192_and_olmoe_T4096_pingpong_trace_traffic_sq.md")],
+    ("dsv3", 8192, "1.0"): [(16.27e9 + 278.7e6, (288, 256, 32, 8, 4), "profiles/dsv3_T8192_uniform_pingpong_288x256_272x256_256x256_trace_traffic_sq.md"),
+                            (18.01e9 + 276.8e6, (272, 256, 32, 8, 4), "profiles/dsv3_T8192_uniform_pingpong_288x256_272x256_256x256_trace_traffic_sq.md")],
+    ("dsv3", 2048, "0.2"): [(5.75e9 + 68.8e6, (256, 256, 32, 8, 4), "profiles/dsv3_T2048_beta02_and_mixtral_T8192_pingpong_256x256_trace_traffic_sq.md")],
+    ("mixtral", 8192, "1.0"): [(11.21e9 + 471.6e6, (256, 256, 32, 8, 4), "profiles/dsv3_T2048_beta02_and_mixtral_T8192_pingpong_256x256_trace_traffic_sq.md")],
+    ("qwen3", 8192, "1.0"): [(1.65e9 + 102.6e6, (272, 256, 32, 8, 4), "profiles/qwen3_T8192_and_olmoe_T4096_pingpong_trace_traffic_sq.md")],
+    ("olmoe", 4096, "1.0"): [(1.15e9 + 68.1e6, (256, 256, 32, 8, 4), "profiles/qwen3_T8192_and_olmoe_T4096_pingpong_trace_traffic_sq.md")],
 }
 
 # Largest point of every other model shape, reported next to the headline.

@@ -221,13 +221,12 @@ int ramp_fused_moe_fp8(const ramp_shape *shape, const ramp_config *cfg,
  * RAMP_CM_PAIRS: the fourth term is l = P = sum_e n_e, the routed pairs, in place of ln(g+1) and
  *   always fitted: gather, SwiGLU, per-pair rows and the combine cost time per pair whatever the
  *   tiling, which g (padded tiles) does not separate from the padding.
- * RAMP_CM_ROUNDS: the wave term counts whole hand-out rounds, w = g_r/W with
- *   g_r = sum over the two launches of ceil(M_tiles/R)*R*ntiles_launch (ramp_config_rounds gives R and
- *   ntiles_launch).  A persistent kernel's fixed workgroups take the M-tiles in rounds of R = 8*group_m over the
- *   8 XCDs, so its time steps at multiples of R M-tiles: the wave staircase of Sec. 4.2 ("time jumps at wave
- *   boundaries") in the units of this kernel's workgroup -> tile map, and what tells the GROUP_M block shapes of
- *   one tile apart.  R = 1 (g_r = g) for kernels whose workgroups are dispatched tile by tile.  Needs the
- *   *_rounds entry points below. */
+ * RAMP_CM_ROUNDS: the wave term counts whole rounds of a persistent kernel's workgroup -> tile map, w = g_r/W with
+ *   g_r = sum over the two launches of ceil(M_tiles/R)*R*ntiles_launch (ramp_config_rounds gives R = 8*group_m and
+ *   ntiles_launch; R = 1, so g_r = g, for kernels whose workgroups are dispatched tile by tile): the wave staircase of
+ *   Sec. 4.2 in the units of the map, and what tells the GROUP_M block shapes of one tile apart.  A regressor of the fit,
+ *   kept for tables fitted with it: the kernels share what whole rounds leave evenly between the XCDs and cut the tiles of
+ *   a part turn, so their time steps less than g_r does.  Needs the *_rounds entry points below. */
 enum { RAMP_CM_EQ6 = 0, RAMP_CM_RELATIVE = 1, RAMP_CM_DISTINCT_TILES = 2, RAMP_CM_WAVE_FLOOR = 4, RAMP_CM_PAIRS = 8,
        RAMP_CM_ROUNDS = 16 };
 

@@ -32,9 +32,9 @@
 // converts finite rows; rows with an infinity or NaN take the general conversion.  Up-projection, kernel trace: Mixtral-shaped
 // T = 8192 1565 -> 1535 us, OLMoE-shaped T = 1024 of 16 experts (128-row tile) 54.6 -> 53.2, Qwen3-shaped T = 3500 120.7 -> 119.5.
 //
-// Measured: Mixtral-shaped layer, T = 8192 (5.8 TFLOP), 256-row tile, kernel trace: up-projection 1535 us = 2.51 PFLOP/s and
-// down-projection 775 us = 2.48 PFLOP/s, against 3073 + 320 (quantising pass) + 1302 us of the 128 x 256 tile with one barrier per
-// slice.  The matrix pipes are busy 64 to 66 % of the up-projection's clocks and 75 to 78 % of the down-projection's, at 1.3 to 1.8 GHz:
+// Measured: Mixtral-shaped layer, T = 8192 (5.8 TFLOP), 256-row tile, kernel trace: up-projection 1520 to 1580 us = 2.44 to 2.53 PFLOP/s
+// and down-projection 770 to 800 us = 2.40 to 2.50 PFLOP/s, against 3073 + 320 (quantising pass) + 1302 us of the 128 x 256 tile with one
+// barrier per slice.  The matrix pipes are busy 68 % of the up-projection's clocks and 78 % of the down-projection's, at 1.5 to 1.8 GHz:
 // the chip holds these kernels at its power limit, so bytes that don't cross the fabric come back as clock.  What the loop waits
 // for is its M phase, LDS reads at 128 bytes a clock and the issue of a 1 KB load every 16 clocks.
 #pragma once

@@ -190,8 +190,8 @@ def profile(layers: LayerSet, fam: Family, points: Sequence[Point], log=None, **
 
 
 # The dispatch model used on this chip: Eq. 6 fitted on relative residuals, with the traffic term on distinct weight
-# tiles, a wave term that has a floor of one wave and counts whole hand-out rounds of the persistent kernels, and the
-# routed pairs as fourth term.  EQ6 (= 0) is the model exactly as printed.
+# tiles, a wave term that has a floor of one wave and counts whole rounds of the persistent kernels' tile map (a regressor:
+# the kernels share the last round out evenly), and the routed pairs as fourth term.  EQ6 (= 0) is the model exactly as printed.
 MI355X_MODEL = ramp.CM_RELATIVE | ramp.CM_DISTINCT_TILES | ramp.CM_WAVE_FLOOR | ramp.CM_PAIRS | ramp.CM_ROUNDS
 
 
